@@ -12,17 +12,14 @@ constexpr int kAmgMaxLevels = 8;
 constexpr int kAmgCoarseMax = 512;  // the coarsest operator is inverted densely
 
 // A sparse matrix of the hierarchy.  lpr = 1: the sliced ELLPACK layout of
-// the solver (kSell rows per slice, column-major inside a slice, padding
-// entries 0 with column 0; one lane per row), for short rows.  lpr > 1
-// (a power of two up to 64): CSR with lpr lanes per row and a shuffle
-// reduction, for the long rows of the Galerkin operators and restrictions.
+// the solver (SellView, one lane per row), for short rows; packed on the
+// finest level where K is.  lpr > 1 (a power of two up to 64): CSR with lpr
+// lanes per row and a shuffle reduction, for the long rows of the Galerkin
+// operators and restrictions.
 struct SellMat {
   int64_t nrows, nslices;  // (nslices: SELL only)
   int lpr;
-  const int32_t* sptr;     // SELL slice offsets, or CSR row offsets [nrows+1]
-  const int32_t* col;
-  const double* val;
-  const float* val32;      // the same values rounded to FP32
+  SellView v;              // (CSR: sptr holds the row offsets [nrows + 1])
 };
 
 // One level of the hierarchy.  Level 0 is K on the free nodes; b of level 0

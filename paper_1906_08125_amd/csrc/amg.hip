@@ -299,33 +299,39 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
                      AmgDev& d, std::string& msg) {
   d = AmgDev{};
   hipError_t e;
-  // level 0: K on the free nodes, from the device copy
+  // level 0: K on the free nodes without its zeros, from the device copy
   const int64_t ns = m.k_nslices;
   std::vector<int32_t> sptr(ns + 1);
-  if ((e = hipMemcpyAsync(sptr.data(), m.k_sptr, sizeof(int32_t) * (ns + 1),
+  if ((e = hipMemcpyAsync(sptr.data(), m.kz.sptr, sizeof(int32_t) * (ns + 1),
                           hipMemcpyDeviceToHost, s)) != hipSuccess ||
       (e = hipStreamSynchronize(s)) != hipSuccess)
     return e;
   const int64_t np = sptr[ns];
-  std::vector<int32_t> scol(np);
-  std::vector<double> sval(np);
-  if ((e = hipMemcpyAsync(scol.data(), m.k_scol, sizeof(int32_t) * np,
-                          hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(sval.data(), m.k_sval, sizeof(double) * np,
-                          hipMemcpyDeviceToHost, s)) != hipSuccess ||
+  const bool packed = m.kz.code != nullptr;
+  std::vector<int32_t> scol(np);   // (packed: the code words)
+  std::vector<double> sval(packed ? kDictMax : np);
+  if ((e = hipMemcpyAsync(scol.data(), packed ? (const void*)m.kz.code : m.kz.col,
+                          sizeof(int32_t) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+      (e = hipMemcpyAsync(sval.data(), packed ? m.kz.dict : m.kz.val,
+                          sizeof(double) * sval.size(), hipMemcpyDeviceToHost, s)) !=
+          hipSuccess ||
       (e = hipStreamSynchronize(s)) != hipSuccess)
     return e;
   std::vector<HCsr> A(1);
   A[0].n = A[0].m = m.n_free;
   A[0].rp.assign(m.n_free + 1, 0);
+  A[0].ci.reserve(np);
+  A[0].v.reserve(np);
   for (int64_t r = 0; r < m.n_free; ++r) {
     const int64_t sl = r / kSell, lane = r % kSell;
     const int64_t w = (sptr[sl + 1] - sptr[sl]) / kSell;
     for (int64_t j = 0; j < w; ++j) {
       const int64_t p = sptr[sl] + j * kSell + lane;
-      if (sval[p] != 0.0) {  // (padding entries are zeros)
-        A[0].ci.push_back(scol[p]);
-        A[0].v.push_back(sval[p]);
+      const uint32_t c = (uint32_t)scol[p];
+      const double v = packed ? sval[c >> kColBits] : sval[p];
+      if (v != 0.0) {  // (padding entries are zeros)
+        A[0].ci.push_back((int32_t)(packed ? c & ((1u << kColBits) - 1) : c));
+        A[0].v.push_back(v);
       }
     }
     A[0].rp[r + 1] = (int64_t)A[0].ci.size();
@@ -392,23 +398,23 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     if (out.lpr == 1) {
       const HSell S = to_sell(M);
       out.nslices = S.nslices;
-      out.sptr = (const int32_t*)up(S.sptr.data(), sizeof(int32_t) * S.sptr.size());
-      out.col = (const int32_t*)up(S.col.data(), sizeof(int32_t) * std::max<size_t>(S.col.size(), 1));
-      out.val = (const double*)up(S.val.data(), sizeof(double) * std::max<size_t>(S.val.size(), 1));
+      out.v.sptr = (const int32_t*)up(S.sptr.data(), sizeof(int32_t) * S.sptr.size());
+      out.v.col = (const int32_t*)up(S.col.data(), sizeof(int32_t) * std::max<size_t>(S.col.size(), 1));
+      out.v.val = (const double*)up(S.val.data(), sizeof(double) * std::max<size_t>(S.val.size(), 1));
       const std::vector<float> v32(S.val.begin(), S.val.end());
-      out.val32 = (const float*)up(v32.data(), sizeof(float) * std::max<size_t>(v32.size(), 1));
+      out.v.val32 = (const float*)up(v32.data(), sizeof(float) * std::max<size_t>(v32.size(), 1));
       // (synchronized before the host copies go out of scope)
-      return out.sptr && out.col && out.val && out.val32 &&
+      return out.v.sptr && out.v.col && out.v.val && out.v.val32 &&
              hipStreamSynchronize(s) == hipSuccess;
     }
     std::vector<int32_t> rp(M.rp.begin(), M.rp.end());
     out.nslices = 0;
-    out.sptr = (const int32_t*)up(rp.data(), sizeof(int32_t) * rp.size());
-    out.col = (const int32_t*)up(M.ci.data(), sizeof(int32_t) * std::max<size_t>(M.ci.size(), 1));
-    out.val = (const double*)up(M.v.data(), sizeof(double) * std::max<size_t>(M.v.size(), 1));
+    out.v.sptr = (const int32_t*)up(rp.data(), sizeof(int32_t) * rp.size());
+    out.v.col = (const int32_t*)up(M.ci.data(), sizeof(int32_t) * std::max<size_t>(M.ci.size(), 1));
+    out.v.val = (const double*)up(M.v.data(), sizeof(double) * std::max<size_t>(M.v.size(), 1));
     const std::vector<float> v32(M.v.begin(), M.v.end());
-    out.val32 = (const float*)up(v32.data(), sizeof(float) * std::max<size_t>(v32.size(), 1));
-    return out.sptr && out.col && out.val && out.val32 &&
+    out.v.val32 = (const float*)up(v32.data(), sizeof(float) * std::max<size_t>(v32.size(), 1));
+    return out.v.sptr && out.v.col && out.v.val && out.v.val32 &&
            hipStreamSynchronize(s) == hipSuccess;
   };
   d.n_levels = L;
@@ -416,8 +422,7 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
   for (int l = 0; l < L; ++l) {
     AmgLevel& lv = d.lv[l];
     if (l == 0) {
-      lv.A = SellMat{m.n_free, m.k_nslices, 1, m.k_sptr, m.k_scol, m.k_sval,
-                     m.k_sval32};
+      lv.A = SellMat{m.n_free, m.k_nslices, 1, m.kz};
       lv.invdiag = m.invdiag;
       lv.invdiag32 = m.invdiag32;
     } else {

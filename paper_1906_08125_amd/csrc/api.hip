@@ -161,19 +161,16 @@ fp::CgArgs cg_args(const pic_mesh* h, const int64_t* charge, double w_sp,
   a.E = E;
   a.x = h->cg_vec[1];
   a.r = h->cg_vec[2];
-  a.u = h->cg_vec[3];
-  a.w = h->cg_vec[4];
-  a.p = h->cg_vec[5];
-  a.s = h->cg_vec[6];
+  a.p = h->cg_vec[3];
+  a.rec0 = h->cg_rec[0];
+  a.rec1 = h->cg_rec[1];
+  a.u = h->cg_rec[0];
+  a.w = h->cg_rec[0] + h->dm.n_free;
+  a.s = h->cg_rec[0] + 2 * h->dm.n_free;
   a.bprev = h->cg_bprev;
   a.mixed = prm->precision == PIC_MIXED;
   a.e32 = e32;
   a.inner_tol = prm->inner_tol;
-  a.r32 = h->cg_vec32[0];
-  a.u32 = h->cg_vec32[1];
-  a.w32 = h->cg_vec32[2];
-  a.p32 = h->cg_vec32[3];
-  a.s32 = h->cg_vec32[4];
   a.part = h->cg_part;
   a.G = h->cg_grid;
   a.ctrl = h->cg_ctrl;
@@ -250,7 +247,9 @@ hipError_t iterate_graphs(pic_mesh* h, const fp::CgArgs& a0, int n, hipStream_t 
   if (!h->cap_stream &&
       (e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking)) != hipSuccess)
     return e;
-  for (int bit = 8; bit >= 0; --bit) {
+  // (Jacobi iterations come in pairs, even and odd: see k_cg_iter)
+  if (!a.amg) n += n & 1;
+  for (int bit = 8; bit >= (a.amg ? 0 : 1); --bit) {
     const int cnt = 1 << bit;
     while (n >= cnt) {
       hipGraphExec_t exec = nullptr;
@@ -338,7 +337,7 @@ hipError_t solve_finish(pic_mesh* h, const fp::CgArgs& a, int spec,
   hipError_t e = cg_wait(h, seq, s, r);
   if (e != hipSuccess) return e;
   if (first_state) *first_state = r.state;
-  // a lean first pass has left x, u and the start's product undone
+  // a lean first pass has left x and the start's product undone
   bool prep = a.lean && r.state == fp::CG_ITER;
   int batch = spec, rounds = 0;
   for (int guard = 0; guard < (1 << 20); ++guard) {
@@ -353,11 +352,13 @@ hipError_t solve_finish(pic_mesh* h, const fp::CgArgs& a, int spec,
       // stops inside it comes back tested.  An AMG iteration is some fifteen
       // dependent launches and a solve needs few: after a speculated round
       // the next ones run 1, 2, 4, ... iterations (launches past the stop
-      // cost as much as working ones); Jacobi rounds start at 8.
+      // cost as much as working ones); Jacobi rounds start at 8 and stop
+      // doubling at 64: a round costs the host's wait and a re-check, some
+      // 30 us, and an iteration past the stop 4.
       if (a.amg)
         batch = rounds == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * batch, 32);
       else
-        batch = batch < 8 ? 8 : std::min(2 * batch, 256);
+        batch = batch < 8 ? 8 : std::min(2 * batch, 64);
       ++rounds;
       if (prep) {
         if ((e = fp::cg_launch_lean_iter(a, s)) != hipSuccess) return e;
@@ -1672,6 +1673,7 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
         fp::CgBatch ca = cb;
         ca.map = batch_map(c_cg, jac_on);
         ca.mask = 0;
+        c_jac += c_jac & 1;
         if ((r = fp::cg_batch_iters(ca, ca.map.off[ca.map.n_seg], c_jac, s)) != hipSuccess)
           return r;
         for (int i = 0; i < n; ++i)

@@ -63,6 +63,24 @@ struct alignas(64) TetGeom32 {
 };
 static_assert(sizeof(TetGeom32) == 64, "TetGeom32 is half a line");
 
+// A sparse matrix in sliced ELLPACK (kSell rows per slice, column-major
+// inside a slice) in one of two forms.  Packed (code != null): one 32-bit
+// word per entry, the column in the low kColBits bits and above them the
+// entry's position in a table of the matrix's distinct values -- exact, and
+// a third of the 12 bytes of a column and an FP64 value.  Plain: col and
+// val (val32: rounded to FP32).  Padding entries have value 0.
+constexpr int kColBits = 24;
+constexpr int kDictMax = 1 << (32 - kColBits);  // table entries; entry 0 is 0
+struct SellView {
+  const int32_t* sptr;     // [slices + 1] offsets
+  const uint32_t* code;
+  const double* dict;      // [kDictMax]
+  const float* dict32;
+  const int32_t* col;
+  const double* val;
+  const float* val32;
+};
+
 struct DevMesh {
   int64_t n_nodes, n_tets, n_free, nnz, nnz_field, n_emit;
   double Lx, Ly, z_top;
@@ -84,10 +102,10 @@ struct DevMesh {
   // small sliced ELLPACK.
   int64_t k_nslices, k_np, d_nslices, d_np;
   const int32_t* k_sptr;   // [k_nslices + 1] slice offsets
-  const int32_t* k_scol;   // free-index columns
-  const int32_t* k_ncol;   // the same columns as node ids
+  const int32_t* k_ncol;   // columns as node ids
   const double* k_sval;
-  const float* k_sval32;
+  // K without its exact zeros, free-index columns (see SellView)
+  SellView kz;
   const double* r_sval;    // [3][k_np] R on the free rows
   const float* r_sval32;   // [3][k_np]
   const int32_t* d_sptr;   // [d_nslices + 1]

@@ -19,10 +19,12 @@ struct pic_mesh {
   bool ws_dry = false;
   int device = 0;
   int n_cu = 0;
-  // solver scratch: b, x, r, u, w, p, s (f64) and the partial sums
-  double* cg_vec[7] = {};
+  // solver scratch: b, x, r, p (f64), the two record arrays of the Jacobi
+  // recursion (the AMG one keeps u, w and s in the first) and the partial
+  // sums
+  double* cg_vec[4] = {};
   double* cg_bprev = nullptr;          // right-hand side of the last pass
-  float* cg_vec32[5] = {};             // r, u, w, p, s of the FP32 recursion
+  double* cg_rec[2] = {};              // [4 n_free] each
   double* cg_part = nullptr;
   int cg_grid = 0;
   fp::CgCtrl* cg_ctrl = nullptr;       // device control word

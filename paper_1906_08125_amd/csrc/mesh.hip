@@ -20,6 +20,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "mesh.h"
@@ -473,10 +474,11 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
       }
     }
   }
-  std::vector<int32_t> k_sptr, k_scol, k_ncol, d_sptr, d_ncol, k_sptr2, t_sptr, t_ncol;
+  std::vector<int32_t> k_sptr, k_ncol, d_sptr, d_ncol, k_sptr2, t_sptr, t_ncol;
   std::vector<double> rt_sval, t_sval;
   std::vector<double> k_sval, r_sval, d_sval;
-  const int64_t k_np = to_sell(rowptr, col, {&val}, NF, 0, k_sptr, k_scol, k_sval);
+  std::vector<int32_t> unused_cols;
+  const int64_t k_np = to_sell(rowptr, col, {&val}, NF, 0, k_sptr, unused_cols, k_sval);
   {
     to_sell(rowptr, ncol, {&rf[0], &rf[1], &rf[2]}, NF, free2node.empty() ? 0 : free2node[0],
             k_sptr2, k_ncol, r_sval);
@@ -484,7 +486,6 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   const int64_t d_np = to_sell(drow, dcol, {&dv[0], &dv[1], &dv[2]}, ND,
                                free2node.empty() ? 0 : free2node[0], d_sptr, d_ncol, d_sval);
   {
-    std::vector<int32_t> unused_cols;
     to_sell(rowptr, col, {&rtv[0], &rtv[1], &rtv[2]}, NF, 0, k_sptr2, unused_cols, rt_sval);
   }
   const int32_t pad_dir = dir_nodes.empty() ? 0 : dir_nodes[0];
@@ -493,6 +494,57 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   if (k_np >= (1ll << 31) || d_np >= (1ll << 31)) {
     msg = "mesh_create: padded matrix too large for 32-bit offsets";
     return PIC_E_ARG;
+  }
+  // K without its exact zeros for the products of the solver (on the Kuhn
+  // grids 7 of the 15 entries of an interior row remain: the edges along
+  // the cubes' diagonals carry no coupling), packed when the columns fit
+  // kColBits bits and the values fit the table (9 distinct ones on the
+  // production tip; a mesh whose coordinates round keeps the plain form)
+  std::vector<int32_t> z_sptr, z_col;
+  std::vector<uint32_t> z_code;
+  std::vector<double> z_val, z_dict;
+  {
+    std::vector<int32_t> zrow(NF + 1, 0), zc;
+    std::vector<double> zv;
+    zc.reserve(col.size());
+    zv.reserve(col.size());
+    for (int64_t r = 0; r < NF; ++r) {
+      for (int32_t k = rowptr[r]; k < rowptr[r + 1]; ++k)
+        if (val[k] != 0.0) {
+          zc.push_back(col[k]);
+          zv.push_back(val[k]);
+        }
+      zrow[r + 1] = (int32_t)zc.size();
+    }
+    const int64_t zp = to_sell(zrow, zc, {&zv}, NF, 0, z_sptr, z_col, z_val);
+    if (NF <= (1 << kColBits)) {
+      std::unordered_map<uint64_t, uint32_t> at;
+      z_dict.assign(kDictMax, 0.0);
+      z_code.assign(std::max<int64_t>(zp, 1), 0);
+      uint64_t last = 0;    // (runs of one value are the rule)
+      uint32_t last_c = 0;
+      at[0] = 0;            // +0.0, the padding
+      for (int64_t q = 0; q < zp; ++q) {
+        uint64_t b;
+        std::memcpy(&b, &z_val[q], sizeof b);
+        if (b != last) {
+          const auto hit = at.find(b);
+          if (hit != at.end()) {
+            last_c = hit->second;
+          } else {
+            last_c = (uint32_t)at.size();
+            if (last_c >= (uint32_t)kDictMax) {
+              z_code.clear();
+              break;
+            }
+            at[b] = last_c;
+            z_dict[last_c] = z_val[q];
+          }
+          last = b;
+        }
+        z_code[q] = (uint32_t)z_col[q] | (last_c << kColBits);
+      }
+    }
   }
   // 6. Neumann load per unit E0 on the top plane
   for (int64_t t = 0; t < T; ++t)
@@ -652,16 +704,25 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   M.bstart = upload(h, bstart, err);
   M.bitem = upload(h, bitem, err);
   {
-    std::vector<float> k_sval32(k_sval.begin(), k_sval.end());
+    M.kz.sptr = upload(h, z_sptr, err);
+    if (!z_code.empty()) {
+      const std::vector<float> z_dict32(z_dict.begin(), z_dict.end());
+      M.kz.code = upload(h, z_code, err);
+      M.kz.dict = upload(h, z_dict, err);
+      M.kz.dict32 = upload(h, z_dict32, err);
+    } else {
+      const std::vector<float> z_val32(z_val.begin(), z_val.end());
+      M.kz.col = upload(h, z_col, err);
+      M.kz.val = upload(h, z_val, err);
+      M.kz.val32 = upload(h, z_val32, err);
+    }
     std::vector<float> r_sval32(r_sval.begin(), r_sval.end());
     std::vector<float> d_sval32(d_sval.begin(), d_sval.end());
     M.k_nslices = (int64_t)k_sptr.size() - 1;
     M.k_np = k_np;
     M.k_sptr = upload(h, k_sptr, err);
-    M.k_scol = upload(h, k_scol, err);
     M.k_ncol = upload(h, k_ncol, err);
     M.k_sval = upload(h, k_sval, err);
-    M.k_sval32 = upload(h, k_sval32, err);
     M.r_sval = upload(h, r_sval, err);
     M.r_sval32 = upload(h, r_sval32, err);
     M.d_nslices = (int64_t)d_sptr.size() - 1;
@@ -695,9 +756,9 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   h->n_dir = (int64_t)dir_nodes.size();
   // solver scratch
   const size_t vb = sizeof(double) * (size_t)std::max<int64_t>(NF, 1);
-  for (int k = 0; k < 7; ++k) h->cg_vec[k] = (double*)dev_alloc(h, vb, err);
+  for (double*& v : h->cg_vec) v = (double*)dev_alloc(h, vb, err);
   h->cg_bprev = (double*)dev_alloc(h, vb, err);
-  for (int k = 0; k < 5; ++k) h->cg_vec32[k] = (float*)dev_alloc(h, vb / 2, err);
+  for (double*& v : h->cg_rec) v = (double*)dev_alloc(h, 4 * vb, err);
   int dev = 0, ncu = 0;
   if (err == hipSuccess) err = hipGetDevice(&dev);
   if (err == hipSuccess) err = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);

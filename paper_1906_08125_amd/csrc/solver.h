@@ -17,9 +17,10 @@ struct CgCtrl {
   double relres;        // last true relative residual
   double rstart;        // ||r|| at the last (re)start (mixed inner target)
   double alpha[2], gamma[2];
-  // iteration counters of batched launches (the host does not track each
-  // instance): it_a is read by upd and written by spmv, it_b the reverse,
-  // so no kernel reads a counter that the same launch writes
+  // iteration counters (the host does not track them).  Jacobi: the even
+  // iterations read it_a and write it_b, the odd ones the reverse; AMG: the
+  // V-cycle and the product read it_a and the update writes it.  No kernel
+  // reads a counter that the same launch writes.
   int32_t it_a, it_b;
   // set by the resfield pass of a conditional re-check (1: the recursion
   // had stopped, the re-check runs) and read by the start pass after it
@@ -50,17 +51,20 @@ struct CgArgs {
   int64_t max_iter;
   double* phi;            // [n_nodes] in: guess, out: solution
   void* E;                // [4 n_nodes] double (float if mixed) or null
-  double *x, *r, *u, *w, *p, *s;  // [n_free]
-  // Mixed precision: the CG recursion runs in FP32 (r, u, w, p, s below)
-  // against K in FP32, while x, b, the true residual, every reduction and
-  // the stopping tests stay FP64.  The recursion stops once its residual
+  double *x, *r, *p;      // [n_free]
+  double *u, *w, *s;      // [n_free], AMG only (within rec0)
+  // Jacobi: a record (r, w, s, d) per row and its successor (d the inverse
+  // diagonal), four doubles, or four floats in mixed precision
+  void *rec0, *rec1;
+  // Mixed precision: the CG recursion runs in FP32 (records and p) against
+  // K in FP32, while x, b, the true residual, every reduction and the
+  // stopping tests stay FP64.  The recursion stops once its residual
   // falls below max(tol ||b||, inner_tol ||r_start||); the true residual is
   // then recomputed in FP64 and the FP32 recursion restarted from it
   // (iterative refinement) until tol is met.
   int mixed;
   int e32;                // E in FP32 from R in FP32 (difference form)
   double inner_tol;
-  float *r32, *u32, *w32, *p32, *s32;  // [n_free]
   double* part;           // [kCgSlots][G]
   int G;                  // workgroups of every solver kernel
   // E already equals R phi for the incoming phi (the previous solve of the
@@ -103,7 +107,7 @@ struct CgArgs {
   int64_t n_clear;
   // lean: the incremental first pass of a step whose warm start is expected
   // to meet the tolerance (no iterations in the step before).  It leaves x
-  // and u (r32 and u32 in mixed precision) to k_cg_prep, launched only if
+  // to k_cg_prep, launched only if
   // the test asks for iterations, and clears the node charges as it reads
   // them (the next step's clear); the later passes of the solve take b
   // from bprev (b_saved).  The test then runs in one workgroup and does
@@ -117,18 +121,16 @@ struct CgArgs {
 // seq != 0: the last kernel of the launch writes the state with this
 // sequence number into args.report (host-mapped).
 hipError_t cg_launch_begin(const CgArgs& a, int64_t seq, hipStream_t s);
-// after a lean first pass whose test asks for iterations: x and u, then the
-// start pass's product (none for AMG)
+// after a lean first pass whose test asks for iterations: x, then the start
+// pass's product (none for AMG)
 hipError_t cg_launch_lean_iter(const CgArgs& a, hipStream_t s);
-hipError_t cg_launch_iters(const CgArgs& a, int it0, int n, int64_t seq,
-                           hipStream_t s);
 hipError_t cg_launch_recheck(const CgArgs& a, int64_t seq, hipStream_t s);
 // the same re-check, done only if the recursion has stopped (state
 // CG_RECHECK; decided on the device, no report): ends a round of
 // iterations so that a solve whose recursion stopped in it comes out of the
 // round with its true-residual test done
 hipError_t cg_launch_recheck_if(const CgArgs& a, hipStream_t s);
-// n iterations numbered by the device counters (no report)
+// n Jacobi iterations, n even, numbered by the device counters (no report)
 hipError_t cg_launch_iters_dev(const CgArgs& a, int n, hipStream_t s);
 // the control state with sequence number seq into a.report
 hipError_t cg_launch_report(const CgArgs& a, int64_t seq, hipStream_t s);
@@ -145,7 +147,7 @@ struct CgBatch {
 // previous solve (CgArgs::incremental; all instances alike)
 hipError_t cg_batch_begin(const CgBatch& b, int grid, int incremental,
                           hipStream_t s);
-hipError_t cg_batch_iters(const CgBatch& b, int grid, int n, hipStream_t s);
+hipError_t cg_batch_iters(const CgBatch& b, int grid, int n, hipStream_t s);  // n even
 hipError_t cg_batch_recheck(const CgBatch& b, int grid, hipStream_t s);
 // cg_launch_recheck_if for every instance of the map
 hipError_t cg_batch_recheck_if(const CgBatch& b, int grid, hipStream_t s);

@@ -5,13 +5,13 @@
 //
 // The solve is a chain of ordinary kernel launches (a launch costs ~3 us on
 // MI355X, a device-wide barrier inside a persistent kernel 12-19 us):
-//   resfield: one pass over phi: b on the fly, r = b - K phi, u = D^-1 r,
-//             x = phi on free nodes, E = R phi on every node, phi = 0 on
-//             Dirichlet nodes; (b,b), (r,r)
+//   resfield: one pass over phi: b on the fly, r = b - K phi, x = phi on
+//             free nodes, E = R phi on every node, phi = 0 on Dirichlet
+//             nodes; (b,b), (r,r)
 //   start   : convergence test on that true residual; stats; when not
-//             converged, w = K u, (r,u), (w,u)
-//   upd(i)  : scalars of iteration i; p, s, x, r, u updates; (r,r), (r,u)
-//   spmv(i) : w = K u; (w,u)
+//             converged, u = D^-1 r, w = K u, (r,u), (w,u)
+//   iter(i) : one iteration in one launch: its scalars, the p, s, x, r, u
+//             updates and w = K u; (r,r), (r,u), (w,u)
 //   scatter : phi = x on free nodes, before the re-check (a resfield pass)
 // K and R share the sparsity of the free rows, so the field of phi comes out
 // of the same pass that tests phi: when the warm start already meets the
@@ -107,47 +107,98 @@ __device__ inline void write_partials(double* part, int stride,
   }
 }
 
-// y_r = sum_j val[j] x[col[j]] over the rows of this workgroup's slices;
-// emit(r, y_r) for every row r < nrows.
-template <typename T, typename F>
-__device__ inline void spmv_sell(const int32_t* __restrict__ sptr,
-                                 const int32_t* __restrict__ scol,
-                                 const T* __restrict__ sval,
-                                 const T* __restrict__ x, int64_t nslices,
-                                 int64_t nrows, VB vb, F&& emit) {
+// emit(r, sum_j val_rj ev(ld(col_rj))) for every row r of M in this
+// workgroup's share, in the arithmetic of T, the sum in entry order.  Up to
+// eight entries per trip (slice widths are uniform across the wave): their
+// words, then their gathers ld, are in flight together.  The packed form
+// looks its values up in a table in LDS.
+template <typename T>
+__device__ inline const T* sell_val(const SellView& M) {
+  if constexpr (std::is_same<T, float>::value) return M.val32;
+  else return M.val;
+}
+template <typename T>
+__device__ inline const T* sell_dict(const SellView& M) {
+  if constexpr (std::is_same<T, float>::value) return M.dict32;
+  else return M.dict;
+}
+
+template <typename T, typename Lf, typename Vf, typename Ef>
+__device__ inline void sell_rows(const SellView& M, int64_t nslices,
+                                 int64_t nrows, VB vb, Lf&& ld, Vf&& ev,
+                                 Ef&& emit) {
+  using X = decltype(ld(0));
   const Range sl = my_range(nslices, vb);
   const int lane = threadIdx.x & (kSell - 1);
   const int sub = threadIdx.x / kSell;
   const int nsub = blockDim.x / kSell;
-  for (int64_t s = sl.lo + sub; s < sl.hi; s += nsub) {
-    const int64_t r = s * kSell + lane;
-    const int32_t p0 = sptr[s], p1 = sptr[s + 1];
-    T acc = T(0);
-    int32_t p = p0 + lane;
-    // four entries per trip (slice widths are uniform across the wave):
-    // their loads are in flight together, the sum keeps the entry order
-    for (; p + 3 * kSell < p1; p += 4 * kSell) {
-      int32_t c[4];
-      T v[4], xv[4];
+  if (M.code) {
+    __shared__ T dict[kDictMax];
+    const T* __restrict__ gd = sell_dict<T>(M);
+    for (int k = threadIdx.x; k < kDictMax; k += blockDim.x) dict[k] = gd[k];
+    __syncthreads();
+    const uint32_t* __restrict__ code = M.code;
+    for (int64_t s = sl.lo + sub; s < sl.hi; s += nsub) {
+      const int32_t p0 = M.sptr[s], p1 = M.sptr[s + 1];
+      T acc = T(0);
+      for (int32_t p = p0 + lane; p < p1; p += 8 * kSell) {
+        const int32_t left = p1 - (p - lane);
+        uint32_t c[8];
+        X xv[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        c[u] = scol[p + u * kSell];
-        v[u] = sval[p + u * kSell];
+        for (int u = 0; u < 8; ++u)
+          if (u * kSell < left) c[u] = code[p + u * kSell];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (u * kSell < left) xv[u] = ld((int32_t)(c[u] & ((1u << kColBits) - 1)));
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (u * kSell < left) acc += dict[c[u] >> kColBits] * ev(xv[u]);
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) xv[u] = x[c[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
+      const int64_t r = s * kSell + lane;
+      if (r < nrows) emit(r, acc);
     }
-    for (; p < p1; p += kSell) acc += sval[p] * x[scol[p]];
+    return;
+  }
+  const int32_t* __restrict__ col = M.col;
+  const T* __restrict__ val = sell_val<T>(M);
+  for (int64_t s = sl.lo + sub; s < sl.hi; s += nsub) {
+    const int32_t p0 = M.sptr[s], p1 = M.sptr[s + 1];
+    T acc = T(0);
+    for (int32_t p = p0 + lane; p < p1; p += 4 * kSell) {
+      const int32_t left = p1 - (p - lane);
+      int32_t c[4];
+      T v[4];
+      X xv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u * kSell < left) {
+          c[u] = col[p + u * kSell];
+          v[u] = val[p + u * kSell];
+        }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u * kSell < left) xv[u] = ld(c[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u * kSell < left) acc += v[u] * ev(xv[u]);
+    }
+    const int64_t r = s * kSell + lane;
     if (r < nrows) emit(r, acc);
   }
 }
 
+// Record of one row in the Jacobi recursion: residual, w = K u, s, and the
+// inverse diagonal.
+template <typename T>
+struct alignas(4 * sizeof(T)) CgRec {
+  T r, w, s, d;
+};
+
 }  // namespace
 
 // Partial-sum slots (each [G] doubles): 0 bb, 1 rr(resid), 2-3 start (ru, wu),
-// 4-5 upd even (rr, ru), 6-7 upd odd, 8 spmv even (wu), 9 spmv odd.
+// 4-5 (rr, ru) of the even iterations, 6-7 of the odd, 8 and 9 (wu) alike.
 __device__ inline double* slot(const CgArgs& a, int k) {
   return a.part + (size_t)k * a.G;
 }
@@ -180,8 +231,7 @@ __device__ inline void report(const CgCtrl* c, CgReport* r, int64_t seq,
 
 // The pass over phi (see the file comment).  reset != 0 starts a new solve
 // (control word cleared by workgroup 0; no other workgroup reads it here).
-// Mixed precision: the FP64 residual is rounded once into the FP32
-// recursion vectors.  FP32 field (e32): E = R phi in the difference form
+// FP32 field (e32): E = R phi in the difference form
 //   E_i = sum_j R_ij (phi_j - phi_i) + S_i phi_i,   S_i = sum_j R_ij (FP64),
 // with R in FP32: the differences are of the size of E h, so rounding R
 // costs a relative error of about 2^-24 in E, while R_ij phi_j alone would
@@ -311,14 +361,7 @@ __device__ inline void k_cg_resfield_body(const CgArgs& a, int reset, VB vb,
       const double ri = bi - kx;
       a.x[r] = pi;
       if (a.bprev) a.bprev[r] = bi;
-      if (a.mixed) {
-        a.r[r] = ri;  // (kept for an incremental next pass)
-        a.r32[r] = (float)ri;
-        a.u32[r] = (float)(ri * m.invdiag[r]);
-      } else {
-        a.r[r] = ri;
-        a.u[r] = ri * m.invdiag[r];
-      }
+      a.r[r] = ri;  // (also kept for an incremental next pass)
       v[0] += bi * bi;
       v[1] += ri * ri;
       if (withE) {
@@ -374,23 +417,10 @@ __device__ inline void k_cg_resfield_body(const CgArgs& a, int reset, VB vb,
   write_partials<2>(slot(a, 0), a.G, v, vb);
 }
 
-// x = phi and u = D^-1 r of free row i (node nd) with residual ri: FP32
-// copies of r and u for the mixed-precision recursion.
-__device__ inline void cg_prep_row(const CgArgs& a, int64_t i, int32_t nd,
-                                   double ri) {
-  a.x[i] = a.phi[nd];
-  if (a.mixed) {
-    a.r32[i] = (float)ri;
-    a.u32[i] = (float)(ri * a.m.invdiag[i]);
-  } else {
-    a.u[i] = ri * a.m.invdiag[i];
-  }
-}
-
 // First pass of a solve whose previous solve (same system, phi unchanged
 // since) ended with the true residual r and right-hand side b_prev: r =
 // (b - b_prev) + r, the same quantity as b - K phi without the product with
-// K; x = phi, u = D^-1 r, (b,b), (r,r) as in the full pass.  The field is
+// K; x = phi, (b,b), (r,r) as in the full pass.  The field is
 // that of phi already.
 __device__ inline void k_cg_resinc_body(const CgArgs& a, VB vb) {
   const DevMesh& m = a.m;
@@ -409,7 +439,7 @@ __device__ inline void k_cg_resinc_body(const CgArgs& a, VB vb) {
     if (a.lean) {
       a.clear_charge[nd] = 0;  // (read above; b stays in bprev)
     } else {
-      cg_prep_row(a, i, nd, ri);
+      a.x[i] = a.phi[nd];
     }
     v[0] += bi * bi;
     v[1] += ri * ri;
@@ -423,13 +453,12 @@ __device__ inline void k_cg_resinc_body(const CgArgs& a, VB vb) {
   write_partials<2>(slot(a, 0), a.G, v, vb);
 }
 
-// x and u of a lean first pass whose test asked for iterations (the same
-// values as the full first pass writes).
+// x of a lean first pass whose test asked for iterations.
 __device__ inline void k_cg_prep_body(const CgArgs& a, VB vb) {
   const DevMesh& m = a.m;
   const Range rows = my_range(m.n_free, vb);
   for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x)
-    cg_prep_row(a, i, m.free2node[i], a.r[i]);
+    a.x[i] = a.phi[m.free2node[i]];
 }
 
 // phi = x on the free nodes (before a re-check pass; dev_gate: only if the
@@ -442,28 +471,39 @@ __device__ inline void k_cg_scatter_body(const CgArgs& a, VB vb, int dev_gate = 
     a.phi[m.free2node[i]] = a.x[i];
 }
 
-// The first product w = K u of a (re)started CG and its two sums.
-__device__ inline void start_product(const CgArgs& a, VB vb) {
+// u = D^-1 r at the (re)start of a Jacobi recursion, from the FP64 residual
+// (rounded to FP32 in mixed precision).
+template <typename T>
+__device__ inline T start_u(const CgArgs& a, int64_t i) {
+  return (T)(a.r[i] * a.m.invdiag[i]);
+}
+
+// The records of a (re)started Jacobi recursion: w = K u, s = 0 (u is not
+// stored: it is D^-1 r); (r,u) and (w,u).
+template <typename T>
+__device__ inline void start_records(const CgArgs& a, VB vb) {
   const DevMesh& m = a.m;
+  const T* __restrict__ d = std::is_same<T, float>::value ? (const T*)m.invdiag32
+                                                          : (const T*)m.invdiag;
+  CgRec<T>* __restrict__ out = (CgRec<T>*)a.rec0;
   double v[2] = {0.0, 0.0};
-  if (a.mixed) {
-    spmv_sell(m.k_sptr, m.k_scol, m.k_sval32, a.u32, m.k_nslices, m.n_free, vb,
-              [&](int64_t i, float s) {
-                a.w32[i] = s;
-                const double ui = a.u32[i];
-                v[0] += (double)a.r32[i] * ui;
-                v[1] += (double)s * ui;
-              });
-  } else {
-    spmv_sell(m.k_sptr, m.k_scol, m.k_sval, a.u, m.k_nslices, m.n_free, vb,
-              [&](int64_t i, double s) {
-                a.w[i] = s;
-                const double ui = a.u[i];
-                v[0] += a.r[i] * ui;
-                v[1] += s * ui;
-              });
-  }
+  sell_rows<T>(m.kz, m.k_nslices, m.n_free, vb,
+               [&](int32_t c) { return start_u<T>(a, c); }, [](T x) { return x; },
+               [&](int64_t i, T w) {
+                 const T r = (T)a.r[i];
+                 const T u = start_u<T>(a, i);
+                 out[i] = CgRec<T>{r, w, T(0), d[i]};
+                 v[0] += (double)r * (double)u;
+                 v[1] += (double)w * (double)u;
+               });
   write_partials<2>(slot(a, 2), a.G, v, vb);
+}
+
+__device__ inline void start_product(const CgArgs& a, VB vb) {
+  if (a.mixed)
+    start_records<float>(a, vb);
+  else
+    start_records<double>(a, vb);
 }
 
 // Convergence test on the true residual of the last resfield pass; when the
@@ -562,15 +602,66 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
   start_product(a, vb);
 }
 
-// Iteration it (0-based since the last (re)start): scalars from the
-// previous products, then the row-local updates.
-// it < 0: take the iteration index from the control word (batched launch).
-__device__ inline void k_cg_upd_body(const CgArgs& a, int it, VB vb) {
+// Iteration it (0-based since the last (re)start; par = it & 1) in one
+// launch.  With the scalars of the previous sums, w = K u_new of row i needs
+// u_new at its neighbours j, which only needs their old records:
+//   s_j' = w_j + beta s_j,  r_j' = r_j - alpha s_j',  u_j' = d_j r_j',
+// so every row forms its neighbours' u' again (three multiply-adds per
+// entry on a 32-byte record out of L2) instead of waiting for a launch that
+// writes it; the new records go to the other array.  The row-local part (p,
+// x, (r,r), (r,u)) runs over even row ranges in a second loop, so that all
+// sums keep the order, and all values the bits, of separate update and
+// product launches.
+// Bound: latency of the record gathers, then the Infinity Cache.  The first
+// slice's words and records are in flight before the scalars are reduced.
+// An FP64 iteration on the production tip (515k rows, 64 MB) takes 17 us;
+// an update launch and a product over all 15 entries per row took 14 + 19,
+// this kernel without the early loads 22, with three waves per SIMD (136
+// registers) 22.
+template <typename T, bool PK>
+__device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
   CgCtrl* c = a.ctrl;
   if (c->state != CG_ITER) return;
-  if (it < 0) {
-    it = c->it_a;
-    if (vb.id == 0 && threadIdx.x == 0) c->it_b = it;
+  const int it = par ? c->it_b : c->it_a;
+  const DevMesh& m = a.m;
+  const SellView& K = m.kz;
+  const CgRec<T>* __restrict__ in = (const CgRec<T>*)(par ? a.rec1 : a.rec0);
+  CgRec<T>* __restrict__ out = (CgRec<T>*)(par ? a.rec0 : a.rec1);
+  const uint32_t* __restrict__ code = K.code;
+  const int32_t* __restrict__ col = K.col;
+  const T* __restrict__ val = sell_val<T>(K);
+  constexpr uint32_t kMask = (1u << kColBits) - 1;
+  constexpr int W = PK ? 8 : 4;   // entries in flight
+  __shared__ T dict[PK ? kDictMax : 1];
+  const int lane = threadIdx.x & (kSell - 1);
+  const int nsub = blockDim.x / kSell;
+  const Range sl = my_range(m.k_nslices, vb);
+  int64_t s = sl.lo + threadIdx.x / kSell;
+  // the first W entries of this lane's row
+  uint32_t cw[W];
+  T vv[W];
+  CgRec<T> q[W], own;
+  int32_t p = 0, left = 0;
+  auto open = [&]() {
+    const int32_t p0 = K.sptr[s];
+    left = K.sptr[s + 1] - p0;
+    p = p0 + lane;
+    const int64_t r = s * kSell + lane;
+    own = in[r < m.n_free ? r : m.n_free - 1];
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+      if (u * kSell < left) {
+        cw[u] = PK ? code[p + u * kSell] : (uint32_t)col[p + u * kSell];
+        if (!PK) vv[u] = val[p + u * kSell];
+      }
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+      if (u * kSell < left) q[u] = in[PK ? cw[u] & kMask : cw[u]];
+  };
+  if (s < sl.hi) open();
+  if (PK) {
+    const T* __restrict__ gd = sell_dict<T>(K);
+    for (int k = threadIdx.x; k < kDictMax; k += blockDim.x) dict[k] = gd[k];
   }
   double alpha, beta, gamma;
   if (it == 0) {
@@ -580,20 +671,22 @@ __device__ inline void k_cg_upd_body(const CgArgs& a, int it, VB vb) {
     alpha = gamma / t[1];
     beta = 0.0;
   } else {
-    const int pb = (it - 1) & 1;
-    double t3[3];
+    const int pb = par ^ 1;
+    double t[3];
     {
-      double t2[2];
-      totals<2>(slot(a, 4 + 2 * pb), a.G, a.G, t2);
-      double t1[1];
-      totals<1>(slot(a, 8 + pb), a.G, 1, t1);
-      t3[0] = t2[0];
-      t3[1] = t2[1];
-      t3[2] = t1[0];
+      const double* p2 = slot(a, 4 + 2 * pb);
+      const double* p1 = slot(a, 8 + pb);
+      t[0] = t[1] = t[2] = 0.0;
+      for (int j = threadIdx.x; j < a.G; j += blockDim.x) {
+        t[0] += p2[j];
+        t[1] += p2[a.G + j];
+        t[2] += p1[j];
+      }
+      block_sum<3>(t);
     }
     // it iterations done since the (re)start; c->iters is stable while
     // iterating, so every workgroup takes the same decision
-    const double rn = sqrt(t3[0]);
+    const double rn = sqrt(t[0]);
     const double bn = sqrt(c->bb);
     double thr = a.tol * (a.bref ? fmax(bn, *a.bref) : bn);
     if (a.mixed) thr = fmax(thr, a.inner_tol * c->rstart);
@@ -606,77 +699,98 @@ __device__ inline void k_cg_upd_body(const CgArgs& a, int it, VB vb) {
     }
     const double g_prev = c->gamma[pb];
     const double a_prev = c->alpha[pb];
-    gamma = t3[1];
+    gamma = t[1];
     beta = gamma / g_prev;
-    alpha = gamma / (t3[2] - beta * gamma / a_prev);
+    alpha = gamma / (t[2] - beta * gamma / a_prev);
   }
   if (vb.id == 0 && threadIdx.x == 0) {
-    c->gamma[it & 1] = gamma;
-    c->alpha[it & 1] = alpha;
+    c->gamma[par] = gamma;
+    c->alpha[par] = alpha;
+    (par ? c->it_a : c->it_b) = it + 1;
   }
-  const DevMesh& m = a.m;
-  const Range rows = my_range(m.n_free, vb);
-  double v[2] = {0.0, 0.0};
-  const bool first = it == 0;
-  if (a.mixed) {
-    const float al = (float)alpha, be = (float)beta;
-    for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
-      const float pi = first ? a.u32[i] : a.u32[i] + be * a.p32[i];
-      const float si = first ? a.w32[i] : a.w32[i] + be * a.s32[i];
-      a.p32[i] = pi;
-      a.s32[i] = si;
-      a.x[i] += alpha * (double)pi;
-      const float ri = a.r32[i] - al * si;
-      a.r32[i] = ri;
-      const float ui = ri * m.invdiag32[i];
-      a.u32[i] = ui;
-      v[0] += (double)ri * ri;
-      v[1] += (double)ri * ui;
+  const T al = (T)alpha, be = (T)beta;
+  auto step = [&](const CgRec<T>& o, T& sn, T& rn) {
+    sn = o.w + be * o.s;
+    rn = o.r - al * sn;
+  };
+  double v[3] = {0.0, 0.0, 0.0};
+  while (s < sl.hi) {
+    T acc = T(0);
+    auto add = [&](T k, const CgRec<T>& o) {
+      T sj, rj;
+      step(o, sj, rj);
+      acc += k * (rj * o.d);
+    };
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+      if (u * kSell < left) add(PK ? dict[cw[u] >> kColBits] : vv[u], q[u]);
+    // longer rows: the rest four entries at a time (packed: one, to stay
+    // within the registers of four waves per SIMD)
+    for (int e = W; PK && e * kSell < left; ++e) {
+      const uint32_t cu = code[p + e * kSell];
+      add(dict[cu >> kColBits], in[cu & kMask]);
     }
-    write_partials<2>(slot(a, 4 + 2 * (it & 1)), a.G, v, vb);
-    return;
+    for (int e = W; !PK && e * kSell < left; e += 4) {
+      uint32_t c[4];
+      T k[4];
+      CgRec<T> o[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if ((e + u) * kSell < left) {
+          c[u] = (uint32_t)col[p + (e + u) * kSell];
+          k[u] = val[p + (e + u) * kSell];
+        }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if ((e + u) * kSell < left) o[u] = in[c[u]];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if ((e + u) * kSell < left) add(k[u], o[u]);
+    }
+    const int64_t r = s * kSell + lane;
+    if (r < m.n_free) {
+      T si, ri;
+      step(own, si, ri);
+      out[r] = CgRec<T>{ri, acc, si, own.d};
+      v[2] += (double)acc * (double)(ri * own.d);
+    }
+    s += nsub;
+    if (s < sl.hi) open();
   }
+  const bool first = it == 0;
+  T* __restrict__ pv = (T*)a.p;
+  double* __restrict__ x = a.x;
+  const Range rows = my_range(m.n_free, vb);
   for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
-    const double pi = first ? a.u[i] : a.u[i] + beta * a.p[i];
-    const double si = first ? a.w[i] : a.w[i] + beta * a.s[i];
-    a.p[i] = pi;
-    a.s[i] = si;
-    a.x[i] += alpha * pi;
-    const double ri = a.r[i] - alpha * si;
-    a.r[i] = ri;
-    const double ui = ri * m.invdiag[i];
-    a.u[i] = ui;
-    v[0] += ri * ri;
-    v[1] += ri * ui;
+    const CgRec<T> o = in[i];
+    const T pi = first ? start_u<T>(a, i) : o.r * o.d + be * pv[i];
+    T si, ri;
+    step(o, si, ri);
+    pv[i] = pi;
+    x[i] += alpha * (double)pi;
+    v[0] += (double)ri * (double)ri;
+    v[1] += (double)ri * (double)(ri * o.d);
   }
-  write_partials<2>(slot(a, 4 + 2 * (it & 1)), a.G, v, vb);
+  block_sum<3>(v);
+  if (threadIdx.x == 0) {
+    slot(a, 4 + 2 * par)[vb.id] = v[0];
+    slot(a, 5 + 2 * par)[vb.id] = v[1];
+    slot(a, 8 + par)[vb.id] = v[2];
+  }
 }
 
-__device__ inline void k_cg_spmv_body(const CgArgs& a, int it,
-                                                int64_t seq, VB vb) {
-  const int32_t state = a.ctrl->state;
-  if (seq && vb.id == 0 && threadIdx.x == 0) report(a.ctrl, a.report, seq, state);
-  if (state != CG_ITER) return;
-  if (it < 0) {
-    it = a.ctrl->it_b;
-    if (vb.id == 0 && threadIdx.x == 0) a.ctrl->it_a = it + 1;
-  }
-  const DevMesh& m = a.m;
-  double v[1] = {0.0};
-  if (a.mixed) {
-    spmv_sell(m.k_sptr, m.k_scol, m.k_sval32, a.u32, m.k_nslices, m.n_free, vb,
-              [&](int64_t i, float s) {
-                a.w32[i] = s;
-                v[0] += (double)s * a.u32[i];
-              });
+__device__ inline void k_cg_iter_body(const CgArgs& a, int par, VB vb) {
+  if (a.m.kz.code) {
+    if (a.mixed)
+      cg_iter<float, true>(a, par, vb);
+    else
+      cg_iter<double, true>(a, par, vb);
   } else {
-    spmv_sell(m.k_sptr, m.k_scol, m.k_sval, a.u, m.k_nslices, m.n_free, vb,
-              [&](int64_t i, double s) {
-                a.w[i] = s;
-                v[0] += s * a.u[i];
-              });
+    if (a.mixed)
+      cg_iter<float, false>(a, par, vb);
+    else
+      cg_iter<double, false>(a, par, vb);
   }
-  write_partials<1>(slot(a, 8 + (it & 1)), a.G, v, vb);
 }
 
 // Single-instance kernels.
@@ -697,12 +811,9 @@ __global__ void __launch_bounds__(kCgBlock) k_cg_start(CgArgs a, int64_t seq,
                                                       int dev_gate) {
   k_cg_start_body(a, seq, VB{(int)blockIdx.x, (int)gridDim.x}, dev_gate);
 }
-__global__ void __launch_bounds__(kCgBlock) k_cg_upd(CgArgs a, int it) {
-  k_cg_upd_body(a, it, VB{(int)blockIdx.x, (int)gridDim.x});
-}
-__global__ void __launch_bounds__(kCgBlock) k_cg_spmv(CgArgs a, int it,
-                                                     int64_t seq) {
-  k_cg_spmv_body(a, it, seq, VB{(int)blockIdx.x, (int)gridDim.x});
+template <typename T, bool PK>
+__global__ void __launch_bounds__(kCgBlock, 4) k_cg_iter(CgArgs a, int par) {
+  cg_iter<T, PK>(a, par, VB{(int)blockIdx.x, (int)gridDim.x});
 }
 
 __global__ void k_cg_report(CgArgs a, int64_t seq) {
@@ -742,17 +853,11 @@ __global__ void __launch_bounds__(kCgBlock) k_cg_start_b(CgBatch b, int gated) {
   const CgArgs a = b.args[i];
   k_cg_start_body(a, 0, vb, gated == 2);
 }
-__global__ void __launch_bounds__(kCgBlock) k_cg_upd_b(CgBatch b) {
+__global__ void __launch_bounds__(kCgBlock, 4) k_cg_iter_b(CgBatch b, int par) {
   int i;
   const VB vb = batch_block(b.map, i);
   const CgArgs a = b.args[i];
-  k_cg_upd_body(a, -1, vb);
-}
-__global__ void __launch_bounds__(kCgBlock) k_cg_spmv_b(CgBatch b) {
-  int i;
-  const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
-  k_cg_spmv_body(a, -1, 0, vb);
+  k_cg_iter_body(a, par, vb);
 }
 // One thread per instance: report the control state with sequence seq.
 __global__ void k_cg_report_b(CgBatch b, int n, int64_t seq) {
@@ -778,47 +883,19 @@ __global__ void k_cg_report_b(CgBatch b, int n, int64_t seq) {
 namespace {
 
 // emit(r, sum_j val_rj g(col_rj)) for every row r of M in this workgroup's
-// share, in the arithmetic of T (the values of M in T: val or val32).
-// SELL (lpr = 1): one lane per row, entries in order, four loads in flight
-// per trip.  CSR (lpr > 1): lpr lanes per row, each summing every lpr-th
-// entry, then a fixed shuffle tree; every group of a workgroup makes the
-// same number of trips, so the shuffles run on whole waves.
-template <typename T>
-__device__ inline const T* mat_val(const SellMat& M) {
-  if constexpr (std::is_same<T, float>::value) return M.val32;
-  else return M.val;
-}
-
+// share, in the arithmetic of T.
+// SELL (lpr = 1): see sell_rows.  CSR (lpr > 1): lpr lanes per row, each
+// summing every lpr-th entry, then a fixed shuffle tree; every group of a
+// workgroup makes the same number of trips, so the shuffles run on whole
+// waves.
 template <typename T, typename Gf, typename Ef>
 __device__ inline void amg_rows(const SellMat& M, VB vb, Gf&& g, Ef&& emit) {
-  const T* __restrict__ val = mat_val<T>(M);
   if (M.lpr == 1) {
-    const Range sl = my_range(M.nslices, vb);
-    const int lane = threadIdx.x & (kSell - 1);
-    for (int64_t s = sl.lo + threadIdx.x / kSell; s < sl.hi;
-         s += blockDim.x / kSell) {
-      const int32_t p1 = M.sptr[s + 1];
-      int32_t p = M.sptr[s] + lane;
-      T acc = 0;
-      for (; p + 3 * kSell < p1; p += 4 * kSell) {
-        int32_t c[4];
-        T v[4], xv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          c[u] = M.col[p + u * kSell];
-          v[u] = val[p + u * kSell];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) xv[u] = g(c[u]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
-      }
-      for (; p < p1; p += kSell) acc += val[p] * g(M.col[p]);
-      const int64_t r = s * kSell + lane;
-      if (r < M.nrows) emit(r, acc);
-    }
+    sell_rows<T>(M.v, M.nslices, M.nrows, vb, g, [](T v) { return v; }, emit);
     return;
   }
+  const T* __restrict__ val = sell_val<T>(M.v);
+  const int32_t* __restrict__ col = M.v.col;
   const int lpr = M.lpr;
   const Range rows = my_range(M.nrows, vb);
   const int sub = threadIdx.x & (lpr - 1);
@@ -829,14 +906,14 @@ __device__ inline void amg_rows(const SellMat& M, VB vb, Gf&& g, Ef&& emit) {
     if (r < rows.hi) {
       // four entries per trip with their loads in flight together, summed
       // in the lane's entry order
-      const int32_t p1 = M.sptr[r + 1];
-      int32_t p = M.sptr[r] + sub;
+      const int32_t p1 = M.v.sptr[r + 1];
+      int32_t p = M.v.sptr[r] + sub;
       for (; p + 3 * lpr < p1; p += 4 * lpr) {
         int32_t c[4];
         T v[4], xv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          c[u] = M.col[p + u * lpr];
+          c[u] = col[p + u * lpr];
           v[u] = val[p + u * lpr];
         }
 #pragma unroll
@@ -844,7 +921,7 @@ __device__ inline void amg_rows(const SellMat& M, VB vb, Gf&& g, Ef&& emit) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
       }
-      for (; p < p1; p += lpr) acc += val[p] * g(M.col[p]);
+      for (; p < p1; p += lpr) acc += val[p] * g(col[p]);
     }
     for (int off = lpr >> 1; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, lpr);
     if (r < rows.hi && sub == 0) emit(r, acc);
@@ -970,11 +1047,13 @@ __device__ inline void amg_spmv_body(const CgArgs& a, VB vb) {
   if (vb.id == 0 && threadIdx.x == 0) c->it_b = it;
   const DevMesh& m = a.m;
   double v[1] = {0.0};
-  spmv_sell(m.k_sptr, m.k_scol, m.k_sval, a.u, m.k_nslices, m.n_free, vb,
-            [&](int64_t i, double s) {
-              a.w[i] = s;
-              v[0] += s * a.u[i];
-            });
+  const double* __restrict__ u = a.u;
+  sell_rows<double>(m.kz, m.k_nslices, m.n_free, vb,
+                    [&](int32_t c) { return u[c]; }, [](double v) { return v; },
+                    [&](int64_t i, double s) {
+                      a.w[i] = s;
+                      v[0] += s * u[i];
+                    });
   write_partials<1>(slot(a, 8 + (it & 1)), a.G, v, vb);
 }
 
@@ -1324,25 +1403,17 @@ hipError_t cg_launch_lean_iter(const CgArgs& a, hipStream_t s) {
   return hipSuccess;
 }
 
-hipError_t cg_launch_iters(const CgArgs& a, int it0, int n, int64_t seq,
-                           hipStream_t s) {
-  for (int k = 0; k < n; ++k) {
-    LAUNCH(k_cg_upd, a, it0 + k);
-    LAUNCH(k_cg_spmv, a, it0 + k, k == n - 1 ? seq : (int64_t)0);
-  }
-  return hipSuccess;
-}
-
 hipError_t cg_launch_report(const CgArgs& a, int64_t seq, hipStream_t s) {
   hipLaunchKernelGGL(k_cg_report, dim3(1), dim3(64), 0, s, a, seq);
   return hipGetLastError();
 }
 
 hipError_t cg_launch_iters_dev(const CgArgs& a, int n, hipStream_t s) {
-  for (int k = 0; k < n; ++k) {
-    LAUNCH(k_cg_upd, a, -1);
-    LAUNCH(k_cg_spmv, a, -1, (int64_t)0);
-  }
+  if (n & 1) return hipErrorInvalidValue;
+  const auto kern = a.m.kz.code
+                        ? (a.mixed ? k_cg_iter<float, true> : k_cg_iter<double, true>)
+                        : (a.mixed ? k_cg_iter<float, false> : k_cg_iter<double, false>);
+  for (int k = 0; k < n; ++k) LAUNCH(kern, a, k & 1);
   return hipSuccess;
 }
 
@@ -1378,10 +1449,8 @@ hipError_t cg_batch_begin(const CgBatch& b, int grid, int incremental,
 }
 
 hipError_t cg_batch_iters(const CgBatch& b, int grid, int n, hipStream_t s) {
-  for (int k = 0; k < n; ++k) {
-    BLAUNCH(k_cg_upd_b, b);
-    BLAUNCH(k_cg_spmv_b, b);
-  }
+  if (n & 1) return hipErrorInvalidValue;
+  for (int k = 0; k < n; ++k) BLAUNCH(k_cg_iter_b, b, k & 1);
   return hipSuccess;
 }
 
