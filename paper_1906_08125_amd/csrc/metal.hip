@@ -23,9 +23,11 @@ namespace {
 
 constexpr int kMB = 256;       // threads per workgroup
 constexpr int kMaxG = 1024;    // workgroups of the row-loop kernels
-constexpr int kMaxS = 65536;   // workgroups of the product (a row per thread)
-constexpr int kChunk = 24;     // CG iterations before the first host check
-constexpr int kChunkBig = 96;  // and between the later ones
+constexpr int kMaxS = 1024;    // workgroups of an iteration (a row per thread)
+// CG iterations before the first host check and between the later ones
+// (both even: see k_cg_iter)
+constexpr int kChunk = 24;
+constexpr int kChunkBig = 96;
 
 struct MetalCtrl {
   double gam[2];     // r.z of the last two iterations (by parity)
@@ -33,11 +35,11 @@ struct MetalCtrl {
   double bb;         // ||b||^2 over the free rows
   double rr;         // ||r||^2 of the last iterate tested
   double tol2;
-  // iterations completed: written by k_cg_step and read by k_cg_spmv,
-  // whose workgroup 0 copies it to it_cur for the next k_cg_step, so that
-  // no kernel reads a counter that its own launch writes
-  int64_t iters;
-  int64_t it_cur;
+  int64_t iters;     // iterations completed (for the host)
+  // the same by parity: the even iterations read it_a and write it_b, the
+  // odd ones the reverse, so that no kernel reads a counter that its own
+  // launch writes
+  int64_t it_a, it_b;
   int32_t done;
   int32_t pad;
 };
@@ -244,6 +246,11 @@ __global__ void k_eliminate(int64_t n, const int32_t* __restrict__ row_ptr,
   dinv[i] = 1.0 / d;
 }
 
+// A row's residual, w = A z, search product s and inverse diagonal.
+struct alignas(32) MetalRec {
+  double r, w, s, d;
+};
+
 struct CgArgsM {
   int64_t n;
   const int32_t* row_ptr;
@@ -260,9 +267,10 @@ struct CgArgsM {
   const uint8_t* dir;
   double dir_value;
   double tol2;       // read by k_cg_init only (the others read ctrl->tol2)
-  double *x, *r, *z, *p, *s, *w;
-  double* part;      // [3][kMaxS]
-  int Gs;            // workgroups of the product
+  double *x, *r, *z, *p;
+  MetalRec* rec[2];  // records by parity of the iteration that reads them
+  double* part;      // [2][3][kMaxS], by parity of the iteration written in
+  int Gs;            // workgroups of an iteration
   MetalCtrl* ctrl;
   int G;
 };
@@ -346,30 +354,32 @@ __global__ void k_cg_start(CgArgsM a) {
     a.ctrl->bb = bb;
     a.ctrl->tol2 = a.tol2;
     a.ctrl->iters = 0;
-    a.ctrl->it_cur = 0;
+    a.ctrl->it_a = a.ctrl->it_b = 0;
     a.ctrl->done = 0;
   }
 }
 
-// The control word's done flag as one value for the whole workgroup (block
-// 0 of k_cg_step may set it while other workgroups start).
-__device__ bool block_done(const MetalCtrl* c) {
-  __shared__ int d;
-  if (threadIdx.x == 0) d = __atomic_load_n(&c->done, __ATOMIC_RELAXED);
+// The sums of r.z, w.z and r.r of this workgroup's rows.
+__device__ void put_partials(double* part, double gz, double wz, double rr) {
+  __shared__ double sh[3][kMB / 64];
+  double v[3] = {gz, wz, rr};
+  for (int o = 32; o > 0; o >>= 1)
+    for (int j = 0; j < 3; ++j) v[j] += __shfl_down(v[j], o, 64);
+  if ((threadIdx.x & 63) == 0)
+    for (int j = 0; j < 3; ++j) sh[j][threadIdx.x >> 6] = v[j];
   __syncthreads();
-  const bool r = d != 0;
-  __syncthreads();
-  return r;
+  if (threadIdx.x < 3) {
+    double t = 0.0;
+    for (int k = 0; k < kMB / 64; ++k) t += sh[threadIdx.x][k];
+    part[threadIdx.x * kMaxS + blockIdx.x] = t;
+  }
 }
 
-// w = A z (one row per lane, 64-row slices of the sliced-ELLPACK copy, so
-// that every load of a wave is contiguous; entries summed in row order,
-// the padding adding zeros) and the partials of r.z, w.z and r.r; the
-// iteration counter for k_cg_step
-__global__ void k_cg_spmv(CgArgsM a) {
-  if (block_done(a.ctrl)) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctrl->it_cur = a.ctrl->iters;
-  __shared__ double sh[kMB / 64];
+// The first records: w = A z (one row per lane, 64-row slices of the
+// sliced-ELLPACK copy, so that every load of a wave is contiguous; entries
+// summed in row order, the padding adding zeros), s = 0, and the partials
+// of r.z, w.z and r.r.
+__global__ void k_cg_first(CgArgsM a) {
   double gz = 0.0, wz = 0.0, rr = 0.0;
   const int lane = threadIdx.x & 63;
   const int64_t ns = (a.n + 63) / 64;
@@ -377,38 +387,17 @@ __global__ void k_cg_spmv(CgArgsM a) {
        sl += (int64_t)gridDim.x * (kMB / 64)) {
     const int32_t p0 = a.sptr[sl], p1 = a.sptr[sl + 1];
     double v = 0.0;
-    int32_t q = p0 + lane;
-    for (; q + 3 * 64 < p1; q += 4 * 64) {
-      int32_t c[4];
-      double av[4], zv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        c[u] = a.scol[q + 64 * u];
-        av[u] = a.sval[q + 64 * u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) zv[u] = a.z[c[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v += av[u] * zv[u];
-    }
-    for (; q < p1; q += 64) v += a.sval[q] * a.z[a.scol[q]];
+    for (int32_t q = p0 + lane; q < p1; q += 64) v += a.sval[q] * a.z[a.scol[q]];
     const int64_t i = sl * 64 + lane;
     if (i < a.n) {
       const double ri = a.r[i], zi = a.z[i];
-      a.w[i] = v;
+      a.rec[0][i] = MetalRec{ri, v, 0.0, a.dinv[i]};
       gz += ri * zi;
       wz += v * zi;
       rr += ri * ri;
     }
   }
-  const double s0 = block_sum(gz, sh);
-  const double s1 = block_sum(wz, sh);
-  const double s2 = block_sum(rr, sh);
-  if (threadIdx.x == 0) {
-    a.part[blockIdx.x] = s0;
-    a.part[kMaxS + blockIdx.x] = s1;
-    a.part[2 * kMaxS + blockIdx.x] = s2;
-  }
+  put_partials(a.part + 3 * kMaxS, gz, wz, rr);
 }
 
 // The assembled (and eliminated) values into the sliced-ELLPACK copy.
@@ -420,21 +409,66 @@ __global__ void k_to_sell(int64_t nnz, const int32_t* __restrict__ c2s,
 }
 
 // One iteration of the single-reduction (Chronopoulos-Gear) form of
-// Jacobi-preconditioned CG: from gamma = r.z, delta = (A z).z,
+// Jacobi-preconditioned CG in one launch: from gamma = r.z,
+// delta = (A z).z,
 //   beta = gamma / gamma_prev, alpha = gamma / (delta - beta gamma / alpha_prev)
 //   (beta = 0, alpha = gamma / delta at the first iteration),
-//   p = z + beta p, s = w + beta s, x += alpha p, r -= alpha s, z = D^-1 r.
+//   p = z + beta p, s = w + beta s, x += alpha p, r -= alpha s, z = D^-1 r,
+//   w = A z for the next one.
 // The residual of the incoming iterate is tested first.  Every workgroup
-// sums the product's partials itself, in the same fixed order (no
-// reduction launch between the product and the step).
-__global__ void k_cg_step(CgArgsM a) {
-  if (block_done(a.ctrl)) return;
-  const int64_t it = a.ctrl->it_cur;
+// sums the previous partials itself, in the same fixed order.  A row's new
+// w needs its neighbours' new z, which only needs their old records: each
+// row forms them again (as the vacuum solver's k_cg_iter does), where a
+// second launch took as long as the work in either.  par: the iteration's
+// parity.
+// Bound: latency (98k rows are 1.5 waves per SIMD): one row's columns,
+// values and records are in flight before the scalars are reduced.
+constexpr int kRowW = 16;  // entries in flight (interior rows have 15)
+__global__ void __launch_bounds__(kMB, 2) k_cg_iter(CgArgsM a, int par) {
+  // every control value this launch reads, in flight at once; the done flag
+  // is acted on behind the reduction's barrier (workgroup 0 may set it
+  // while other workgroups of the launch start: those then find the same
+  // test met)
+  const MetalCtrl* ct = a.ctrl;
+  const int32_t done = __atomic_load_n(&ct->done, __ATOMIC_RELAXED);
+  const int64_t it = par ? ct->it_b : ct->it_a;
+  const double bb = ct->bb, tol2 = ct->tol2;
+  const double g_prev = ct->gam[par], a_prev = ct->alpha[par];
+  const MetalRec* __restrict__ in = a.rec[par];
+  MetalRec* __restrict__ out = a.rec[par ^ 1];
+  const int32_t* __restrict__ scol = a.scol;
+  const double* __restrict__ sval = a.sval;
+  const int lane = threadIdx.x & 63;
+  const int64_t ns = (a.n + 63) / 64;
+  int64_t sl = (int64_t)blockIdx.x * (kMB / 64) + (threadIdx.x >> 6);
+  int32_t c[kRowW], q0 = 0, left = 0;
+  double av[kRowW], pi = 0.0, xi = 0.0;
+  MetalRec q[kRowW], own;
+  auto open = [&]() {
+    const int32_t p0 = a.sptr[sl];
+    left = a.sptr[sl + 1] - p0;
+    q0 = p0 + lane;
+#pragma unroll
+    for (int u = 0; u < kRowW; ++u)
+      if (u * 64 < left) {
+        c[u] = scol[q0 + u * 64];
+        av[u] = sval[q0 + u * 64];
+      }
+    const int64_t i = sl * 64 + lane;
+    const int64_t ic = i < a.n ? i : a.n - 1;
+    own = in[ic];
+    pi = a.p[ic];
+    xi = a.x[ic];
+#pragma unroll
+    for (int u = 0; u < kRowW; ++u)
+      if (u * 64 < left) q[u] = in[c[u]];
+  };
+  if (sl < ns) open();
   double red[3];
-  sum3_fixed(a.part, a.Gs, red);
+  sum3_fixed(a.part + (par ^ 1) * 3 * kMaxS, a.Gs, red);
+  if (done) return;
   const double gam = red[0], del = red[1], rr = red[2];
-  const double bb = a.ctrl->bb;
-  if (bb == 0.0 || rr <= a.ctrl->tol2 * bb) {
+  if (bb == 0.0 || rr <= tol2 * bb) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       a.ctrl->rr = rr;
       a.ctrl->iters = it;
@@ -447,27 +481,46 @@ __global__ void k_cg_step(CgArgsM a) {
     beta = 0.0;
     alpha = gam / del;
   } else {
-    beta = gam / a.ctrl->gam[it & 1];
-    alpha = gam / (del - beta * gam / a.ctrl->alpha[it & 1]);
-  }
-  for (int64_t i = (int64_t)blockIdx.x * kMB + threadIdx.x; i < a.n;
-       i += (int64_t)a.G * kMB) {
-    // p and s hold nothing yet at the first iteration (not even zeros)
-    const double pi = it == 0 ? a.z[i] : a.z[i] + beta * a.p[i];
-    const double si = it == 0 ? a.w[i] : a.w[i] + beta * a.s[i];
-    a.p[i] = pi;
-    a.s[i] = si;
-    a.x[i] += alpha * pi;
-    const double ri = a.r[i] - alpha * si;
-    a.r[i] = ri;
-    a.z[i] = ri * a.dinv[i];
+    beta = gam / g_prev;
+    alpha = gam / (del - beta * gam / a_prev);
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    a.ctrl->gam[(it + 1) & 1] = gam;
-    a.ctrl->alpha[(it + 1) & 1] = alpha;
+    a.ctrl->gam[par ^ 1] = gam;
+    a.ctrl->alpha[par ^ 1] = alpha;
     a.ctrl->rr = rr;
     a.ctrl->iters = it + 1;
+    (par ? a.ctrl->it_a : a.ctrl->it_b) = it + 1;
   }
+  double gz = 0.0, wz = 0.0, r2 = 0.0;
+  while (sl < ns) {
+    double v = 0.0;
+    auto add = [&](double k, const MetalRec& o) {
+      const double sj = o.w + beta * o.s;
+      v += k * ((o.r - alpha * sj) * o.d);
+    };
+#pragma unroll
+    for (int u = 0; u < kRowW; ++u)
+      if (u * 64 < left) add(av[u], q[u]);
+    for (int u = kRowW; u * 64 < left; ++u) add(sval[q0 + u * 64], in[scol[q0 + u * 64]]);
+    const int64_t i = sl * 64 + lane;
+    if (i < a.n) {
+      const double z0 = own.r * own.d;
+      // p holds nothing yet at the first iteration (not even zeros)
+      const double pn = it == 0 ? z0 : z0 + beta * pi;
+      const double si = own.w + beta * own.s;
+      const double ri = own.r - alpha * si;
+      const double zi = ri * own.d;
+      a.p[i] = pn;
+      a.x[i] = xi + alpha * pn;
+      out[i] = MetalRec{ri, v, si, own.d};
+      gz += ri * zi;
+      wz += v * zi;
+      r2 += ri * ri;
+    }
+    sl += (int64_t)gridDim.x * (kMB / 64);
+    if (sl < ns) open();
+  }
+  put_partials(a.part + par * 3 * kMaxS, gz, wz, r2);
 }
 
 // A zero right-hand side has the zero solution on the free rows.
@@ -499,7 +552,8 @@ unsigned blocks_for(int64_t n) { return (unsigned)((n + kMB - 1) / kMB); }
 struct MetalImpl {
   int64_t n = 0, nt = 0, nf = 0, nnz = 0, ninc = 0, nfin = 0;
   double *xyz = nullptr, *A = nullptr, *b = nullptr, *dinv = nullptr;
-  double *r = nullptr, *z = nullptr, *p = nullptr, *sv = nullptr, *w = nullptr;
+  double *r = nullptr, *z = nullptr, *p = nullptr;
+  MetalRec* rec[2] = {};
   double* part = nullptr;
   int32_t *tet = nullptr, *face = nullptr, *row_ptr = nullptr, *col = nullptr;
   int32_t *sptr = nullptr, *scol = nullptr, *c2s = nullptr;  // sliced ELLPACK
@@ -683,14 +737,17 @@ pic_status metal_build(const pic_metal_desc* d, hipStream_t s, pic_metal** out,
   up(&M.fin_face, fin_face.data(), fin_face.size());
   if (e == hipSuccess) e = dalloc(h, &M.geo, nt);
   if (e == hipSuccess) e = dalloc(h, &M.A, col.size());
-  for (double** v : {&M.b, &M.dinv, &M.r, &M.z, &M.p, &M.sv, &M.w, &M.x})
+  for (double** v : {&M.b, &M.dinv, &M.r, &M.z, &M.p, &M.x})
     if (e == hipSuccess) e = dalloc(h, v, n);
-  // the search directions start as NaN (all bits set): the first CG
-  // iteration must set them outright, and a read before that write would
-  // spoil every solve, not only those on reused memory
+  for (MetalRec*& v : M.rec)
+    if (e == hipSuccess) e = dalloc(h, &v, n);
+  // the search directions and records start as NaN (all bits set): the
+  // first CG iteration must set them outright, and a read before that write
+  // would spoil every solve, not only those on reused memory
   if (e == hipSuccess) e = hipMemsetAsync(M.p, 0xFF, sizeof(double) * (size_t)n, s);
-  if (e == hipSuccess) e = hipMemsetAsync(M.sv, 0xFF, sizeof(double) * (size_t)n, s);
-  if (e == hipSuccess) e = dalloc(h, &M.part, 3 * kMaxS);
+  for (MetalRec* v : M.rec)
+    if (e == hipSuccess) e = hipMemsetAsync(v, 0xFF, sizeof(MetalRec) * (size_t)n, s);
+  if (e == hipSuccess) e = dalloc(h, &M.part, 6 * kMaxS);
   if (e == hipSuccess) e = dalloc(h, &M.ctrl, 1);
   if (e == hipSuccess) e = hipMemsetAsync(M.ctrl, 0, sizeof(MetalCtrl), s);
   int32_t* bad = nullptr;
@@ -739,18 +796,17 @@ CgArgsM cg_args(MetalImpl& M, double dir_value, double tol) {
   a.n = M.n; a.row_ptr = M.row_ptr; a.col = M.col; a.A = M.A; a.b = M.b;
   a.sptr = M.sptr; a.scol = M.scol; a.sval = M.sval;
   a.dinv = M.dinv; a.dir = M.dir; a.dir_value = dir_value; a.tol2 = tol * tol;
-  a.x = M.x; a.r = M.r; a.z = M.z; a.p = M.p; a.s = M.sv; a.w = M.w; a.part = M.part;
+  a.x = M.x; a.r = M.r; a.z = M.z; a.p = M.p; a.part = M.part;
+  a.rec[0] = M.rec[0]; a.rec[1] = M.rec[1];
   a.ctrl = M.ctrl; a.G = M.G;
   a.Gs = (int)std::min<int64_t>(kMaxS, (M.n + kMB - 1) / kMB);  // 4 slices each
   return a;
 }
 
-// One iteration: the step (which first tests the incoming iterate) and the
-// product for the next one.
-void launch_iter(const CgArgsM& a, hipStream_t s) {
-  const dim3 g(a.G), b(kMB);
-  hipLaunchKernelGGL(k_cg_step, g, b, 0, s, a);
-  hipLaunchKernelGGL(k_cg_spmv, dim3(a.Gs), b, 0, s, a);
+// count iterations from an even one.
+void launch_iters(const CgArgsM& a, int64_t count, hipStream_t s) {
+  for (int64_t k = 0; k < count; ++k)
+    hipLaunchKernelGGL(k_cg_iter, dim3(a.Gs), dim3(kMB), 0, s, a, (int)(k & 1));
 }
 
 // Capture count iterations into a graph on a private stream (capture is
@@ -762,7 +818,7 @@ hipError_t capture_iters(MetalImpl& M, int count, hipGraph_t* graph, hipGraphExe
   const CgArgsM a = cg_args(M, 0.0, 1.0);
   e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    for (int k = 0; k < count; ++k) launch_iter(a, cs);
+    launch_iters(a, count, cs);
     hipError_t e2 = hipStreamEndCapture(cs, graph);
     e = hipGetLastError();
     if (e == hipSuccess) e = e2;
@@ -792,7 +848,7 @@ pic_status run_cg(pic_metal* h, double* x, double dir_value, double tol,
     hipLaunchKernelGGL(k_cg_dir, g, b, 0, s, a);
     hipLaunchKernelGGL(k_cg_init, g, b, 0, s, a);
     hipLaunchKernelGGL(k_cg_start, dim3(1), b, 0, s, a);
-    hipLaunchKernelGGL(k_cg_spmv, dim3(a.Gs), b, 0, s, a);
+    hipLaunchKernelGGL(k_cg_first, dim3(a.Gs), b, 0, s, a);
     e = hipGetLastError();
   }
   // a first chunk of kChunk iterations (short solves, such as a heat step,
@@ -813,7 +869,8 @@ pic_status run_cg(pic_metal* h, double* x, double dir_value, double tol,
       e = hipGraphLaunch(M.chunk, s);
       it += kChunk;
     } else {
-      for (; it < max_iter; ++it) launch_iter(a, s);
+      launch_iters(a, max_iter - it, s);
+      it = max_iter;
       e = hipGetLastError();
     }
   }
