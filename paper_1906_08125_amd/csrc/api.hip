@@ -1560,10 +1560,17 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
   if ((e = hipEventRecord(b->uploaded, s)) != hipSuccess) return hip_fail(e, "pic_batch_step");
   std::vector<int> c_part(n);
   for (int i = 0; i < n; ++i) c_part[i] = c_push[i] + c_inj[i];
-  const fp::BatchMap m_clear = batch_map(c_clear), m_part = batch_map(c_part),
-                     m_fb = batch_map(c_fb), m_stats = batch_map(c_stats),
+  // the particle launches: instances without packed tet records, then those
+  // that have them
+  std::vector<char> has_pk(n), no_pk(n);
+  for (int i = 0; i < n; ++i) {
+    has_pk[i] = b->h[i]->dm.tc != nullptr;
+    no_pk[i] = !has_pk[i];
+  }
+  const fp::BatchMap m_part[2] = {batch_map(c_part, no_pk), batch_map(c_part, has_pk)};
+  const fp::BatchMap m_clear = batch_map(c_clear), m_fb = batch_map(c_fb), m_stats = batch_map(c_stats),
                      m_cg = batch_map(c_cg);
-  const int g_clear = m_clear.off[n], g_part = m_part.off[n], g_fb = m_fb.off[n],
+  const int g_clear = m_clear.off[n], g_fb = m_fb.off[n],
             g_stats = m_stats.off[n], g_cg = m_cg.off[n];
   (void)g_cg;
   pic_mesh* h0 = b->h[0];
@@ -1580,8 +1587,11 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       return hip_fail(e, "pic_batch_step begin");
     prof_end(h0, s);
     prof_begin(h0, PIC_K_PUSH, s);
-    if ((e = fp::launch_particles_b(A, m_part, g_part, f32 ? 1 : 0, s)) != hipSuccess)
-      return hip_fail(e, "pic_batch_step particles");
+    for (int pk = 0; pk < 2; ++pk)
+      if (m_part[pk].n_seg > 0 &&
+          (e = fp::launch_particles_b(A, m_part[pk], m_part[pk].off[m_part[pk].n_seg],
+                                      f32 ? 1 : 0, pk, s)) != hipSuccess)
+        return hip_fail(e, "pic_batch_step particles");
     prof_end(h0, s);
     prof_begin(h0, PIC_K_FALLBACK, s);
     if ((e = fp::launch_fallback_b(A, m_fb, g_fb, s)) != hipSuccess ||

@@ -55,13 +55,32 @@ struct alignas(128) TetGeom {
 static_assert(sizeof(TetGeom) == 128, "TetGeom is one line");
 
 // FP32 copy of the map and vertex ids, for the mixed-precision field
-// gather only (the walk and the deposition use TetGeom).
+// gather only (the walk and the deposition use TetGeom); meshes without
+// packed records only.
 struct alignas(64) TetGeom32 {
   float v0[3];
   float m[9];
   int32_t node[4];
 };
 static_assert(sizeof(TetGeom32) == 64, "TetGeom32 is half a line");
+
+// The same record for meshes with few distinct maps (the cubes' six on a
+// Kuhn lattice): half a line, the map's place in a table that the particle
+// kernels hold in LDS instead of the nine numbers.  A visit of the particle
+// loop then gathers three 16-byte words per lane instead of eight (the
+// neighbour of the exit face is read when the walk leaves the tet).
+// Table entry: the map (9), then lam_c max_j |m_kj| for k = 1..3 (see
+// lam_test).
+constexpr int kMapMax = 32;
+constexpr int kMapLen = 12;
+struct alignas(64) TetPack {
+  double v0[3];
+  uint32_t map;
+  uint32_t pad;
+  int32_t node[4];
+  uint32_t nbr[4];
+};
+static_assert(sizeof(TetPack) == 64, "TetPack is half a line");
 
 // A sparse matrix in sliced ELLPACK (kSell rows per slice, column-major
 // inside a slice) in one of two forms.  Packed (code != null): one 32-bit
@@ -86,6 +105,12 @@ struct DevMesh {
   double Lx, Ly, z_top;
   const TetWalk* tw;
   const TetGeom* tg;
+  // packed records and their table (FP64, and rounded to FP32 for the
+  // mixed-precision gather), or null where a mesh has more than kMapMax
+  // distinct maps, which has tg32 instead
+  const TetPack* tc;
+  const double* maps;       // [kMapMax][kMapLen]
+  const float* maps32;
   const TetGeom32* tg32;
   // Jacobi inverse diagonal of the stiffness on free nodes
   const double* invdiag;

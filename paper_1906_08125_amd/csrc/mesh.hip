@@ -139,6 +139,40 @@ void* mesh_mem(pic_mesh* h, size_t bytes, hipError_t& err) {
   return p;
 }
 
+// The packed records of a mesh with at most kMapMax distinct maps (equal
+// bit for bit, so nothing is lost) and the table; false for other meshes.
+bool pack_records(const std::vector<TetGeom>& tg, double lam_c,
+                  std::vector<double>& maps, std::vector<TetPack>& tc) {
+  const size_t T = tg.size();
+  int n = 0;
+  maps.assign((size_t)kMapMax * kMapLen, 0.0);
+  tc.resize(T);
+  for (size_t t = 0; t < T; ++t) {
+    const TetGeom& g = tg[t];
+    int k = 0;
+    while (k < n && std::memcmp(&maps[(size_t)k * kMapLen], g.m, sizeof g.m) != 0) ++k;
+    if (k == n) {
+      if (n == kMapMax) return false;
+      double* e = &maps[(size_t)n++ * kMapLen];
+      std::memcpy(e, g.m, sizeof g.m);
+      for (int r = 0; r < 3; ++r) {
+        const double* m = g.m + 3 * r;
+        e[9 + r] = lam_c * std::max(std::max(std::fabs(m[0]), std::fabs(m[1])),
+                                    std::fabs(m[2]));
+      }
+    }
+    TetPack& p = tc[t];
+    for (int c = 0; c < 3; ++c) p.v0[c] = g.v0[c];
+    p.map = (uint32_t)k;
+    p.pad = 0;
+    for (int c = 0; c < 4; ++c) {
+      p.node[c] = g.node[c];
+      p.nbr[c] = g.nbr[c];
+    }
+  }
+  return true;
+}
+
 template <typename T>
 T* upload(pic_mesh* h, const std::vector<T>& v, hipError_t& err) {
   void* p = mesh_mem(h, v.size() * sizeof(T), err);
@@ -662,7 +696,17 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   M.z_top = d->z_top;
   M.tw = upload(h, tw, err);
   M.tg = upload(h, tg, err);
-  {
+  // |lambda_k - lambda*_k| <= lam_c max_j |m_kj| |d|_1 (see lam_test)
+  M.lam_c = (4.01 + 1.01 * kappa) * 1.1102230246251565e-16;
+  std::vector<double> maps;
+  std::vector<TetPack> tc;
+  const bool packed = pack_records(tg, M.lam_c, maps, tc);
+  if (packed) {
+    const std::vector<float> maps32(maps.begin(), maps.end());
+    M.tc = upload(h, tc, err);
+    M.maps = upload(h, maps, err);
+    M.maps32 = upload(h, maps32, err);
+  } else {
     std::vector<TetGeom32> tg32(T);
     for (int64_t t = 0; t < T; ++t) {
       for (int k = 0; k < 3; ++k) tg32[t].v0[k] = (float)tg[t].v0[k];
@@ -796,8 +840,6 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
     M.finv[k] = (double)kFineSeed * M.binv[k];
   }
   M.jump_len2 = (0.25 * edge) * (0.25 * edge);
-  // |lambda_k - lambda*_k| <= lam_c max_j |m_kj| |d|_1 (see lam_test)
-  M.lam_c = (4.01 + 1.01 * kappa) * 1.1102230246251565e-16;
   M.fseed = (int32_t*)dev_alloc(
       h, sizeof(int32_t) * (size_t)M.fnb[0] * M.fnb[1] * M.fnb[2], err);
   if (err == hipSuccess && !h->ws_dry)
@@ -811,7 +853,7 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   // tip: 3 resident per CU, 91 us per push against 100 us for 8 per CU and
   // 107 us for 4), and fewer injecting workgroups queue behind it.
   for (int f32 = 0; f32 < 2; ++f32) {
-    const int per_cu = std::max(1, particle_blocks_per_cu(f32));
+    const int per_cu = std::max(1, particle_blocks_per_cu(f32, packed));
     int g = std::min(h->grid_push, std::max(8, h->n_cu * per_cu));
     h->step_push[f32] = g >= 8 ? g - g % 8 : g;
   }

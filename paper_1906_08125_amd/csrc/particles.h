@@ -90,9 +90,10 @@ struct DepositArgs {
 };
 
 hipError_t launch_begin(const EmitArgs& a, int grid, hipStream_t s);
-// Workgroups of the particle kernel (FP64 or FP32 storage) resident on one
-// compute unit at once, by the runtime's occupancy calculator (0 on error).
-int particle_blocks_per_cu(int f32);
+// Workgroups of the particle kernel (FP64 or FP32 storage; packed tet records
+// or not) resident on one compute unit at once, by the runtime's occupancy
+// calculator (0 on error).
+int particle_blocks_per_cu(int f32, int packed);
 // e: the step's emission, computed by workgroup 0 while the others push
 // (e.defer set; the injecting workgroups wait for it), or null
 hipError_t launch_particles(const StepArgs& a, const EmitArgs* e, int g_push,
@@ -109,8 +110,9 @@ hipError_t launch_deposit(const DepositArgs& a, int grid, hipStream_t s);
 // block schedules given (one schedule per kernel kind).
 hipError_t launch_begin_b(const EmitArgs* E, const BatchMap& map, int grid,
                           hipStream_t s);
+// (the instances of one launch all have packed tet records, or none has)
 hipError_t launch_particles_b(const StepArgs* A, const BatchMap& map, int grid,
-                              int f32, hipStream_t s);
+                              int f32, int packed, hipStream_t s);
 hipError_t launch_fallback_b(const StepArgs* A, const BatchMap& map, int grid,
                              hipStream_t s);
 hipError_t launch_stats_b(const StepArgs* A, const BatchMap& map, int grid,

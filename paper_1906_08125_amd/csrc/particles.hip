@@ -109,16 +109,122 @@ __device__ inline double4 ld_E(const void* E, int f32, int32_t node) {
   return reinterpret_cast<const double4*>(E)[node];
 }
 
+// A tet's record in registers, from the mesh's 128-byte records or, where
+// it has them, from the packed ones and the table of maps in LDS.  The two
+// give the same bits everywhere; the kernels are compiled for either.
+// Packed, the FP64 push needs fewer registers and gathers 17 words per
+// particle where it gathered 28: see k_particles.
+typedef __attribute__((address_space(3))) const double* lds_d;
+typedef __attribute__((address_space(3))) const float* lds_f;
+
+struct MapTable {
+  double m[kMapMax * kMapLen];
+  float m32[kMapMax * kMapLen];
+};
+
+// (the caller synchronizes)
+__device__ inline void maps_load(const DevMesh& m, MapTable& M, bool f32) {
+  for (int k = threadIdx.x; k < kMapMax * kMapLen; k += blockDim.x) {
+    M.m[k] = m.maps[k];
+    if (f32) M.m32[k] = m.maps32[k];
+  }
+}
+
+template <bool PK>
+struct Geo;
+
+template <>
+struct Geo<false> {
+  TetGeom g;
+  __device__ inline void load(const DevMesh& m, int t) { g = m.tg[t]; }
+  __device__ inline const int32_t* node() const { return g.node; }
+  __device__ inline void origin(double v[3]) const {
+    v[0] = g.v0[0];
+    v[1] = g.v0[1];
+    v[2] = g.v0[2];
+  }
+  __device__ inline void map(const MapTable*, double r[9]) const {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r[k] = g.m[k];
+  }
+  // lam_c max_j |m_kj|
+  __device__ inline double bound(const DevMesh& m, const MapTable*, int k) const {
+    const double* r = g.m + 3 * (k - 1);
+    return m.lam_c * fmax(fmax(fabs(r[0]), fabs(r[1])), fabs(r[2]));
+  }
+  // (selects, not an indexed load: the record stays in registers)
+  __device__ inline uint32_t nbr(const DevMesh&, int, int f) const {
+    return f == 0 ? g.nbr[0] : f == 1 ? g.nbr[1] : f == 2 ? g.nbr[2] : g.nbr[3];
+  }
+};
+
+template <>
+struct Geo<true> {
+  double v0[3];
+  uint32_t mp;
+  int32_t nd[4];
+  __device__ inline void load(const DevMesh& m, int t) {
+    const TetPack* p = m.tc + t;
+    v0[0] = p->v0[0];
+    v0[1] = p->v0[1];
+    v0[2] = p->v0[2];
+    mp = p->map * kMapLen;
+    const int4 n = *reinterpret_cast<const int4*>(p->node);
+    nd[0] = n.x;
+    nd[1] = n.y;
+    nd[2] = n.z;
+    nd[3] = n.w;
+  }
+  __device__ inline const int32_t* node() const { return nd; }
+  __device__ inline void origin(double v[3]) const {
+    v[0] = v0[0];
+    v[1] = v0[1];
+    v[2] = v0[2];
+  }
+  __device__ inline void map(const MapTable* M, double r[9]) const {
+    const lds_d q = (lds_d)M->m + mp;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r[k] = q[k];
+  }
+  __device__ inline double bound(const DevMesh&, const MapTable* M, int k) const {
+    return ((lds_d)M->m + mp)[8 + k];
+  }
+  __device__ inline uint32_t nbr(const DevMesh& m, int t, int f) const {
+    return m.tc[t].nbr[f];
+  }
+};
+
+// Barycentric coordinates of p in tet g (the fixed arithmetic of
+// barycentric()).
+template <bool PK>
+__device__ inline void geo_lam(const Geo<PK>& g, const MapTable* M, double px,
+                               double py, double pz, double lam[4]) {
+  double v[3], r[9];
+  g.origin(v);
+  g.map(M, r);
+  const double dx = px - v[0], dy = py - v[1], dz = pz - v[2];
+  const double l1 = (r[0] * dx + r[1] * dy) + r[2] * dz;
+  const double l2 = (r[3] * dx + r[4] * dy) + r[5] * dz;
+  const double l3 = (r[6] * dx + r[7] * dy) + r[8] * dz;
+  lam[0] = ((1.0 - l1) - l2) - l3;
+  lam[1] = l1;
+  lam[2] = l2;
+  lam[3] = l3;
+}
+
 // Field at p inside tet g: sum_i lambda_i E_i in a fixed order.
-__device__ inline void gather_field(const TetGeom& g, const void* E,
-                                    double x, double y, double z,
-                                    double& ex, double& ey, double& ez) {
+template <bool PK>
+__device__ inline void gather_field(const Geo<PK>& g, const MapTable* M,
+                                    const void* E, double x, double y,
+                                    double z, double& ex, double& ey,
+                                    double& ez) {
+  const int32_t* nd = g.node();
+  const double4 e0 = ld_E(E, 0, nd[0]);
+  const double4 e1 = ld_E(E, 0, nd[1]);
+  const double4 e2 = ld_E(E, 0, nd[2]);
+  const double4 e3 = ld_E(E, 0, nd[3]);
   double lam[4];
-  barycentric(g, x, y, z, lam);
-  const double4 e0 = ld_E(E, 0, g.node[0]);
-  const double4 e1 = ld_E(E, 0, g.node[1]);
-  const double4 e2 = ld_E(E, 0, g.node[2]);
-  const double4 e3 = ld_E(E, 0, g.node[3]);
+  geo_lam<PK>(g, M, x, y, z, lam);
   ex = ((lam[0] * e0.x + lam[1] * e1.x) + lam[2] * e2.x) + lam[3] * e3.x;
   ey = ((lam[0] * e0.y + lam[1] * e1.y) + lam[2] * e2.y) + lam[3] * e3.y;
   ez = ((lam[0] * e0.z + lam[1] * e1.z) + lam[2] * e2.z) + lam[3] * e3.z;
@@ -127,19 +233,30 @@ __device__ inline void gather_field(const TetGeom& g, const void* E,
 // Cell field of a tet (cell mode): E = -(grad phi)_t with grad lambda_k the
 // rows m_k (k = 1..3) and grad lambda_0 = -(m_1 + m_2 + m_3), summed in a
 // fixed order.
-__device__ inline void cell_field(const TetGeom& g, const double* phi,
-                                  double& ex, double& ey, double& ez) {
-  const double p0 = phi[g.node[0]], p1 = phi[g.node[1]], p2 = phi[g.node[2]],
-               p3 = phi[g.node[3]];
-  double e[3];
+template <bool PK>
+__device__ inline void cell_field(const Geo<PK>& g, const MapTable* M,
+                                  const double* phi, double& ex, double& ey,
+                                  double& ez) {
+  const int32_t* nd = g.node();
+  const double p0 = phi[nd[0]], p1 = phi[nd[1]], p2 = phi[nd[2]], p3 = phi[nd[3]];
+  double r[9], e[3];
+  g.map(M, r);
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double g0 = -((g.m[k] + g.m[3 + k]) + g.m[6 + k]);
-    e[k] = -(((p0 * g0 + p1 * g.m[k]) + p2 * g.m[3 + k]) + p3 * g.m[6 + k]);
+    const double g0 = -((r[k] + r[3 + k]) + r[6 + k]);
+    e[k] = -(((p0 * g0 + p1 * r[k]) + p2 * r[3 + k]) + p3 * r[6 + k]);
   }
   ex = e[0];
   ey = e[1];
   ez = e[2];
+}
+
+// The cell field of an emitting face's tet.
+__device__ inline void face_cell_field(const DevMesh& m, int t, const double* phi,
+                                       double& ex, double& ey, double& ez) {
+  Geo<false> g;
+  g.load(m, t);
+  cell_field<false>(g, nullptr, phi, ex, ey, ez);
 }
 
 __device__ inline void deposit_one(const TetGeom& g, double x, double y,
@@ -190,18 +307,18 @@ __device__ inline int fine_seed(const DevMesh& m, double x, double y,
 // lambda_k > B_k, i.e. p is certainly strictly inside.  Otherwise exitf is
 // the face (opposite vertex k) with the most negative lambda_k among those
 // certainly negative (lambda_k < -B_k), or -1 when there is none.
-__device__ inline bool lam_test(const TetGeom& g, double x, double y, double z,
-                                double C, double lam[4], int& exitf) {
-  barycentric(g, x, y, z, lam);
-  const double dx = x - g.v0[0], dy = y - g.v0[1], dz = z - g.v0[2];
+template <bool PK>
+__device__ inline bool lam_test(const DevMesh& m, const Geo<PK>& g,
+                                const MapTable* M, double x, double y, double z,
+                                double lam[4], int& exitf) {
+  geo_lam<PK>(g, M, x, y, z, lam);
+  double v[3];
+  g.origin(v);
+  const double dx = x - v[0], dy = y - v[1], dz = z - v[2];
   const double dn = (fabs(dx) + fabs(dy)) + fabs(dz);
   double B[4];
 #pragma unroll
-  for (int k = 1; k < 4; ++k) {
-    const double* r = g.m + 3 * (k - 1);
-    const double M = fmax(fmax(fabs(r[0]), fabs(r[1])), fabs(r[2]));
-    B[k] = (C * M) * dn;
-  }
+  for (int k = 1; k < 4; ++k) B[k] = g.bound(m, M, k) * dn;
   B[0] = 3.01 * 1.1102230246251565e-16 *
              (((1.0 + fabs(lam[1])) + fabs(lam[2])) + fabs(lam[3])) +
          1.0001 * ((B[1] + B[2]) + B[3]);
@@ -227,9 +344,11 @@ __device__ inline bool lam_test(const TetGeom& g, double x, double y, double z,
 // frame (then no other tet holds it, so it is the canonical answer), with
 // lam its barycentric coordinates there and G its record, or -1 when the
 // exact bucket scan must decide.
-__device__ inline int walk(const DevMesh& m, double x, double y, double z,
-                           int t, int sx, int sy, int& steps, bool far,
-                           TetGeom& G, double lam[4], bool have_G = true) {
+template <bool PK>
+__device__ inline int walk(const DevMesh& m, const MapTable* M, double x,
+                           double y, double z, int t, int sx, int sy,
+                           int& steps, bool far, Geo<PK>& G, double lam[4],
+                           bool have_G = true) {
   bool jumped = false;
   for (steps = 0; steps < kMaxWalk; ++steps) {
     bool reload = steps > 0 || !have_G;
@@ -244,17 +363,13 @@ __device__ inline int walk(const DevMesh& m, double x, double y, double z,
         reload = true;
       }
     }
-    if (reload) G = m.tg[t];
+    if (reload) G.load(m, t);
     int exitf;
-    if (lam_test(G, x + (double)sx * m.Lx, y + (double)sy * m.Ly, z, m.lam_c,
-                 lam, exitf))
+    if (lam_test<PK>(m, G, M, x + (double)sx * m.Lx, y + (double)sy * m.Ly, z,
+                     lam, exitf))
       return (sx == 0 && sy == 0) ? t : -1;
     if (exitf < 0) return -1;
-    // (selects, not an indexed load: G stays in registers)
-    const uint32_t nb = exitf == 0 ? G.nbr[0]
-                        : exitf == 1 ? G.nbr[1]
-                        : exitf == 2 ? G.nbr[2]
-                                     : G.nbr[3];
+    const uint32_t nb = G.nbr(m, t, exitf);
     if ((nb & kNoNbr) == kNoNbr) return -1;
     sx += (int)((nb >> 28) & 3u) - 1;
     sy += (int)(nb >> 30) - 1;
@@ -375,19 +490,21 @@ __device__ inline void table_flush(ChargeTable& T, int64_t* charge) {
   }
 }
 
-__device__ inline void deposit_table(const TetGeom& g, const double lam[4],
+__device__ inline void deposit_table(const int32_t* node, const double lam[4],
                                      double w, ChargeTable& T,
                                      int64_t* charge) {
   int64_t q[4];
   charge_split(lam, w, q);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) table_add(T, g.node[k], q[k], charge);
+  for (int k = 0; k < 4; ++k) table_add(T, node[k], q[k], charge);
 }
 
 // G: the record of the hint tet (have_G), or to be loaded when needed.
-__device__ inline void settle(const DevMesh& m, const StepArgs& a, int64_t i,
-                              double x, double y, double z, int sx, int sy,
-                              int hint, TetGeom& G, double w, long long qfx,
+template <bool PK>
+__device__ inline void settle(const DevMesh& m, const MapTable* M,
+                              const StepArgs& a, int64_t i, double x, double y,
+                              double z, int sx, int sy, int hint, Geo<PK>& G,
+                              double w, long long qfx,
                               Acc& acc, ChargeTable& T, bool far,
                               bool have_G = true) {
   if (z >= m.z_top) {
@@ -398,12 +515,12 @@ __device__ inline void settle(const DevMesh& m, const StepArgs& a, int64_t i,
   }
   int steps = 0;
   double lam[4];
-  const int t = walk(m, x, y, z, hint, sx, sy, steps, far, G, lam, have_G);
+  const int t = walk<PK>(m, M, x, y, z, hint, sx, sy, steps, far, G, lam, have_G);
   acc.walk_steps += steps;
   if (steps > acc.walk_max) acc.walk_max = steps;
   if (t >= 0) {
     a.tet[i] = t;
-    deposit_table(G, lam, w, T, a.charge);
+    deposit_table(G.node(), lam, w, T, a.charge);
     acc.n_after += 1;
     acc.q_after += qfx;
   } else {
@@ -488,7 +605,7 @@ __device__ void emit_block(const EmitArgs& a) {
     if (f < m.n_emit) {
       double ex, ey, ez;
       if (a.cell)
-        cell_field(m.tg[m.e_tet[f]], a.phi, ex, ey, ez);
+        face_cell_field(m, m.e_tet[f], a.phi, ex, ey, ez);
       else
         face_field(m, a.E, a.f32, f, ex, ey, ez);
       F = sqrt((ex * ex + ey * ey) + ez * ez);
@@ -652,8 +769,9 @@ __device__ inline T& at_off(const void* base, uint32_t bytes) {
   return *reinterpret_cast<T*>(reinterpret_cast<char*>(const_cast<void*>(base)) + bytes);
 }
 
-__device__ inline void push_role64(const StepArgs& a, int g, int G, Acc& acc,
-                                   ChargeTable& T) {
+template <bool PK>
+__device__ inline void push_role64(const StepArgs& a, const MapTable* M, int g,
+                                   int G, Acc& acc, ChargeTable& T) {
   const DevMesh& m = a.m;
   const int64_t n = a.scratch->inj_base;
   const Span sp = block_span(n, G, g);
@@ -681,12 +799,13 @@ __device__ inline void push_role64(const StepArgs& a, int g, int G, Acc& acc,
     double x = at_off<double>(X, o8), y = at_off<double>(Y, o8), z = at_off<double>(Z, o8);
     double vx = at_off<double>(VX, o8), vy = at_off<double>(VY, o8),
            vz = at_off<double>(VZ, o8);
-    TetGeom G = m.tg[t];
+    Geo<PK> R;
+    R.load(m, t);
     double ex, ey, ez;
     if (a.cell)
-      cell_field(G, a.phi, ex, ey, ez);
+      cell_field<PK>(R, M, a.phi, ex, ey, ez);
     else
-      gather_field(G, a.E, x, y, z, ex, ey, ez);
+      gather_field<PK>(R, M, a.E, x, y, z, ex, ey, ez);
     const double qx = Q * ex, qy = Q * ey, qz = Q * ez;
     vx = (vx + qx) + qx;
     vy = (vy + qy) + qy;
@@ -704,15 +823,16 @@ __device__ inline void push_role64(const StepArgs& a, int g, int G, Acc& acc,
     at_off<double>(VX, o8) = vx;
     at_off<double>(VY, o8) = vy;
     at_off<double>(VZ, o8) = vz;
-    settle(m, a, i, x, y, z, sx, sy, t, G, w, qfx, acc, T, far);
+    settle<PK>(m, M, a, i, x, y, z, sx, sy, t, R, w, qfx, acc, T, far);
   }
 }
 
 // Live particles, mixed precision: FP32 position, velocity, field gather,
 // kick and drift; the barycentric weights, the walk and the deposition take
 // the stored FP32 position widened exactly to FP64.
-__device__ inline void push_role32(const StepArgs& a, int g, int G, Acc& acc,
-                                   ChargeTable& T) {
+template <bool PK>
+__device__ inline void push_role32(const StepArgs& a, const MapTable* M, int g,
+                                   int G, Acc& acc, ChargeTable& T) {
   const DevMesh& m = a.m;
   const int64_t n = a.scratch->inj_base;
   const Span sp = block_span(n, G, g);
@@ -741,28 +861,48 @@ __device__ inline void push_role32(const StepArgs& a, int g, int G, Acc& acc,
     acc.q_before += qfx;
     float x = at_off<float>(X, o4), y = at_off<float>(Y, o4), z = at_off<float>(Z, o4);
     float vx = at_off<float>(VX, o4), vy = at_off<float>(VY, o4), vz = at_off<float>(VZ, o4);
-    // FP32 gather from the FP32 record (half the bytes of the FP64 one,
-    // which the walk loads only when it needs the hint tet itself)
-    const TetGeom32 G32 = m.tg32[t];
+    // FP32 gather, from the packed record rounded to FP32, or from the FP32
+    // record (half the bytes of the FP64 one, which the walk loads only
+    // when it needs the hint tet itself)
+    Geo<PK> R;
+    float v0[3], r[9];
+    int32_t nd[4];
+    if constexpr (PK) {
+      R.load(m, t);
+      const lds_f q = (lds_f)M->m32 + R.mp;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) r[k] = q[k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v0[k] = (float)R.v0[k];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) nd[k] = R.nd[k];
+    } else {
+      const TetGeom32 G32 = m.tg32[t];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) r[k] = G32.m[k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v0[k] = G32.v0[k];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) nd[k] = G32.node[k];
+    }
     float ex, ey, ez;
     if (a.cell) {
       // -(grad phi)_t from the potential differences to vertex 0 (FP64
       // differences, FP32 products: no cancellation of the potential's size)
-      const double p0 = a.phi[G32.node[0]];
-      const float d1 = (float)(a.phi[G32.node[1]] - p0);
-      const float d2 = (float)(a.phi[G32.node[2]] - p0);
-      const float d3 = (float)(a.phi[G32.node[3]] - p0);
-      ex = -((d1 * G32.m[0] + d2 * G32.m[3]) + d3 * G32.m[6]);
-      ey = -((d1 * G32.m[1] + d2 * G32.m[4]) + d3 * G32.m[7]);
-      ez = -((d1 * G32.m[2] + d2 * G32.m[5]) + d3 * G32.m[8]);
+      const double p0 = a.phi[nd[0]];
+      const float d1 = (float)(a.phi[nd[1]] - p0);
+      const float d2 = (float)(a.phi[nd[2]] - p0);
+      const float d3 = (float)(a.phi[nd[3]] - p0);
+      ex = -((d1 * r[0] + d2 * r[3]) + d3 * r[6]);
+      ey = -((d1 * r[1] + d2 * r[4]) + d3 * r[7]);
+      ez = -((d1 * r[2] + d2 * r[5]) + d3 * r[8]);
     } else {
-      const float dx0 = x - G32.v0[0], dy0 = y - G32.v0[1], dz0 = z - G32.v0[2];
-      const float l1 = (G32.m[0] * dx0 + G32.m[1] * dy0) + G32.m[2] * dz0;
-      const float l2 = (G32.m[3] * dx0 + G32.m[4] * dy0) + G32.m[5] * dz0;
-      const float l3 = (G32.m[6] * dx0 + G32.m[7] * dy0) + G32.m[8] * dz0;
+      const float4 e0 = E[nd[0]], e1 = E[nd[1]], e2 = E[nd[2]], e3 = E[nd[3]];
+      const float dx0 = x - v0[0], dy0 = y - v0[1], dz0 = z - v0[2];
+      const float l1 = (r[0] * dx0 + r[1] * dy0) + r[2] * dz0;
+      const float l2 = (r[3] * dx0 + r[4] * dy0) + r[5] * dz0;
+      const float l3 = (r[6] * dx0 + r[7] * dy0) + r[8] * dz0;
       const float l0 = ((1.0f - l1) - l2) - l3;
-      const float4 e0 = E[G32.node[0]], e1 = E[G32.node[1]],
-                   e2 = E[G32.node[2]], e3 = E[G32.node[3]];
       ex = ((l0 * e0.x + l1 * e1.x) + l2 * e2.x) + l3 * e3.x;
       ey = ((l0 * e0.y + l1 * e1.y) + l2 * e2.y) + l3 * e3.y;
       ez = ((l0 * e0.z + l1 * e1.z) + l2 * e2.z) + l3 * e3.z;
@@ -797,13 +937,13 @@ __device__ inline void push_role32(const StepArgs& a, int g, int G, Acc& acc,
     at_off<float>(VX, o4) = vx;
     at_off<float>(VY, o4) = vy;
     at_off<float>(VZ, o4) = vz;
-    TetGeom G4;
-    settle(m, a, i, x, y, z, sx, sy, t, G4, w, qfx, acc, T, far, false);
+    settle<PK>(m, M, a, i, x, y, z, sx, sy, t, R, w, qfx, acc, T, far, PK);
   }
 }
 
-__device__ inline void inject_role(const StepArgs& a, int g, int G, Acc& acc,
-                                   ChargeTable& T) {
+template <bool PK>
+__device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
+                                   int G, Acc& acc, ChargeTable& T) {
   const DevMesh& m = a.m;
   const int64_t n = a.scratch->inj_fit;
   const int64_t base = a.scratch->inj_base;
@@ -835,7 +975,7 @@ __device__ inline void inject_role(const StepArgs& a, int g, int G, Acc& acc,
     const double pz = (A[2] + R1 * (A[5] - A[2])) + R2 * (A[8] - A[2]);
     double Ex, Ey, Ez;
     if (a.cell) {
-      cell_field(m.tg[m.e_tet[f]], a.phi, Ex, Ey, Ez);
+      face_cell_field(m, m.e_tet[f], a.phi, Ex, Ey, Ez);
     } else {
       const int32_t* nd = m.e_nodes + 3 * (int64_t)f;
       const double4 ea = ld_E(a.E, a.f32, nd[0]);
@@ -884,8 +1024,9 @@ __device__ inline void inject_role(const StepArgs& a, int g, int G, Acc& acc,
     acc.n_inj += 1;
     acc.q_inj += qfx;
     const int h = m.e_tet[f];
-    TetGeom G = m.tg[h];
-    settle(m, a, i, x, y, z, sx, sy, h, G, w, qfx, acc, T, false);
+    Geo<PK> H;
+    H.load(m, h);
+    settle<PK>(m, M, a, i, x, y, z, sx, sy, h, H, w, qfx, acc, T, false);
   }
 }
 
@@ -924,22 +1065,29 @@ __device__ inline bool emit_wait(const StepArgs& a) {
   return seen != 0;
 }
 
-// One instance per storage precision, so that only one push is compiled in.
-// wait: the injecting workgroups wait for the emission (see emit_wait).
-template <bool F32>
+// One instance per storage precision and record form, so that only one push
+// is compiled in.  wait: the injecting workgroups wait for the emission (see
+// emit_wait).
+template <bool F32, bool PK>
 __device__ inline void particles_body(const StepArgs& a, VB vb, bool wait) {
   Acc acc;
   acc_zero(acc);
   __shared__ ChargeTable T;
-  table_clear(T);
+  const MapTable* M = nullptr;
+  if constexpr (PK) {
+    __shared__ MapTable maps;
+    maps_load(a.m, maps, F32);
+    M = &maps;
+  }
+  table_clear(T);  // (synchronizes)
   const int g_push = a.g_push;
   if (vb.id < g_push) {
     if (F32)
-      push_role32(a, vb.id, g_push, acc, T);
+      push_role32<PK>(a, M, vb.id, g_push, acc, T);
     else
-      push_role64(a, vb.id, g_push, acc, T);
+      push_role64<PK>(a, M, vb.id, g_push, acc, T);
   } else if (!wait || emit_wait(a)) {
-    inject_role(a, vb.id - g_push, vb.n - g_push, acc, T);
+    inject_role<PK>(a, M, vb.id - g_push, vb.n - g_push, acc, T);
   }
   table_flush(T, a.charge);
   acc_flush(acc, a.acc_rows, vb.id, a.acc_stride);
@@ -952,25 +1100,25 @@ __device__ inline void particles_body(const StepArgs& a, VB vb, bool wait) {
 // and spills 9 dwords per lane at this bound, which the fourth wave's latency
 // hiding more than pays for (86.6 against 90.4 us per push at 1e6
 // superparticles); the FP32 push fits in 124 either way.
-template <bool F32>
+template <bool F32, bool PK>
 __global__ void __launch_bounds__(kBlock, 4) k_particles(StepArgs a, EmitArgs e) {
   if (gate_closed(a.gate)) return;
   if (!e.defer) {
-    particles_body<F32>(a, VB{(int)blockIdx.x, (int)gridDim.x}, false);
+    particles_body<F32, PK>(a, VB{(int)blockIdx.x, (int)gridDim.x}, false);
   } else if (blockIdx.x == 0) {
     emit_publish(e);
   } else {
-    particles_body<F32>(a, VB{(int)blockIdx.x - 1, (int)gridDim.x - 1}, true);
+    particles_body<F32, PK>(a, VB{(int)blockIdx.x - 1, (int)gridDim.x - 1}, true);
   }
 }
 
-template <bool F32>
+template <bool F32, bool PK>
 __global__ void __launch_bounds__(kBlock) k_particles_b(const StepArgs* A,
                                                         BatchMap map) {
   int i;
   const VB vb = batch_block(map, i);
   const StepArgs a = A[i];  // a private copy: no aliasing with the stores
-  particles_body<F32>(a, vb, false);
+  particles_body<F32, PK>(a, vb, false);
 }
 
 // ---------------------------------------------------------------------------
@@ -1052,8 +1200,16 @@ __global__ void __launch_bounds__(kBlock) k_stats_b(const StepArgs* A,
 // ---------------------------------------------------------------------------
 // Stand-alone location and deposition entry points.
 // ---------------------------------------------------------------------------
+template <bool PK>
 __global__ void __launch_bounds__(kBlock) k_locate(LocateArgs a) {
   const DevMesh& m = a.m;
+  const MapTable* M = nullptr;
+  if constexpr (PK) {
+    __shared__ MapTable maps;
+    maps_load(m, maps, false);
+    M = &maps;
+    __syncthreads();
+  }
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < a.n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const double x = a.x[i], y = a.y[i], z = a.z[i];
@@ -1065,9 +1221,10 @@ __global__ void __launch_bounds__(kBlock) k_locate(LocateArgs a) {
     const int h = a.tet[i];
     int t = -1, steps = 0;
     if (h >= 0 && h < m.n_tets) {
-      TetGeom G = m.tg[h];
+      Geo<PK> G;
+      G.load(m, h);
       double lam[4];
-      t = walk(m, x, y, z, h, 0, 0, steps, false, G, lam);
+      t = walk<PK>(m, M, x, y, z, h, 0, 0, steps, false, G, lam);
     }
     if (t >= 0) {
       a.tet[i] = t;
@@ -1137,11 +1294,10 @@ hipError_t launch_begin_b(const EmitArgs* E, const BatchMap& map, int grid,
   return hipGetLastError();
 }
 hipError_t launch_particles_b(const StepArgs* A, const BatchMap& map, int grid,
-                              int f32, hipStream_t s) {
-  if (f32)
-    hipLaunchKernelGGL(k_particles_b<true>, dim3(grid), dim3(kBlock), 0, s, A, map);
-  else
-    hipLaunchKernelGGL(k_particles_b<false>, dim3(grid), dim3(kBlock), 0, s, A, map);
+                              int f32, int packed, hipStream_t s) {
+  const auto kern = packed ? (f32 ? k_particles_b<true, true> : k_particles_b<false, true>)
+                           : (f32 ? k_particles_b<true, false> : k_particles_b<false, false>);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, A, map);
   return hipGetLastError();
 }
 hipError_t launch_fallback_b(const StepArgs* A, const BatchMap& map, int grid,
@@ -1154,11 +1310,11 @@ hipError_t launch_stats_b(const StepArgs* A, const BatchMap& map, int grid,
   hipLaunchKernelGGL(k_stats_b, dim3(grid), dim3(kBlock), 0, s, A, map);
   return hipGetLastError();
 }
-int particle_blocks_per_cu(int f32) {
+int particle_blocks_per_cu(int f32, int packed) {
   int n = 0;
-  const hipError_t e =
-      f32 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_particles<true>, kBlock, 0)
-          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_particles<false>, kBlock, 0);
+  const auto kern = packed ? (f32 ? k_particles<true, true> : k_particles<false, true>)
+                           : (f32 ? k_particles<true, false> : k_particles<false, false>);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, kBlock, 0);
   return e == hipSuccess ? n : 0;
 }
 
@@ -1173,10 +1329,9 @@ hipError_t launch_particles(const StepArgs& a, const EmitArgs* e, int g_push,
     ee = EmitArgs{};
   }
   const int grid = g_push + g_inj + (ee.defer ? 1 : 0);
-  if (a.f32)
-    hipLaunchKernelGGL(k_particles<true>, dim3(grid), dim3(kBlock), 0, s, b, ee);
-  else
-    hipLaunchKernelGGL(k_particles<false>, dim3(grid), dim3(kBlock), 0, s, b, ee);
+  const auto kern = a.m.tc ? (a.f32 ? k_particles<true, true> : k_particles<false, true>)
+                           : (a.f32 ? k_particles<true, false> : k_particles<false, false>);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, b, ee);
   return hipGetLastError();
 }
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s) {
@@ -1197,7 +1352,8 @@ hipError_t launch_fallback(const StepArgs& a, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_locate(const LocateArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_locate, dim3(grid), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(a.m.tc ? k_locate<true> : k_locate<false>, dim3(grid), dim3(kBlock), 0,
+                     s, a);
   hipLaunchKernelGGL(k_locate_scan, dim3(grid), dim3(kBlock), 0, s, a);
   return hipGetLastError();
 }
