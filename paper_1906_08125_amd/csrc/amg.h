@@ -24,19 +24,28 @@ struct SellMat {
 
 // One level of the hierarchy.  Level 0 is K on the free nodes; b of level 0
 // is the CG residual and its smoothed output is the CG vector u.
+//
+// The V(1,1)-cycle with weighted-Jacobi smoothing is applied with its
+// products folded at setup.  Pre-smoothing from zero, x = w D^-1 b, leaves
+// the residual (I - w A D^-1) b, so the next level's right-hand side is
+//   Rs b,  Rs = P^T (I - w A D^-1) = Ps^T,  Ps = (I - w D^-1 A) P,
+// and post-smoothing x + P y gives
+//   2 w D^-1 b - w D^-1 A (w D^-1 b) + Ps y.
+// A level is then one launch down and one up (two and two before: the
+// smoothing and the transfer each way), and stores neither x nor the
+// residual.  Ps has the pattern of A P, which the Galerkin product forms
+// anyway.
 struct AmgLevel {
   SellMat A;
   const double* invdiag;
   double omega;   // Jacobi weight 4 / (3 lambda_max(D^-1 A))
-  SellMat P;      // prolongation from the next level (rows: this level)
-  SellMat R;      // restriction P^T (rows: the next level)
+  SellMat Ps;     // smoothed prolongation from the next level (rows: this)
+  SellMat Rs;     // its transpose (rows: the next level)
   double* b;      // right-hand side (levels > 0)
-  double* x;      // pre-smoothed iterate, then corrected
-  double* r;      // residual after pre-smoothing
-  double* t;      // post-smoothed iterate (levels > 0)
+  double* t;      // the cycle's result (levels > 0)
   // FP32 copies for the FP32 V-cycle (mixed precision)
   const float* invdiag32;
-  float *b32, *x32, *r32, *t32;
+  float *b32, *t32;
 };
 
 struct AmgDev {

@@ -222,6 +222,23 @@ HCsr smoothed_p(const HCsr& A, const std::vector<double>& d,
   return P;
 }
 
+// (I - omega D^-1 A) P from P and AP = A P (rows sorted; the pattern of P
+// lies in that of AP, whose rows hold a_ii P_i).
+HCsr smooth_again(const HCsr& P, const HCsr& AP, const std::vector<double>& d,
+                  double omega) {
+  HCsr S = AP;
+  for (int64_t i = 0; i < S.n; ++i) {
+    const double s = -omega / d[i];
+    int64_t q = P.rp[i];
+    const int64_t qe = P.rp[i + 1];
+    for (int64_t p = S.rp[i]; p < S.rp[i + 1]; ++p) {
+      S.v[p] *= s;
+      if (q < qe && P.ci[q] == S.ci[p]) S.v[p] += P.v[q++];
+    }
+  }
+  return S;
+}
+
 struct HSell {
   int64_t nrows = 0, nslices = 0;
   std::vector<int32_t> sptr, col;
@@ -336,14 +353,14 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     }
     A[0].rp[r + 1] = (int64_t)A[0].ci.size();
   }
-  std::vector<HCsr> P, R;
+  std::vector<HCsr> Ps, Rs;
   std::vector<std::vector<double>> diag;
   std::vector<double> omega;
   double theta = 0.08;
   // (at least one level with a smoother: its first kernel holds the
   // stopping test)
-  while ((A.back().n > kAmgCoarseMax || P.empty()) &&
-         (int)P.size() < kAmgMaxLevels) {
+  while ((A.back().n > kAmgCoarseMax || Ps.empty()) &&
+         (int)Ps.size() < kAmgMaxLevels) {
     const HCsr& Al = A.back();
     diag.push_back(diag_of(Al));
     const std::vector<double>& dl = diag.back();
@@ -356,19 +373,20 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     const std::vector<int32_t> agg = aggregate(Al, dl, theta, nc);
     if (nc >= Al.n) break;  // no coarsening possible
     omega.push_back(4.0 / (3.0 * lambda_max(Al, dl)));
-    P.push_back(smoothed_p(Al, dl, agg, nc, omega.back()));
-    R.push_back(transpose(P.back()));
-    const HCsr AP = multiply(Al, P.back());
-    A.push_back(symmetrize(multiply(R.back(), AP)));
+    const HCsr P = smoothed_p(Al, dl, agg, nc, omega.back());
+    const HCsr AP = multiply(Al, P);
+    Ps.push_back(smooth_again(P, AP, dl, omega.back()));
+    Rs.push_back(transpose(Ps.back()));
+    A.push_back(symmetrize(multiply(transpose(P), AP)));
     theta *= 0.5;
   }
-  for (const auto* v : {&A, &P, &R})
+  for (const auto* v : {&A, &Ps, &Rs})
     for (const HCsr& M : *v)
       if (M.rp[M.n] >= (int64_t)1 << 31) {
         msg = "amg: level matrix too large for 32-bit offsets";
         return hipErrorInvalidValue;
       }
-  const int L = (int)P.size();
+  const int L = (int)Ps.size();
   const HCsr& Ac = A.back();
   if (L == 0 || Ac.n > 4 * kAmgCoarseMax) {
     msg = "amg: the operator does not coarsen";
@@ -390,11 +408,12 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     return p;
   };
   // short rows: SELL, one lane per row; long rows: CSR with enough lanes
-  // per row that each lane sums a handful of entries
-  auto up_sell = [&](const HCsr& M, SellMat& out) -> bool {
+  // per row that each lane sums a handful of entries (lpr: as given, else
+  // by the row length)
+  auto up_sell = [&](const HCsr& M, SellMat& out, int lpr = 0) -> bool {
     const double avg = M.n ? (double)M.rp[M.n] / (double)M.n : 0.0;
     out.nrows = M.n;
-    out.lpr = avg <= 24.0 ? 1 : avg <= 96.0 ? 8 : avg <= 384.0 ? 32 : 64;
+    out.lpr = lpr ? lpr : avg <= 24.0 ? 1 : avg <= 96.0 ? 8 : avg <= 384.0 ? 32 : 64;
     if (out.lpr == 1) {
       const HSell S = to_sell(M);
       out.nslices = S.nslices;
@@ -436,18 +455,14 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
         return hipErrorOutOfMemory;
     }
     lv.omega = omega[l];
-    if (!up_sell(P[l], lv.P) || !up_sell(R[l], lv.R)) return hipErrorOutOfMemory;
+    // (one kernel sums a row of A and of Ps: the same lanes per row)
+    if (!up_sell(Ps[l], lv.Ps, lv.A.lpr) || !up_sell(Rs[l], lv.Rs)) return hipErrorOutOfMemory;
     const size_t vb = sizeof(double) * (size_t)A[l].n;
     lv.b = l > 0 ? (double*)alloc(ctx, vb) : nullptr;
-    lv.x = (double*)alloc(ctx, vb);
-    lv.r = (double*)alloc(ctx, vb);
     lv.t = l > 0 ? (double*)alloc(ctx, vb) : nullptr;
-    if (!lv.x || !lv.r || (l > 0 && (!lv.b || !lv.t))) return hipErrorOutOfMemory;
     lv.b32 = l > 0 ? (float*)alloc(ctx, vb / 2) : nullptr;
-    lv.x32 = (float*)alloc(ctx, vb / 2);
-    lv.r32 = (float*)alloc(ctx, vb / 2);
     lv.t32 = l > 0 ? (float*)alloc(ctx, vb / 2) : nullptr;
-    if (!lv.x32 || !lv.r32 || (l > 0 && (!lv.b32 || !lv.t32))) return hipErrorOutOfMemory;
+    if (l > 0 && (!lv.b || !lv.t || !lv.b32 || !lv.t32)) return hipErrorOutOfMemory;
   }
   d.n_coarse = Ac.n;
   d.coarse_inv = (const double*)up(dense.data(), sizeof(double) * dense.size());

@@ -107,11 +107,6 @@ __device__ inline void write_partials(double* part, int stride,
   }
 }
 
-// emit(r, sum_j val_rj ev(ld(col_rj))) for every row r of M in this
-// workgroup's share, in the arithmetic of T, the sum in entry order.  Up to
-// eight entries per trip (slice widths are uniform across the wave): their
-// words, then their gathers ld, are in flight together.  The packed form
-// looks its values up in a table in LDS.
 template <typename T>
 __device__ inline const T* sell_val(const SellView& M) {
   if constexpr (std::is_same<T, float>::value) return M.val32;
@@ -123,66 +118,79 @@ __device__ inline const T* sell_dict(const SellView& M) {
   else return M.dict;
 }
 
+// The table of a packed matrix in LDS (synchronizes; null when plain).
+template <typename T>
+__device__ inline const T* sell_table(const SellView& M) {
+  if (!M.code) return nullptr;
+  __shared__ T dict[kDictMax];
+  const T* __restrict__ gd = sell_dict<T>(M);
+  for (int k = threadIdx.x; k < kDictMax; k += blockDim.x) dict[k] = gd[k];
+  __syncthreads();
+  return dict;
+}
+
+// sum_j val_rj ev(ld(col_rj)) of this lane's row r of slice s, in the
+// arithmetic of T and in entry order.  Up to eight entries per trip (slice
+// widths are uniform across the wave): their words, then their gathers ld,
+// are in flight together.  The packed form looks its values up in dict.
+template <typename T, typename Lf, typename Vf>
+__device__ inline T sell_sum(const SellView& M, const T* dict, int64_t s,
+                             int lane, Lf&& ld, Vf&& ev) {
+  using X = decltype(ld(0));
+  const int32_t p0 = M.sptr[s], p1 = M.sptr[s + 1];
+  T acc = T(0);
+  if (dict) {
+    const uint32_t* __restrict__ code = M.code;
+    for (int32_t p = p0 + lane; p < p1; p += 8 * kSell) {
+      const int32_t left = p1 - (p - lane);
+      uint32_t c[8];
+      X xv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (u * kSell < left) c[u] = code[p + u * kSell];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (u * kSell < left) xv[u] = ld((int32_t)(c[u] & ((1u << kColBits) - 1)));
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (u * kSell < left) acc += dict[c[u] >> kColBits] * ev(xv[u]);
+    }
+    return acc;
+  }
+  const int32_t* __restrict__ col = M.col;
+  const T* __restrict__ val = sell_val<T>(M);
+  for (int32_t p = p0 + lane; p < p1; p += 4 * kSell) {
+    const int32_t left = p1 - (p - lane);
+    int32_t c[4];
+    T v[4];
+    X xv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u * kSell < left) {
+        c[u] = col[p + u * kSell];
+        v[u] = val[p + u * kSell];
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u * kSell < left) xv[u] = ld(c[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u * kSell < left) acc += v[u] * ev(xv[u]);
+  }
+  return acc;
+}
+
+// emit(r, sum_j val_rj ev(ld(col_rj))) for every row r of M in this
+// workgroup's share (see sell_sum).
 template <typename T, typename Lf, typename Vf, typename Ef>
 __device__ inline void sell_rows(const SellView& M, int64_t nslices,
                                  int64_t nrows, VB vb, Lf&& ld, Vf&& ev,
                                  Ef&& emit) {
-  using X = decltype(ld(0));
+  const T* dict = sell_table<T>(M);
   const Range sl = my_range(nslices, vb);
   const int lane = threadIdx.x & (kSell - 1);
-  const int sub = threadIdx.x / kSell;
-  const int nsub = blockDim.x / kSell;
-  if (M.code) {
-    __shared__ T dict[kDictMax];
-    const T* __restrict__ gd = sell_dict<T>(M);
-    for (int k = threadIdx.x; k < kDictMax; k += blockDim.x) dict[k] = gd[k];
-    __syncthreads();
-    const uint32_t* __restrict__ code = M.code;
-    for (int64_t s = sl.lo + sub; s < sl.hi; s += nsub) {
-      const int32_t p0 = M.sptr[s], p1 = M.sptr[s + 1];
-      T acc = T(0);
-      for (int32_t p = p0 + lane; p < p1; p += 8 * kSell) {
-        const int32_t left = p1 - (p - lane);
-        uint32_t c[8];
-        X xv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (u * kSell < left) c[u] = code[p + u * kSell];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (u * kSell < left) xv[u] = ld((int32_t)(c[u] & ((1u << kColBits) - 1)));
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (u * kSell < left) acc += dict[c[u] >> kColBits] * ev(xv[u]);
-      }
-      const int64_t r = s * kSell + lane;
-      if (r < nrows) emit(r, acc);
-    }
-    return;
-  }
-  const int32_t* __restrict__ col = M.col;
-  const T* __restrict__ val = sell_val<T>(M);
-  for (int64_t s = sl.lo + sub; s < sl.hi; s += nsub) {
-    const int32_t p0 = M.sptr[s], p1 = M.sptr[s + 1];
-    T acc = T(0);
-    for (int32_t p = p0 + lane; p < p1; p += 4 * kSell) {
-      const int32_t left = p1 - (p - lane);
-      int32_t c[4];
-      T v[4];
-      X xv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (u * kSell < left) {
-          c[u] = col[p + u * kSell];
-          v[u] = val[p + u * kSell];
-        }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (u * kSell < left) xv[u] = ld(c[u]);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (u * kSell < left) acc += v[u] * ev(xv[u]);
-    }
+  for (int64_t s = sl.lo + threadIdx.x / kSell; s < sl.hi; s += blockDim.x / kSell) {
+    const T acc = sell_sum<T>(M, dict, s, lane, ld, ev);
     const int64_t r = s * kSell + lane;
     if (r < nrows) emit(r, acc);
   }
@@ -882,20 +890,55 @@ __global__ void k_cg_report_b(CgBatch b, int n, int64_t seq) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// emit(r, sum_j val_rj g(col_rj)) for every row r of M in this workgroup's
-// share, in the arithmetic of T.
-// SELL (lpr = 1): see sell_rows.  CSR (lpr > 1): lpr lanes per row, each
-// summing every lpr-th entry, then a fixed shuffle tree; every group of a
-// workgroup makes the same number of trips, so the shuffles run on whole
-// waves.
-template <typename T, typename Gf, typename Ef>
-__device__ inline void amg_rows(const SellMat& M, VB vb, Gf&& g, Ef&& emit) {
-  if (M.lpr == 1) {
-    sell_rows<T>(M.v, M.nslices, M.nrows, vb, g, [](T v) { return v; }, emit);
-    return;
-  }
+// sum over this lane's share of CSR row r (lpr lanes per row, this one sub):
+// every lpr-th entry, four per trip with their loads in flight together.
+template <typename T, typename Gf>
+__device__ inline T csr_part(const SellMat& M, int64_t r, int sub, Gf&& g) {
+  const int lpr = M.lpr;
   const T* __restrict__ val = sell_val<T>(M.v);
   const int32_t* __restrict__ col = M.v.col;
+  const int32_t p1 = M.v.sptr[r + 1];
+  int32_t p = M.v.sptr[r] + sub;
+  T acc = 0;
+  for (; p + 3 * lpr < p1; p += 4 * lpr) {
+    int32_t c[4];
+    T v[4], xv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      c[u] = col[p + u * lpr];
+      v[u] = val[p + u * lpr];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) xv[u] = g(c[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
+  }
+  for (; p < p1; p += lpr) acc += val[p] * g(col[p]);
+  return acc;
+}
+
+// emit(r, f(r, M's row sum over g, N's row sum over h)) for the rows of this
+// workgroup's share; M and N have the same rows and lanes per row (N may be
+// null: its sum is 0).  SELL (lpr = 1): one lane per row, see sell_sum.  CSR
+// (lpr > 1): lpr lanes per row, f of the lanes' shares summed by a fixed
+// shuffle tree (f is linear in the sums); every group of a workgroup makes
+// the same number of trips, so the shuffles run on whole waves.
+template <typename T, typename Gf, typename Hf, typename Ff, typename Ef>
+__device__ inline void amg_rows(const SellMat& M, const SellMat* N, VB vb,
+                                Gf&& g, Hf&& h, Ff&& f, Ef&& emit) {
+  auto id = [](T v) { return v; };
+  if (M.lpr == 1) {
+    const T* dict = sell_table<T>(M.v);
+    const Range sl = my_range(M.nslices, vb);
+    const int lane = threadIdx.x & (kSell - 1);
+    for (int64_t s = sl.lo + threadIdx.x / kSell; s < sl.hi; s += blockDim.x / kSell) {
+      const int64_t r = s * kSell + lane;
+      const T a = sell_sum<T>(M.v, dict, s, lane, g, id);
+      const T b = N ? sell_sum<T>(N->v, (const T*)nullptr, s, lane, h, id) : T(0);
+      if (r < M.nrows) emit(r, f(r, a, b));
+    }
+    return;
+  }
   const int lpr = M.lpr;
   const Range rows = my_range(M.nrows, vb);
   const int sub = threadIdx.x & (lpr - 1);
@@ -903,26 +946,8 @@ __device__ inline void amg_rows(const SellMat& M, VB vb, Gf&& g, Ef&& emit) {
   for (int64_t r0 = rows.lo; r0 < rows.hi; r0 += ngrp) {
     const int64_t r = r0 + grp;
     T acc = 0;
-    if (r < rows.hi) {
-      // four entries per trip with their loads in flight together, summed
-      // in the lane's entry order
-      const int32_t p1 = M.v.sptr[r + 1];
-      int32_t p = M.v.sptr[r] + sub;
-      for (; p + 3 * lpr < p1; p += 4 * lpr) {
-        int32_t c[4];
-        T v[4], xv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          c[u] = col[p + u * lpr];
-          v[u] = val[p + u * lpr];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) xv[u] = g(c[u]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
-      }
-      for (; p < p1; p += lpr) acc += val[p] * g(col[p]);
-    }
+    if (r < rows.hi)
+      acc = f(r, csr_part<T>(M, r, sub, g), N ? csr_part<T>(*N, r, sub, h) : T(0));
     for (int off = lpr >> 1; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, lpr);
     if (r < rows.hi && sub == 0) emit(r, acc);
   }
@@ -954,47 +979,30 @@ __device__ inline bool amg_stop(const CgArgs& a, VB vb) {
 template <typename T>
 struct LevelVecs {
   const T* dinv;
-  T *b, *x, *r, *t;
+  T *b, *t;
 };
 template <typename T>
 __host__ __device__ inline LevelVecs<T> level_vecs(const AmgLevel& L) {
   if constexpr (std::is_same<T, float>::value)
-    return LevelVecs<T>{L.invdiag32, L.b32, L.x32, L.r32, L.t32};
+    return LevelVecs<T>{L.invdiag32, L.b32, L.t32};
   else
-    return LevelVecs<T>{L.invdiag, L.b, L.x, L.r, L.t};
+    return LevelVecs<T>{L.invdiag, L.b, L.t};
 }
 
 }  // namespace
 
-// Pre-smoothing from zero and the residual: x = w D^-1 b,
-// r = b - A x = b - w sum_j a_ij d_j^-1 b_j.  On the finest level b is the
-// CG residual (FP64; rounded once to T).
+// Down a level: nb = Rs b, the next level's right-hand side.  On the finest
+// level b is the CG residual (FP64; rounded once to T).
 template <typename T>
 __device__ inline void amg_down_body(const CgArgs& a, const AmgLevel& L,
-                                     int level, VB vb) {
+                                     int level, T* nb, VB vb) {
   if (a.ctrl->state != CG_ITER) return;
   if (level == 0 && amg_stop(a, vb)) return;
-  const LevelVecs<T> V = level_vecs<T>(L);
   const double* __restrict__ r64 = a.r;
-  const T* __restrict__ bl = V.b;
-  const T* __restrict__ dinv = V.dinv;
-  const T omega = (T)L.omega;
-  auto B = [&](int64_t c) -> T { return level == 0 ? (T)r64[c] : bl[c]; };
-  amg_rows<T>(L.A, vb, [&](int32_t c) { return B(c) * dinv[c]; },
-              [&](int64_t r, T ax) {
-                const T br = B(r);
-                V.x[r] = omega * (dinv[r] * br);
-                V.r[r] = br - omega * ax;
-              });
-}
-
-// y = M x for the rows of M (restriction and prolongation; add: y += M x).
-template <typename T>
-__device__ inline void amg_apply_body(const CgArgs& a, const SellMat& M,
-                                      const T* x, T* y, int add, VB vb) {
-  if (a.ctrl->state != CG_ITER) return;
-  amg_rows<T>(M, vb, [&](int32_t c) { return x[c]; },
-              [&](int64_t r, T v) { y[r] = add ? y[r] + v : v; });
+  const T* __restrict__ bl = level_vecs<T>(L).b;
+  auto B = [&](int32_t c) -> T { return level == 0 ? (T)r64[c] : bl[c]; };
+  amg_rows<T>(L.Rs, nullptr, vb, B, B, [](int64_t, T s, T) { return s; },
+              [&](int64_t r, T v) { nb[r] = v; });
 }
 
 // Coarsest level: x = A^-1 b with the dense inverse, one wave per row.
@@ -1014,21 +1022,25 @@ __device__ inline void amg_coarse_body(const CgArgs& a, int64_t n, const T* inv,
   }
 }
 
-// Post-smoothing: out = x + w D^-1 (b - A x); on the finest level out is
-// the CG vector u (FP64) and the workgroups write their share of (r,u).
+// Up a level: out = w D^-1 (2 b - w A D^-1 b) + Ps y, y the next level's
+// result; on the finest level out is the CG vector u (FP64) and the
+// workgroups write their share of (r,u).
 template <typename T>
-__device__ inline void amg_post_body(const CgArgs& a, const AmgLevel& L,
-                                     int level, VB vb) {
+__device__ inline void amg_up_body(const CgArgs& a, const AmgLevel& L,
+                                   int level, const T* __restrict__ y, VB vb) {
   if (a.ctrl->state != CG_ITER) return;
   const LevelVecs<T> V = level_vecs<T>(L);
   const double* __restrict__ r64 = a.r;
-  const T* __restrict__ x = V.x;
+  const T* __restrict__ bl = V.b;
+  const T* __restrict__ dinv = V.dinv;
   const T omega = (T)L.omega;
+  auto B = [&](int64_t c) -> T { return level == 0 ? (T)r64[c] : bl[c]; };
   double v[1] = {0.0};
-  amg_rows<T>(L.A, vb, [&](int32_t c) { return x[c]; },
-              [&](int64_t r, T ax) {
-                const T br = level == 0 ? (T)r64[r] : V.b[r];
-                const T o = x[r] + omega * (V.dinv[r] * (br - ax));
+  amg_rows<T>(L.A, &L.Ps, vb, [&](int32_t c) { return B(c) * dinv[c]; },
+              [&](int32_t c) { return y[c]; },
+              [&](int64_t r, T ax, T py) { return py - (omega * omega) * (dinv[r] * ax); },
+              [&](int64_t r, T s) {
+                const T o = (T(2) * omega) * (dinv[r] * B(r)) + s;
                 if (level == 0) {
                   a.u[r] = (double)o;
                   v[0] += r64[r] * (double)o;
@@ -1099,14 +1111,8 @@ __device__ inline void amg_upd_body(const CgArgs& a, VB vb) {
 // One instance: the level, matrix and vectors come as kernel arguments.
 template <typename T>
 __global__ void __launch_bounds__(kCgBlock) k_amg_down(CgArgs a, AmgLevel L,
-                                                       int level) {
-  amg_down_body<T>(a, L, level, VB{(int)blockIdx.x, (int)gridDim.x});
-}
-template <typename T>
-__global__ void __launch_bounds__(kCgBlock) k_amg_apply(CgArgs a, SellMat M,
-                                                        const T* x, T* y,
-                                                        int add) {
-  amg_apply_body<T>(a, M, x, y, add, VB{(int)blockIdx.x, (int)gridDim.x});
+                                                       int level, T* nb) {
+  amg_down_body<T>(a, L, level, nb, VB{(int)blockIdx.x, (int)gridDim.x});
 }
 template <typename T>
 __global__ void __launch_bounds__(kCgBlock) k_amg_coarse(CgArgs a, int64_t n,
@@ -1115,9 +1121,9 @@ __global__ void __launch_bounds__(kCgBlock) k_amg_coarse(CgArgs a, int64_t n,
   amg_coarse_body<T>(a, n, inv, b, x, VB{(int)blockIdx.x, (int)gridDim.x});
 }
 template <typename T>
-__global__ void __launch_bounds__(kCgBlock) k_amg_post(CgArgs a, AmgLevel L,
-                                                       int level) {
-  amg_post_body<T>(a, L, level, VB{(int)blockIdx.x, (int)gridDim.x});
+__global__ void __launch_bounds__(kCgBlock) k_amg_up(CgArgs a, AmgLevel L,
+                                                     int level, const T* y) {
+  amg_up_body<T>(a, L, level, y, VB{(int)blockIdx.x, (int)gridDim.x});
 }
 __global__ void __launch_bounds__(kCgBlock) k_amg_spmv(CgArgs a) {
   amg_spmv_body(a, VB{(int)blockIdx.x, (int)gridDim.x});
@@ -1146,32 +1152,22 @@ __global__ void __launch_bounds__(kCgBlock) k_amg_down_b(AmgBatch b, int level) 
   int i;
   const VB vb = batch_block(b.map, i);
   const CgArgs a = b.args[i];
-  const AmgLevel L = ((const AmgDev*)a.amg_dev)->lv[level];
-  amg_down_body<T>(a, L, level, vb);
-}
-// restriction of level l's residual into the next level's right-hand side
-template <typename T>
-__global__ void __launch_bounds__(kCgBlock) k_amg_restrict_b(AmgBatch b, int level) {
-  int i;
-  const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
   const AmgDev* D = (const AmgDev*)a.amg_dev;
-  const AmgLevel& L = D->lv[level];
+  const AmgLevel L = D->lv[level];
   T* nb = level + 1 < D->n_levels ? level_vecs<T>(D->lv[level + 1]).b
                                   : coarse_vec<T>(*D, 0);
-  amg_apply_body<T>(a, L.R, (const T*)level_vecs<T>(L).r, nb, 0, vb);
+  amg_down_body<T>(a, L, level, nb, vb);
 }
-// the coarse correction of level l added to its pre-smoothed iterate
 template <typename T>
-__global__ void __launch_bounds__(kCgBlock) k_amg_prolong_b(AmgBatch b, int level) {
+__global__ void __launch_bounds__(kCgBlock) k_amg_up_b(AmgBatch b, int level) {
   int i;
   const VB vb = batch_block(b.map, i);
   const CgArgs a = b.args[i];
   const AmgDev* D = (const AmgDev*)a.amg_dev;
-  const AmgLevel& L = D->lv[level];
+  const AmgLevel L = D->lv[level];
   const T* y = level + 1 < D->n_levels ? level_vecs<T>(D->lv[level + 1]).t
                                        : coarse_vec<T>(*D, 1);
-  amg_apply_body<T>(a, L.P, y, level_vecs<T>(L).x, 1, vb);
+  amg_up_body<T>(a, L, level, y, vb);
 }
 template <typename T>
 __global__ void __launch_bounds__(kCgBlock) k_amg_coarse_b(AmgBatch b) {
@@ -1184,14 +1180,6 @@ __global__ void __launch_bounds__(kCgBlock) k_amg_coarse_b(AmgBatch b) {
   else inv = D->coarse_inv;
   amg_coarse_body<T>(a, D->n_coarse, inv, coarse_vec<T>(*D, 0),
                      coarse_vec<T>(*D, 1), vb);
-}
-template <typename T>
-__global__ void __launch_bounds__(kCgBlock) k_amg_post_b(AmgBatch b, int level) {
-  int i;
-  const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
-  const AmgLevel L = ((const AmgDev*)a.amg_dev)->lv[level];
-  amg_post_body<T>(a, L, level, vb);
 }
 __global__ void __launch_bounds__(kCgBlock) k_amg_spmv_b(AmgBatch b) {
   int i;
@@ -1229,8 +1217,8 @@ CoarseVecs<T> coarse_host(const AmgDev& d) {
 // thread (a row takes M.lpr lanes; the rows of a SELL slice share a lane
 // column), at most the solver grid, so that the small coarse passes neither
 // loop over row groups in one workgroup nor launch and drain hundreds of
-// idle workgroups.  The finest level's smoothing kernels keep the solver
-// grid (they also reduce over it).
+// idle workgroups.  The finest level's way up keeps the solver grid (it also
+// reduces over it).
 int amg_grid(const CgArgs& a, const SellMat& M) {
   const int64_t lanes = M.nrows * (int64_t)M.lpr;
   const int64_t want = (lanes + kCgBlock - 1) / kCgBlock;
@@ -1250,21 +1238,16 @@ hipError_t amg_iters_t(const CgArgs& a, const AmgDev& d, int n, hipStream_t s) {
   for (int k = 0; k < n; ++k) {
     for (int l = 0; l < L; ++l) {
       const AmgLevel& lv = d.lv[l];
-      hipLaunchKernelGGL(k_amg_down<T>, dim3(l == 0 ? a.G : amg_grid(a, lv.A)), b, 0,
-                         s, a, lv, l);
       T* nb = l + 1 < L ? vec(d.lv[l + 1]).b : cv.b;
-      hipLaunchKernelGGL(k_amg_apply<T>, dim3(amg_grid(a, lv.R)), b, 0, s, a, lv.R,
-                         (const T*)vec(lv).r, nb, 0);
+      hipLaunchKernelGGL(k_amg_down<T>, dim3(amg_grid(a, lv.Rs)), b, 0, s, a, lv, l, nb);
     }
     hipLaunchKernelGGL(k_amg_coarse<T>, dim3(gc), b, 0, s, a, d.n_coarse, cv.inv,
                        (const T*)cv.b, cv.x);
     for (int l = L - 1; l >= 0; --l) {
       const AmgLevel& lv = d.lv[l];
       const T* y = l + 1 < L ? vec(d.lv[l + 1]).t : cv.x;
-      hipLaunchKernelGGL(k_amg_apply<T>, dim3(amg_grid(a, lv.P)), b, 0, s, a, lv.P, y,
-                         vec(lv).x, 1);
-      hipLaunchKernelGGL(k_amg_post<T>, dim3(l == 0 ? a.G : amg_grid(a, lv.A)), b, 0,
-                         s, a, lv, l);
+      hipLaunchKernelGGL(k_amg_up<T>, dim3(l == 0 ? a.G : amg_grid(a, lv.A)), b, 0, s, a,
+                         lv, l, y);
     }
     hipLaunchKernelGGL(k_amg_spmv, dim3(a.G), b, 0, s, a);
     hipLaunchKernelGGL(k_amg_upd, dim3(a.G), b, 0, s, a);
@@ -1315,7 +1298,7 @@ hipError_t amg_batch_t(const CgArgs* dargs, const std::vector<const CgArgs*>& ha
   int L = 0;
   for (size_t i = 0; i < on.size(); ++i)
     if (on[i]) L = std::max(L, hier((int)i).n_levels);
-  BatchMap mA[kAmgMaxLevels], mR[kAmgMaxLevels], mP[kAmgMaxLevels];
+  BatchMap mA[kAmgMaxLevels], mR[kAmgMaxLevels];
   for (int l = 0; l < L; ++l) {
     mA[l] = sched(on, [&](int i) {
       const AmgDev& d = hier(i);
@@ -1323,11 +1306,7 @@ hipError_t amg_batch_t(const CgArgs* dargs, const std::vector<const CgArgs*>& ha
     });
     mR[l] = sched(on, [&](int i) {
       const AmgDev& d = hier(i);
-      return l >= d.n_levels ? 0 : amg_grid(*hargs[i], d.lv[l].R);
-    });
-    mP[l] = sched(on, [&](int i) {
-      const AmgDev& d = hier(i);
-      return l >= d.n_levels ? 0 : amg_grid(*hargs[i], d.lv[l].P);
+      return l >= d.n_levels ? 0 : amg_grid(*hargs[i], d.lv[l].Rs);
     });
   }
   const BatchMap mC = sched(on, [&](int i) { return coarse_grid(*hargs[i], hier(i).n_coarse); });
@@ -1335,15 +1314,11 @@ hipError_t amg_batch_t(const CgArgs* dargs, const std::vector<const CgArgs*>& ha
   auto grid = [](const BatchMap& m) { return m.off[m.n_seg]; };
   auto B = [&](const BatchMap& m) { return AmgBatch{dargs, m}; };
   for (int k = 0; k < n; ++k) {
-    for (int l = 0; l < L; ++l) {
-      if (grid(mA[l])) hipLaunchKernelGGL(k_amg_down_b<T>, dim3(grid(mA[l])), blk, 0, s, B(mA[l]), l);
-      if (grid(mR[l])) hipLaunchKernelGGL(k_amg_restrict_b<T>, dim3(grid(mR[l])), blk, 0, s, B(mR[l]), l);
-    }
+    for (int l = 0; l < L; ++l)
+      if (grid(mR[l])) hipLaunchKernelGGL(k_amg_down_b<T>, dim3(grid(mR[l])), blk, 0, s, B(mR[l]), l);
     if (grid(mC)) hipLaunchKernelGGL(k_amg_coarse_b<T>, dim3(grid(mC)), blk, 0, s, B(mC));
-    for (int l = L - 1; l >= 0; --l) {
-      if (grid(mP[l])) hipLaunchKernelGGL(k_amg_prolong_b<T>, dim3(grid(mP[l])), blk, 0, s, B(mP[l]), l);
-      if (grid(mA[l])) hipLaunchKernelGGL(k_amg_post_b<T>, dim3(grid(mA[l])), blk, 0, s, B(mA[l]), l);
-    }
+    for (int l = L - 1; l >= 0; --l)
+      if (grid(mA[l])) hipLaunchKernelGGL(k_amg_up_b<T>, dim3(grid(mA[l])), blk, 0, s, B(mA[l]), l);
     if (grid(mG)) {
       hipLaunchKernelGGL(k_amg_spmv_b, dim3(grid(mG)), blk, 0, s, B(mG));
       hipLaunchKernelGGL(k_amg_upd_b, dim3(grid(mG)), blk, 0, s, B(mG));
