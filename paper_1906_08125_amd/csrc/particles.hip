@@ -259,6 +259,17 @@ __device__ inline void face_cell_field(const DevMesh& m, int t, const double* ph
   cell_field<false>(g, nullptr, phi, ex, ey, ez);
 }
 
+// A place in a queue for every lane that calls (one atomic per wave).
+__device__ inline int queue_slot(int32_t* count) {
+  const unsigned long long here = __ballot(1);
+  const int lane = threadIdx.x & 63;
+  const int lead = __ffsll((long long)here) - 1;
+  int base = 0;
+  if (lane == lead) base = atomicAdd(count, __popcll(here));
+  base = __shfl(base, lead, 64);
+  return base + __popcll(here & ((1ull << lane) - 1));
+}
+
 __device__ inline void deposit_one(const TetGeom& g, double x, double y,
                                    double z, double w, int64_t* charge) {
   double lam[4];
@@ -1218,20 +1229,29 @@ __global__ void __launch_bounds__(kBlock) k_locate(LocateArgs a) {
       a.where[i] = PIC_WHERE_ANODE;
       continue;
     }
-    const int h = a.tet[i];
+    int h = a.tet[i];
     int t = -1, steps = 0;
-    if (h >= 0 && h < m.n_tets) {
+    // without a hint the walk starts at the seed of the point's sub-cell (it
+    // only answers when it is certain, so the answer does not depend on
+    // where it starts), and only the points it cannot certify -- on a face,
+    // in the metal, outside -- are left to the exact scan, a wave each.
+    // Locating and depositing 300k points without hints: 475 us with every
+    // one scanned (351 us, and 50 of atomics on the queue's counter), 126 so
+    const bool hint = h >= 0 && h < m.n_tets;
+    if (!hint) {
+      h = fine_seed(m, x, y, z);
+      if (h < 0) h = bucket_guess(m, x, y, z);
+    }
+    if (h >= 0) {
       Geo<PK> G;
-      G.load(m, h);
       double lam[4];
-      t = walk<PK>(m, M, x, y, z, h, 0, 0, steps, false, G, lam);
+      t = walk<PK>(m, M, x, y, z, h, 0, 0, steps, !hint, G, lam, false);
     }
     if (t >= 0) {
       a.tet[i] = t;
       a.where[i] = PIC_WHERE_INSIDE;
     } else {
-      const int slot = atomicAdd(a.n_queue, 1);
-      a.queue[slot] = (int32_t)i;
+      a.queue[queue_slot(a.n_queue)] = (int32_t)i;
     }
   }
 }
