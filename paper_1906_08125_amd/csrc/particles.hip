@@ -598,7 +598,21 @@ __device__ inline void face_field(const DevMesh& m, const void* E, int f32,
 // the metal, Eq. nsp and the rounding of Eq. rnd_nsp; an exclusive scan of
 // the counts gives every new particle its slot.
 // ---------------------------------------------------------------------------
-template <int NT>
+// PUB: the offsets and inj_fit are read by other workgroups of the same
+// launch (see emit_publish), so they go past the caches.
+template <bool PUB>
+__device__ inline void emit_put(int32_t* p, int32_t v) {
+  if (PUB)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = v;
+}
+
+__device__ inline int32_t emit_get(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int NT, bool PUB>
 __device__ void emit_block(const EmitArgs& a) {
   const DevMesh& m = a.m;
   __shared__ long long s_scan[NT / 64];
@@ -681,7 +695,7 @@ __device__ void emit_block(const EmitArgs& a) {
     }
     if (f < m.n_emit && a.counts) {
       a.counts[f] = (int32_t)cnt;
-      a.offsets[f] = (int32_t)(offset + before + inc - cnt);
+      emit_put<PUB>(a.offsets + f, (int32_t)(offset + before + inc - cnt));
     }
     offset += chunk;
     __syncthreads();
@@ -696,14 +710,14 @@ __device__ void emit_block(const EmitArgs& a) {
       st->n_clamp = n_clamp;
     }
     if (a.counts) {
-      a.offsets[m.n_emit] = (int32_t)offset;
+      emit_put<PUB>(a.offsets + m.n_emit, (int32_t)offset);
       const long long base = *a.n_slots;
       long long fit = a.capacity - base;
       if (fit > offset) fit = offset;
       if (fit < 0) fit = 0;
       a.scratch->inj_base = (int32_t)base;
       a.scratch->inj_total = (int32_t)offset;
-      a.scratch->inj_fit = (int32_t)fit;
+      emit_put<PUB>(&a.scratch->inj_fit, (int32_t)fit);
       *a.n_slots = (int32_t)(base + fit);
       if (a.stats) {
         a.stats->n_trunc = offset - fit;
@@ -717,7 +731,7 @@ __device__ void emit_block(const EmitArgs& a) {
 constexpr int kBeginBlock = 512;  // 1024 would cap registers below the emission path's needs
 
 __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a) {
-  emit_block<kBlock>(a);
+  emit_block<kBlock, false>(a);
 }
 
 // Start of a step: workgroup 0 clears the step's stats and counters and
@@ -738,7 +752,7 @@ __device__ inline void begin_body(const EmitArgs& a, VB vb) {
       if (threadIdx.x == 0) a.scratch->inj_base = *a.n_slots;
       return;
     }
-    emit_block<kBeginBlock>(a);
+    emit_block<kBeginBlock, false>(a);
     return;
   }
   const int64_t G = vb.n - 1;
@@ -952,24 +966,36 @@ __device__ inline void push_role32(const StepArgs& a, const MapTable* M, int g,
   }
 }
 
+constexpr int kEmitLds = 1024;  // emitting faces whose offsets fit in LDS
+
 template <bool PK>
 __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
                                    int G, Acc& acc, ChargeTable& T) {
   const DevMesh& m = a.m;
-  const int64_t n = a.scratch->inj_fit;
+  const int64_t n = emit_get(&a.scratch->inj_fit);
   const int64_t base = a.scratch->inj_base;
   const double dt = a.dt;
+  // the offsets for the search of a slot's face: in LDS where they fit (ten
+  // dependent loads from LDS instead of memory)
   const int32_t* off = a.offsets;
+  __shared__ int32_t s_off[kEmitLds];
+  const bool in_lds = m.n_emit <= kEmitLds;
+  if (g * (int64_t)blockDim.x >= n) return;  // (the whole workgroup)
+  if (in_lds) {
+    for (int f = threadIdx.x; f < (int)m.n_emit; f += blockDim.x) s_off[f] = emit_get(off + f);
+    __syncthreads();
+  }
+  auto at = [&](int f) { return in_lds ? s_off[f] : emit_get(off + f); };
   for (int64_t s = g * (int64_t)blockDim.x + threadIdx.x; s < n;
        s += (int64_t)G * blockDim.x) {
     // face: last f with off[f] <= s
     int lo = 0, hi = (int)m.n_emit - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= s) lo = mid; else hi = mid - 1;
+      if (at(mid) <= s) lo = mid; else hi = mid - 1;
     }
     const int f = lo;
-    const int64_t o = s - off[f];
+    const int64_t o = s - at(f);
     uint64_t r4[4];
     philox4x64_10(a.seed, a.instance, (uint64_t)a.step, (uint64_t)f,
                   (uint64_t)o, 1, r4);
@@ -1047,12 +1073,19 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
 // workgroups (dispatched last) wait for the flag.  The wait is bounded: a
 // flag not seen in time (never expected) skips the injection and marks the
 // step with a device error.
+// What is published (the offsets and inj_fit) is stored and loaded with
+// device-scope atomics, which go past the per-XCD caches, and each wave's
+// stores are complete before the barrier ahead of the flag: neither side
+// needs a fence, which would write back or invalidate an L2 that the pushing
+// workgroups are using (the waiting side did so at every poll).  With the
+// offsets searched in LDS, the particle kernel of a small step (10k
+// superparticles, 276 emitting faces) went from 40 to 30 us.
 __device__ inline void emit_publish(const EmitArgs& e) {
-  emit_block<kBlock>(e);
-  __threadfence();  // every thread's counts and offsets reach L2
+  emit_block<kBlock, true>(e);
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have arrived
   __syncthreads();
   if (threadIdx.x == 0)
-    __hip_atomic_store(&e.scratch->emitted, 1, __ATOMIC_RELEASE,
+    __hip_atomic_store(&e.scratch->emitted, 1, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1061,8 +1094,7 @@ __device__ inline bool emit_wait(const StepArgs& a) {
   if (threadIdx.x == 0) {
     int ok = 0;
     for (int it = 0; it < (1 << 22); ++it) {
-      if (__hip_atomic_load(&a.scratch->emitted, __ATOMIC_ACQUIRE,
-                            __HIP_MEMORY_SCOPE_AGENT) != 0) {
+      if (emit_get(&a.scratch->emitted) != 0) {
         ok = 1;
         break;
       }
@@ -1072,7 +1104,6 @@ __device__ inline bool emit_wait(const StepArgs& a) {
     seen = ok;
   }
   __syncthreads();
-  __atomic_thread_fence(__ATOMIC_ACQUIRE);
   return seen != 0;
 }
 
