@@ -605,9 +605,11 @@ class Window:
                        j_scale=j_scale, instance=instance, tol=tol,
                        max_iter=max_iter)
         self.base = _Checkpoint(state)        # population with base weights
+        # (the recompute solves as the forward did: its preconditioner too)
         self.scratch = State(mesh, state.capacity, state.precision,
                              solve_precision=state.solve_precision,
-                             inner_tol=state.inner_tol)
+                             inner_tol=state.inner_tol,
+                             precond=state.precond)
         self.cks = []
         self.charge = torch.zeros(mesh.n_nodes, dtype=torch.int64,
                                   device=state.phi.device)
@@ -634,7 +636,7 @@ class Window:
                                 st.E, tol=self.kw["tol"],
                                 max_iter=self.kw["max_iter"],
                                 precision=st.precision,
-                                inner_tol=st.inner_tol)
+                                inner_tol=st.inner_tol, precond=st.precond)
 
     def forward(self, E0: float, s, counts=None, wQ=1.0, wE=1.0):
         """Runs the window from the base population; returns (J_Q, J_E) as
