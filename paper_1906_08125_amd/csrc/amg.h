@@ -10,6 +10,10 @@ namespace fp {
 
 constexpr int kAmgMaxLevels = 8;
 constexpr int kAmgCoarseMax = 512;  // the coarsest operator is inverted densely
+// A last smoothed level of at most this many rows is applied with all below
+// it as one dense matrix (see AmgDev): three dependent launches near the
+// floor (18 us at 1,089 rows) against one product that reads 5 to 16 MB.
+constexpr int kAmgDenseMax = 2048;
 
 // A sparse matrix of the hierarchy.  lpr = 1: the sliced ELLPACK layout of
 // the solver (SellView, one lane per row), for short rows; packed on the
@@ -51,8 +55,11 @@ struct AmgLevel {
 struct AmgDev {
   int n_levels;   // levels with a smoother; the dense coarsest level follows
   AmgLevel lv[kAmgMaxLevels];
+  // The coarsest level: the inverse of its operator, or, where the last
+  // smoothed level is small, that level's whole cycle
+  // 2 w D^-1 - w^2 D^-1 A D^-1 + Ps inv Rs (the same preconditioner).
   int64_t n_coarse;
-  const double* coarse_inv;  // [n_coarse][n_coarse] inverse, row-major
+  const double* coarse_inv;  // [n_coarse][n_coarse], row-major
   double* coarse_b;
   double* coarse_x;
   const float* coarse_inv32;

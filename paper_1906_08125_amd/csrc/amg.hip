@@ -309,6 +309,42 @@ bool spd_inverse(std::vector<double>& a, int64_t n) {
   return true;
 }
 
+// Host work allowed for a dense cycle (multiply-adds; a tenth of a second).
+constexpr int64_t kDenseWork = 100000000;
+
+// The V(1,1)-cycle of a level over the dense inverse inv of the next one as
+// a dense matrix: 2 w D^-1 - w^2 D^-1 A D^-1 + Ps inv Rs.
+std::vector<double> dense_cycle(const HCsr& A, const std::vector<double>& d,
+                                double omega, const HCsr& Ps, const HCsr& Rs,
+                                const std::vector<double>& inv) {
+  const int64_t n = A.n, nc = Ps.m;
+  std::vector<double> M(nc * n, 0.0);  // inv Rs
+  for (int64_t k = 0; k < nc; ++k)
+    for (int64_t q = 0; q < nc; ++q) {
+      const double v = inv[k * nc + q];
+      for (int64_t p = Rs.rp[q]; p < Rs.rp[q + 1]; ++p) M[k * n + Rs.ci[p]] += v * Rs.v[p];
+    }
+  std::vector<double> C(n * n, 0.0);
+  for (int64_t i = 0; i < n; ++i) {
+    double* c = &C[i * n];
+    for (int64_t p = Ps.rp[i]; p < Ps.rp[i + 1]; ++p) {
+      const double v = Ps.v[p];
+      const double* m = &M[(int64_t)Ps.ci[p] * n];
+      for (int64_t j = 0; j < n; ++j) c[j] += v * m[j];
+    }
+    for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p)
+      c[A.ci[p]] -= omega * omega * A.v[p] / (d[i] * d[A.ci[p]]);
+    c[i] += 2.0 * omega / d[i];
+  }
+  // exact symmetry of the applied operator
+  for (int64_t i = 0; i < n; ++i)
+    for (int64_t j = i + 1; j < n; ++j) {
+      const double v = 0.5 * (C[i * n + j] + C[j * n + i]);
+      C[i * n + j] = C[j * n + i] = v;
+    }
+  return C;
+}
+
 }  // namespace
 
 hipError_t amg_build(const DevMesh& m, hipStream_t s,
@@ -386,7 +422,7 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
         msg = "amg: level matrix too large for 32-bit offsets";
         return hipErrorInvalidValue;
       }
-  const int L = (int)Ps.size();
+  int L = (int)Ps.size();
   const HCsr& Ac = A.back();
   if (L == 0 || Ac.n > 4 * kAmgCoarseMax) {
     msg = "amg: the operator does not coarsen";
@@ -399,6 +435,14 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     msg = "amg: coarsest operator not positive definite";
     return hipErrorInvalidValue;
   }
+  int64_t n_coarse = Ac.n;
+  for (int l = 0; l <= L; ++l) d.rows[l] = A[l].n;
+  if (L >= 2 && A[L - 1].n <= kAmgDenseMax &&
+      Ps[L - 1].rp[A[L - 1].n] * A[L - 1].n <= kDenseWork) {
+    --L;
+    dense = dense_cycle(A[L], diag[L], omega[L], Ps[L], Rs[L], dense);
+    n_coarse = A[L].n;
+  }
   // upload
   auto up = [&](const void* src, size_t bytes) -> void* {
     void* p = alloc(ctx, bytes);
@@ -408,12 +452,12 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     return p;
   };
   // short rows: SELL, one lane per row; long rows: CSR with enough lanes
-  // per row that each lane sums a handful of entries (lpr: as given, else
-  // by the row length)
+  // per row that each lane sums 3 to 6 entries, one trip with all its loads
+  // in flight (lpr: as given, else by the row length)
   auto up_sell = [&](const HCsr& M, SellMat& out, int lpr = 0) -> bool {
     const double avg = M.n ? (double)M.rp[M.n] / (double)M.n : 0.0;
     out.nrows = M.n;
-    out.lpr = lpr ? lpr : avg <= 24.0 ? 1 : avg <= 96.0 ? 8 : avg <= 384.0 ? 32 : 64;
+    out.lpr = lpr ? lpr : avg <= 24.0 ? 1 : avg <= 48.0 ? 8 : avg <= 96.0 ? 16 : avg <= 192.0 ? 32 : 64;
     if (out.lpr == 1) {
       const HSell S = to_sell(M);
       out.nslices = S.nslices;
@@ -437,7 +481,6 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
            hipStreamSynchronize(s) == hipSuccess;
   };
   d.n_levels = L;
-  for (int l = 0; l <= L; ++l) d.rows[l] = A[l].n;
   for (int l = 0; l < L; ++l) {
     AmgLevel& lv = d.lv[l];
     if (l == 0) {
@@ -464,14 +507,14 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     lv.t32 = l > 0 ? (float*)alloc(ctx, vb / 2) : nullptr;
     if (l > 0 && (!lv.b || !lv.t || !lv.b32 || !lv.t32)) return hipErrorOutOfMemory;
   }
-  d.n_coarse = Ac.n;
+  d.n_coarse = n_coarse;
   d.coarse_inv = (const double*)up(dense.data(), sizeof(double) * dense.size());
   const std::vector<float> dense32(dense.begin(), dense.end());
   d.coarse_inv32 = (const float*)up(dense32.data(), sizeof(float) * dense32.size());
-  d.coarse_b = (double*)alloc(ctx, sizeof(double) * Ac.n);
-  d.coarse_x = (double*)alloc(ctx, sizeof(double) * Ac.n);
-  d.coarse_b32 = (float*)alloc(ctx, sizeof(float) * Ac.n);
-  d.coarse_x32 = (float*)alloc(ctx, sizeof(float) * Ac.n);
+  d.coarse_b = (double*)alloc(ctx, sizeof(double) * n_coarse);
+  d.coarse_x = (double*)alloc(ctx, sizeof(double) * n_coarse);
+  d.coarse_b32 = (float*)alloc(ctx, sizeof(float) * n_coarse);
+  d.coarse_x32 = (float*)alloc(ctx, sizeof(float) * n_coarse);
   if (!d.coarse_inv || !d.coarse_b || !d.coarse_x || !d.coarse_inv32 ||
       !d.coarse_b32 || !d.coarse_x32)
     return hipErrorOutOfMemory;

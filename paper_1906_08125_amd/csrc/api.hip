@@ -167,6 +167,7 @@ fp::CgArgs cg_args(const pic_mesh* h, const int64_t* charge, double w_sp,
   a.u = h->cg_rec[0];
   a.w = h->cg_rec[0] + h->dm.n_free;
   a.s = h->cg_rec[0] + 2 * h->dm.n_free;
+  a.z = h->cg_rec[0] + 3 * h->dm.n_free;
   a.bprev = h->cg_bprev;
   a.mixed = prm->precision == PIC_MIXED;
   a.e32 = e32;
@@ -349,14 +350,14 @@ hipError_t solve_finish(pic_mesh* h, const fp::CgArgs& a, int spec,
       batch = 16;
     } else {
       // Every round ends with the conditional re-check, so a recursion that
-      // stops inside it comes back tested.  An AMG iteration is some fifteen
-      // dependent launches and a solve needs few: after a speculated round
-      // the next ones run 1, 2, 4, ... iterations (launches past the stop
-      // cost as much as working ones); Jacobi rounds start at 8 and stop
+      // stops inside it comes back tested.  A solve needs few AMG iterations
+      // and one past the stop costs as much as a working one (40 to 60 us,
+      // against 30 for a round's end and the host's wait): the rounds run 4
+      // iterations, after a speculated one 1, 2, 4; Jacobi rounds start at 8 and stop
       // doubling at 64: a round costs the host's wait and a re-check, some
       // 30 us, and an iteration past the stop 4.
       if (a.amg)
-        batch = rounds == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * batch, 32);
+        batch = rounds == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * batch, 4);
       else
         batch = batch < 8 ? 8 : std::min(2 * batch, 64);
       ++rounds;
@@ -1720,9 +1721,9 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
         (e = fp::cg_batch_report(cb, n, seq, s)) != hipSuccess ||
         (e = batch_wait(b, seq, s)) != hipSuccess)
       return hip_fail(e, "pic_batch_step solve");
-    // later rounds: Jacobi 8, 16, 32, ... iterations; AMG (some fifteen
-    // dependent launches per iteration, launches past the stop costing as
-    // much as working ones) 1, 2, 4, ... after a speculated round, else from 4
+    // later rounds: Jacobi 8, 16, 32, ... iterations; AMG (an iteration past
+    // the stop costs as much as a working one) 1, 2, 4 after a speculated
+    // round, else 4
     int batch = spec, amg_batch = 0;
     for (int guard = 0; guard < (1 << 20); ++guard) {
       uint64_t mask = 0;
@@ -1737,7 +1738,7 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       seq = batch_next_seq(b);
       batch = batch < 8 ? 8 : std::min(2 * batch, 256);
       if (mask) batch = std::min(batch, 16);
-      amg_batch = guard == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * amg_batch, 16);
+      amg_batch = guard == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * amg_batch, 4);
       if ((e = iterate(active, mask, batch, amg_batch, nullptr)) != hipSuccess ||
           (e = fp::cg_batch_report(cb, n, seq, s)) != hipSuccess ||
           (e = batch_wait(b, seq, s)) != hipSuccess)

@@ -53,6 +53,7 @@ struct CgArgs {
   void* E;                // [4 n_nodes] double (float if mixed) or null
   double *x, *r, *p;      // [n_free]
   double *u, *w, *s;      // [n_free], AMG only (within rec0)
+  void* z;                // [n_free] D^-1 r in the V-cycle's arithmetic, AMG
   // Jacobi: a record (r, w, s, d) per row and its successor (d the inverse
   // diagonal), four doubles, or four floats in mixed precision
   void *rec0, *rec1;

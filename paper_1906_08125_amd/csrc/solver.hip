@@ -461,18 +461,56 @@ __device__ inline void k_cg_resinc_body(const CgArgs& a, VB vb) {
   write_partials<2>(slot(a, 0), a.G, v, vb);
 }
 
+// D^-1 r of a row for the V-cycle, in its arithmetic: gathered on the way
+// up the finest level in place of r and the diagonal.
+__device__ inline void amg_put_z(const CgArgs& a, int64_t i, double ri) {
+  if (a.amg32)
+    ((float*)a.z)[i] = (float)ri * a.m.invdiag32[i];
+  else
+    ((double*)a.z)[i] = ri * a.m.invdiag[i];
+}
+
 // x of a lean first pass whose test asked for iterations.
 __device__ inline void k_cg_prep_body(const CgArgs& a, VB vb) {
   const DevMesh& m = a.m;
   const Range rows = my_range(m.n_free, vb);
-  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x)
+  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
     a.x[i] = a.phi[m.free2node[i]];
+    if (a.amg) amg_put_z(a, i, a.r[i]);
+  }
+}
+
+// The stopping test on the recursive residual after it iterations of the
+// current (re)start, whose (r,r) is rr (every workgroup decides alike).
+__device__ inline bool recursion_stops(const CgArgs& a, const CgCtrl* c, int it,
+                                       double rr) {
+  const double bn = sqrt(c->bb);
+  double thr = a.tol * (a.bref ? fmax(bn, *a.bref) : bn);
+  if (a.mixed) thr = fmax(thr, a.inner_tol * c->rstart);
+  return sqrt(rr) <= thr || c->iters + it >= a.max_iter;
 }
 
 // phi = x on the free nodes (before a re-check pass; dev_gate: only if the
-// recursion has stopped).
+// recursion has stopped).  The conditional form ends a round of iterations,
+// so it also makes the stopping test that the next iteration would open
+// with: a solve that needs just the iterations of its round ends in it.
 __device__ inline void k_cg_scatter_body(const CgArgs& a, VB vb, int dev_gate = 0) {
-  if (dev_gate && a.ctrl->state != CG_RECHECK) return;
+  if (dev_gate) {
+    CgCtrl* c = a.ctrl;
+    const int32_t state = c->state;
+    const int it = c->it_a;
+    if (state == CG_DONE || state == CG_NOCONV) return;
+    // (workgroup 0 may set RECHECK while others start: the same decision)
+    double t[1] = {0.0};
+    if (it > 0) totals<1>(slot(a, 4 + 2 * ((it - 1) & 1)), a.G, 1, t);
+    if (state == CG_ITER) {
+      if (it == 0 || !recursion_stops(a, c, it, t[0])) return;
+      if (vb.id == 0 && threadIdx.x == 0) {
+        c->state = CG_RECHECK;
+        c->iters_final = c->iters + it;
+      }
+    }
+  }
   const DevMesh& m = a.m;
   const Range rows = my_range(m.n_free, vb);
   for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x)
@@ -606,7 +644,12 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
   }
   if (done || noconv) return;
   if (dev_gate == 3) return;  // the test of a lean first pass only
-  if (a.amg) return;  // its iterations start with the V-cycle
+  if (a.amg) {  // its iterations start with the V-cycle
+    const Range rows = my_range(a.m.n_free, vb);
+    for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x)
+      amg_put_z(a, i, a.r[i]);
+    return;
+  }
   start_product(a, vb);
 }
 
@@ -694,11 +737,7 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
     }
     // it iterations done since the (re)start; c->iters is stable while
     // iterating, so every workgroup takes the same decision
-    const double rn = sqrt(t[0]);
-    const double bn = sqrt(c->bb);
-    double thr = a.tol * (a.bref ? fmax(bn, *a.bref) : bn);
-    if (a.mixed) thr = fmax(thr, a.inner_tol * c->rstart);
-    if (rn <= thr || c->iters + it >= a.max_iter) {
+    if (recursion_stops(a, c, it, t[0])) {
       if (vb.id == 0 && threadIdx.x == 0) {
         c->state = CG_RECHECK;
         c->iters_final = c->iters + it;
@@ -891,29 +930,29 @@ __global__ void k_cg_report_b(CgBatch b, int n, int64_t seq) {
 namespace {
 
 // sum over this lane's share of CSR row r (lpr lanes per row, this one sub):
-// every lpr-th entry, four per trip with their loads in flight together.
+// every lpr-th entry, up to eight per trip with their loads in flight
+// together (a remainder summed one by one was a chain of loads per entry).
 template <typename T, typename Gf>
 __device__ inline T csr_part(const SellMat& M, int64_t r, int sub, Gf&& g) {
   const int lpr = M.lpr;
   const T* __restrict__ val = sell_val<T>(M.v);
   const int32_t* __restrict__ col = M.v.col;
   const int32_t p1 = M.v.sptr[r + 1];
-  int32_t p = M.v.sptr[r] + sub;
   T acc = 0;
-  for (; p + 3 * lpr < p1; p += 4 * lpr) {
-    int32_t c[4];
-    T v[4], xv[4];
+  for (int32_t p = M.v.sptr[r] + sub; p < p1; p += 8 * lpr) {
+    int32_t c[8];
+    T v[8], xv[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      c[u] = col[p + u * lpr];
-      v[u] = val[p + u * lpr];
+    for (int u = 0; u < 8; ++u) {
+      const int32_t q = p + u * lpr;
+      c[u] = col[q < p1 ? q : p];
+      v[u] = q < p1 ? val[q] : T(0);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) xv[u] = g(c[u]);
+    for (int u = 0; u < 8; ++u) xv[u] = g(c[u]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
+    for (int u = 0; u < 8; ++u) acc += v[u] * xv[u];
   }
-  for (; p < p1; p += lpr) acc += val[p] * g(col[p]);
   return acc;
 }
 
@@ -923,56 +962,55 @@ __device__ inline T csr_part(const SellMat& M, int64_t r, int sub, Gf&& g) {
 // (lpr > 1): lpr lanes per row, f of the lanes' shares summed by a fixed
 // shuffle tree (f is linear in the sums); every group of a workgroup makes
 // the same number of trips, so the shuffles run on whole waves.
-template <typename T, typename Gf, typename Hf, typename Ff, typename Ef>
-__device__ inline void amg_rows(const SellMat& M, const SellMat* N, VB vb,
-                                Gf&& g, Hf&& h, Ff&& f, Ef&& emit) {
+// gate() decides whether the launch does anything (false: nothing is
+// emitted).  It is asked once the first rows' loads are under way, not
+// ahead of them: the control word is written by another XCD just before,
+// and waiting for it first cost every launch of a V-cycle close to 1 us.
+// GB: the gate holds a barrier.
+template <typename T, bool GB, typename Gf, typename Hf, typename Ff, typename Ef,
+          typename Qf>
+__device__ inline bool amg_rows(const SellMat& M, const SellMat* N, VB vb,
+                                Gf&& g, Hf&& h, Ff&& f, Ef&& emit, Qf&& gate) {
   auto id = [](T v) { return v; };
   if (M.lpr == 1) {
     const T* dict = sell_table<T>(M.v);
     const Range sl = my_range(M.nslices, vb);
     const int lane = threadIdx.x & (kSell - 1);
-    for (int64_t s = sl.lo + threadIdx.x / kSell; s < sl.hi; s += blockDim.x / kSell) {
+    int64_t s = sl.lo + threadIdx.x / kSell;
+    if (GB || s >= sl.hi) {
+      if (!gate()) return false;
+    }
+    bool ask = !GB;
+    for (; s < sl.hi; s += blockDim.x / kSell) {
       const int64_t r = s * kSell + lane;
       const T a = sell_sum<T>(M.v, dict, s, lane, g, id);
       const T b = N ? sell_sum<T>(N->v, (const T*)nullptr, s, lane, h, id) : T(0);
+      if (ask) {
+        if (!gate()) return false;
+        ask = false;
+      }
       if (r < M.nrows) emit(r, f(r, a, b));
     }
-    return;
+    return true;
   }
   const int lpr = M.lpr;
   const Range rows = my_range(M.nrows, vb);
   const int sub = threadIdx.x & (lpr - 1);
   const int grp = threadIdx.x / lpr, ngrp = blockDim.x / lpr;
+  auto part = [&](int64_t r) {
+    return r < rows.hi
+               ? f(r, csr_part<T>(M, r, sub, g), N ? csr_part<T>(*N, r, sub, h) : T(0))
+               : T(0);
+  };
+  T acc = part(rows.lo + grp);
+  if (!gate()) return false;
   for (int64_t r0 = rows.lo; r0 < rows.hi; r0 += ngrp) {
     const int64_t r = r0 + grp;
-    T acc = 0;
-    if (r < rows.hi)
-      acc = f(r, csr_part<T>(M, r, sub, g), N ? csr_part<T>(*N, r, sub, h) : T(0));
+    if (r0 > rows.lo) acc = part(r);
     for (int off = lpr >> 1; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, lpr);
     if (r < rows.hi && sub == 0) emit(r, acc);
   }
-}
-
-// The stopping test on the recursive residual of the previous update
-// (iterations after the first of a (re)start); true when the solve leaves
-// the iteration (every workgroup decides alike).
-__device__ inline bool amg_stop(const CgArgs& a, VB vb) {
-  CgCtrl* c = a.ctrl;
-  const int it = c->it_a;
-  if (it == 0) return false;
-  double t[1];
-  totals<1>(slot(a, 4 + 2 * ((it - 1) & 1)), a.G, 1, t);
-  const double rn = sqrt(t[0]);
-  const double bn = sqrt(c->bb);
-  const double thr = a.tol * (a.bref ? fmax(bn, *a.bref) : bn);
-  if (rn <= thr || c->iters + it >= a.max_iter) {
-    if (vb.id == 0 && threadIdx.x == 0) {
-      c->state = CG_RECHECK;
-      c->iters_final = c->iters + it;
-    }
-    return true;
-  }
-  return false;
+  return true;
 }
 
 // Vectors and diagonal of a level in the arithmetic of T.
@@ -992,33 +1030,67 @@ __host__ __device__ inline LevelVecs<T> level_vecs(const AmgLevel& L) {
 }  // namespace
 
 // Down a level: nb = Rs b, the next level's right-hand side.  On the finest
-// level b is the CG residual (FP64; rounded once to T).
+// level b is the CG residual (FP64; rounded once to T), and the launch opens
+// with the stopping test.
 template <typename T>
 __device__ inline void amg_down_body(const CgArgs& a, const AmgLevel& L,
                                      int level, T* nb, VB vb) {
-  if (a.ctrl->state != CG_ITER) return;
-  if (level == 0 && amg_stop(a, vb)) return;
+  CgCtrl* c = a.ctrl;
+  const int32_t state = c->state;
   const double* __restrict__ r64 = a.r;
   const T* __restrict__ bl = level_vecs<T>(L).b;
-  auto B = [&](int32_t c) -> T { return level == 0 ? (T)r64[c] : bl[c]; };
-  amg_rows<T>(L.Rs, nullptr, vb, B, B, [](int64_t, T s, T) { return s; },
-              [&](int64_t r, T v) { nb[r] = v; });
+  auto F = [](int64_t, T s, T) { return s; };
+  auto put = [&](int64_t r, T v) { nb[r] = v; };
+  if (level > 0) {
+    auto B = [&](int32_t i) { return bl[i]; };
+    amg_rows<T, false>(L.Rs, nullptr, vb, B, B, F, put, [&]() { return state == CG_ITER; });
+    return;
+  }
+  // the partial sums of either parity, in flight ahead of the rows
+  const int it = c->it_a;
+  double t[2] = {0.0, 0.0};
+  for (int j = threadIdx.x; j < a.G; j += blockDim.x) {
+    t[0] += slot(a, 4)[j];
+    t[1] += slot(a, 6)[j];
+  }
+  auto B = [&](int32_t i) { return (T)r64[i]; };
+  amg_rows<T, true>(L.Rs, nullptr, vb, B, B, F, put, [&]() {
+    block_sum<2>(t);
+    if (state != CG_ITER) return false;
+    if (it == 0 || !recursion_stops(a, c, it, t[(it - 1) & 1])) return true;
+    if (vb.id == 0 && threadIdx.x == 0) {
+      c->state = CG_RECHECK;
+      c->iters_final = c->iters + it;
+    }
+    return false;
+  });
 }
 
-// Coarsest level: x = A^-1 b with the dense inverse, one wave per row.
+// Coarsest level: x = M b with its dense matrix, one wave per row, eight
+// entries per lane in flight.
 template <typename T>
 __device__ inline void amg_coarse_body(const CgArgs& a, int64_t n, const T* inv,
                                        const T* b, T* x, VB vb) {
-  if (a.ctrl->state != CG_ITER) return;
+  const int32_t state = a.ctrl->state;
   const Range rows = my_range(n, vb);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t i0 = rows.lo; i0 < rows.hi; i0 += blockDim.x >> 6) {
-    const int64_t i = i0 + wave;
+  for (int64_t i = rows.lo + wave; i < rows.hi; i += blockDim.x >> 6) {
+    const T* __restrict__ m = inv + i * n;
     T s = 0;
-    if (i < rows.hi)
-      for (int64_t j = lane; j < n; j += 64) s += inv[i * n + j] * b[j];
+    for (int64_t j0 = lane; j0 < n; j0 += 8 * 64) {
+      T mv[8], bv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int64_t j = j0 + 64 * u;
+        mv[u] = j < n ? m[j] : T(0);
+        bv[u] = j < n ? b[j] : T(0);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += mv[u] * bv[u];
+    }
+    if (state != CG_ITER) return;
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (i < rows.hi && lane == 0) x[i] = s;
+    if (lane == 0) x[i] = s;
   }
 }
 
@@ -1028,27 +1100,31 @@ __device__ inline void amg_coarse_body(const CgArgs& a, int64_t n, const T* inv,
 template <typename T>
 __device__ inline void amg_up_body(const CgArgs& a, const AmgLevel& L,
                                    int level, const T* __restrict__ y, VB vb) {
-  if (a.ctrl->state != CG_ITER) return;
+  const int32_t state = a.ctrl->state;
+  const int it = a.ctrl->it_a;
   const LevelVecs<T> V = level_vecs<T>(L);
   const double* __restrict__ r64 = a.r;
   const T* __restrict__ bl = V.b;
   const T* __restrict__ dinv = V.dinv;
   const T omega = (T)L.omega;
-  auto B = [&](int64_t c) -> T { return level == 0 ? (T)r64[c] : bl[c]; };
+  const T* __restrict__ z0 = (const T*)a.z;
+  auto Z = [&](int64_t c) -> T { return level == 0 ? z0[c] : bl[c] * dinv[c]; };
   double v[1] = {0.0};
-  amg_rows<T>(L.A, &L.Ps, vb, [&](int32_t c) { return B(c) * dinv[c]; },
-              [&](int32_t c) { return y[c]; },
-              [&](int64_t r, T ax, T py) { return py - (omega * omega) * (dinv[r] * ax); },
-              [&](int64_t r, T s) {
-                const T o = (T(2) * omega) * (dinv[r] * B(r)) + s;
-                if (level == 0) {
-                  a.u[r] = (double)o;
-                  v[0] += r64[r] * (double)o;
-                } else {
-                  V.t[r] = o;
-                }
-              });
-  if (level == 0) write_partials<1>(slot(a, 5 + 2 * (a.ctrl->it_a & 1)), a.G, v, vb);
+  const bool on = amg_rows<T, false>(
+      L.A, &L.Ps, vb, [&](int32_t c) { return Z(c); },
+      [&](int32_t c) { return y[c]; },
+      [&](int64_t r, T ax, T py) { return py - (omega * omega) * (dinv[r] * ax); },
+      [&](int64_t r, T s) {
+        const T o = (T(2) * omega) * Z(r) + s;
+        if (level == 0) {
+          a.u[r] = (double)o;
+          v[0] += r64[r] * (double)o;
+        } else {
+          V.t[r] = o;
+        }
+      },
+      [&]() { return state == CG_ITER; });
+  if (on && level == 0) write_partials<1>(slot(a, 5 + 2 * (it & 1)), a.G, v, vb);
 }
 
 // w = K u and (w,u); it_b = it_a.
@@ -1076,34 +1152,65 @@ __device__ inline void amg_upd_body(const CgArgs& a, VB vb) {
   if (c->state != CG_ITER) return;
   const int it = c->it_b;
   const int pb = it & 1;
-  double t1[1], t2[1];
-  totals<1>(slot(a, 5 + 2 * pb), a.G, 1, t1);
-  totals<1>(slot(a, 8 + pb), a.G, 1, t2);
-  const double gamma = t1[0];
+  const double g_prev = c->gamma[pb ^ 1], a_prev = c->alpha[pb ^ 1];
+  double t[2] = {0.0, 0.0};
+  for (int j = threadIdx.x; j < a.G; j += blockDim.x) {
+    t[0] += slot(a, 5 + 2 * pb)[j];
+    t[1] += slot(a, 8 + pb)[j];
+  }
+  // two rows per trip, the first trip's loads in flight ahead of the sums
+  const Range rows = my_range(a.m.n_free, vb);
+  const bool first = it == 0;
+  double u[2], w[2], p[2], sv[2], x[2], r[2];
+  auto fetch = [&](int64_t i0) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int64_t i = i0 + k * (int64_t)blockDim.x;
+      if (i >= rows.hi) continue;
+      u[k] = a.u[i];
+      w[k] = a.w[i];
+      x[k] = a.x[i];
+      r[k] = a.r[i];
+      if (!first) {
+        p[k] = a.p[i];
+        sv[k] = a.s[i];
+      }
+    }
+  };
+  const int64_t lo = rows.lo + threadIdx.x, step = 2 * (int64_t)blockDim.x;
+  fetch(lo);
+  block_sum<2>(t);
+  const double gamma = t[0];
   double alpha, beta;
-  if (it == 0) {
+  if (first) {
     beta = 0.0;
-    alpha = gamma / t2[0];
+    alpha = gamma / t[1];
   } else {
-    beta = gamma / c->gamma[pb ^ 1];
-    alpha = gamma / (t2[0] - beta * gamma / c->alpha[pb ^ 1]);
+    beta = gamma / g_prev;
+    alpha = gamma / (t[1] - beta * gamma / a_prev);
   }
   if (vb.id == 0 && threadIdx.x == 0) {
     c->gamma[pb] = gamma;
     c->alpha[pb] = alpha;
     c->it_a = it + 1;
   }
-  const Range rows = my_range(a.m.n_free, vb);
   double v[1] = {0.0};
-  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
-    const double pi = it == 0 ? a.u[i] : a.u[i] + beta * a.p[i];
-    const double si = it == 0 ? a.w[i] : a.w[i] + beta * a.s[i];
-    a.p[i] = pi;
-    a.s[i] = si;
-    a.x[i] += alpha * pi;
-    const double ri = a.r[i] - alpha * si;
-    a.r[i] = ri;
-    v[0] += ri * ri;
+  for (int64_t i0 = lo; i0 < rows.hi; i0 += step) {
+    if (i0 > lo) fetch(i0);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int64_t i = i0 + k * (int64_t)blockDim.x;
+      if (i >= rows.hi) continue;
+      const double pi = first ? u[k] : u[k] + beta * p[k];
+      const double si = first ? w[k] : w[k] + beta * sv[k];
+      a.p[i] = pi;
+      a.s[i] = si;
+      a.x[i] = x[k] + alpha * pi;
+      const double ri = r[k] - alpha * si;
+      a.r[i] = ri;
+      amg_put_z(a, i, ri);
+      v[0] += ri * ri;
+    }
   }
   write_partials<1>(slot(a, 4 + 2 * pb), a.G, v, vb);
 }
