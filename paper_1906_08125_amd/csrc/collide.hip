@@ -2,8 +2,8 @@
 // superparticles of each tet, on slots sorted by tet (as a re-sort leaves
 // them):
 //   k_coll_keys      a Philox key per superparticle, (step, id) counter;
-//   k_coll_rank      each superparticle finds the run of its tet (a scan
-//                    of its neighbours) and, in a short run, its rank by
+//   k_coll_rank      each superparticle finds the run of its tet (ballots
+//                    over its neighbours) and, in a short run, its rank by
 //                    (key, id, slot); perm lists the run in rank order;
 //   k_coll_rank_big  long runs (the tets at the emitter hold hundreds):
 //                    a workgroup per run, keys staged through LDS;
@@ -34,7 +34,6 @@ constexpr int kRankTile = 1024;  // keys per LDS tile of a long run
 constexpr int kBigRuns = 1024;   // long runs ranked side by side
 constexpr int kBigChunks = 4;    // member chunks of a run side by side
 constexpr double kLandau = 13.0;
-constexpr double kTwoPi = 6.283185307179586;
 
 __device__ inline double3 ld_v(const CollideArgs& a, int32_t i) {
   if (a.f32)
@@ -56,9 +55,11 @@ __device__ inline void st_v(const CollideArgs& a, int32_t i, double3 v) {
   }
 }
 
-// Tet volume from the stored inverse map: V = 1 / (6 |det m|).
-__device__ inline double tet_volume(const TetGeom& g) {
-  const double* r = g.m;
+// Tet volume from the stored inverse map: V = 1 / (6 |det m|).  (Packed
+// records: the map's number and its entry of the table, a few lines that
+// stay in cache, instead of a record per pair.)
+__device__ inline double tet_volume(const DevMesh& m, int32_t t) {
+  const double* r = m.tc ? m.maps + m.tc[t].map * kMapLen : m.tg[t].m;
   const double det = r[0] * (r[4] * r[8] - r[5] * r[7]) -
                      r[1] * (r[3] * r[8] - r[5] * r[6]) +
                      r[2] * (r[3] * r[7] - r[4] * r[6]);
@@ -79,7 +80,8 @@ __device__ void collide_pair(const CollideArgs& a, int32_t ia, int32_t ib,
                 (uint64_t)j, r);
   const double U1 = 1.0 - unit_double(r[0]), U2 = unit_double(r[1]),
                U3 = unit_double(r[2]);
-  const double g = sqrt(-2.0 * log(U1)) * cos(kTwoPi * U2);
+  // (angles as multiples of pi: their reduction is exact and short)
+  const double g = sqrt(-2.0 * log(U1)) * cospi(2.0 * U2);
   double delta = sqrt(var) * g;
   double st, omc;  // sin theta, 1 - cos theta
   if (delta != delta) delta = 0.0;  // infinite variance times g = 0
@@ -91,9 +93,8 @@ __device__ void collide_pair(const CollideArgs& a, int32_t ia, int32_t ib,
     st = 2.0 * r;
     omc = 2.0 - 2.0 * r * r;
   }
-  const double phi = kTwoPi * U3;
   double sp, cp;
-  sincos(phi, &sp, &cp);
+  sincospi(2.0 * U3, &sp, &cp);
   const double up = sqrt(ux * ux + uy * uy);
   double dx, dy, dz;
   if (up > 0.0) {
@@ -138,61 +139,81 @@ __device__ inline int before(uint64_t kj, int64_t dj, int32_t j, uint64_t ki,
          ((int)(kj == ki) & ((int)(dj < di) | ((int)(dj == di) & (int)(j < i))));
 }
 
-// Every wave stages the tets, keys, ids and weights of the slots
-// [i0 - 64, i0 + 128) around its 64 slots in LDS; each slot scans its
-// neighbours there (at most kSmallRun + 1 each way) for the run of its
-// tet.  A run of up to kSmallRun is ranked here (each member counts the
-// members before it; the first member sums the weights); the first member
-// of a longer run finds its end by binary search and lists it for
-// k_coll_rank_big.
-constexpr int kWin = 192;    // staged slots per wave
+// A wave takes 64 slots and sees the window [i0 - 64, i0 + 128) around
+// them.  Three ballots mark where a run of equal tets starts in the window;
+// a slot's run is then between two set bits (at most kSmallRun long, it lies
+// inside).  A run of up to kSmallRun is ranked here: each member counts the
+// smaller keys in LDS, and the run's weights are a difference of prefix sums
+// over the wave.  The first member of a longer run finds its end by binary
+// search and lists it for k_coll_rank_big.
+// Bound: LDS reads of the keys (one per member and run member) and the
+// latency of the loads.  Scanning the neighbours' tets slot by slot, with
+// ids and weights staged as well, took 43 us at 500k superparticles.
+constexpr int kWin = 192;    // slots of the window
 constexpr int kWinLo = 64;   // of them before the wave's first slot
-// the backward scan reads down to li - kSmallRun - 1 >= 0, the forward
-// scan up to li + kSmallRun + 1 < kWin (li = kWinLo + lane)
-static_assert(kSmallRun + 1 <= kWinLo, "the backward scan stays staged");
-static_assert(kWinLo + 63 + kSmallRun + 1 < kWin, "the forward scan too");
+static_assert(kSmallRun <= kWinLo - 2, "a short run lies in the window");
 
 __global__ void __launch_bounds__(kThreads) k_coll_rank(CollideArgs a) {
-  __shared__ int32_t s_tet[kThreads / 64][kWin];
   __shared__ uint64_t s_key[kThreads / 64][kWin];
-  __shared__ int64_t s_id[kThreads / 64][kWin];
-  __shared__ double s_w[kThreads / 64][kWin];
   const int32_t n = *a.n_slots;
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
   const int32_t stride = gridDim.x * blockDim.x;
+  const uint64_t upto = ~0ull >> (63 - lane);  // bits 0 .. lane
   // wave-uniform loop over blocks of 64 slots
   for (int32_t i0 = blockIdx.x * blockDim.x + (threadIdx.x - lane); i0 < n;
        i0 += stride) {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    int32_t tt[kWin / 64], tp[kWin / 64];
+    long long q[2];
 #pragma unroll
     for (int k = 0; k < kWin / 64; ++k) {
       const int32_t j = i0 - kWinLo + 64 * k + lane;
       const bool in = j >= 0 && j < n;
-      s_tet[wv][64 * k + lane] = in ? a.tet[j] : -2;
+      tt[k] = in ? a.tet[j] : -2;
+      tp[k] = j >= 1 && j <= n ? a.tet[j - 1] : -2;
       s_key[wv][64 * k + lane] = in ? a.key[j] : 0;
-      s_id[wv][64 * k + lane] = in ? a.id[j] : 0;
-      s_w[wv][64 * k + lane] = in ? a.w[j] : 0.0;
+      if (k >= 1) q[k - 1] = in ? fx_round(a.w[j] * kFx) : 0;
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    uint64_t head[kWin / 64];
+#pragma unroll
+    for (int k = 0; k < kWin / 64; ++k) head[k] = __ballot(tt[k] != tp[k]);
+    // inclusive prefix sums of the weights of this wave's slots and of the
+    // 64 after them
+    long long sum[2] = {q[0], q[1]};
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const long long o = __shfl_up(sum[k], off, 64);
+        if (lane >= off) sum[k] += o;
+      }
     const int32_t i = i0 + lane;
     const int li = kWinLo + lane;  // this slot in the window
-    const int32_t t = i < n ? s_tet[wv][li] : -2;
+    const int32_t t = tt[1];
+    // [ls, le): the run, as far as the window shows it
+    const uint64_t lo1 = head[1] & upto, hi1 = head[1] & ~upto;
+    const int ls = lo1 ? kWinLo + 63 - __clzll((long long)lo1)
+                   : head[0] ? 63 - __clzll((long long)head[0]) : -1;
+    const int le = hi1 ? kWinLo + __ffsll((long long)hi1) - 1
+                   : head[2] ? kWinLo + 64 + __ffsll((long long)head[2]) - 1 : kWin;
+    // (every lane takes part in the shuffles)
+    const long long s_end1 = __shfl(sum[0], le - kWinLo - 1, 64);
+    const long long s_all1 = __shfl(sum[0], 63, 64);
+    const long long s_end2 = __shfl(sum[1], le - kWinLo - 65, 64);
     if (i >= n) continue;
     if (t < 0) {
       a.seg_n[i] = 0;
       continue;
     }
-    int ls = li, le = li + 1;
-    while (li - ls <= kSmallRun && s_tet[wv][ls - 1] == t) --ls;
-    while (le - ls <= kSmallRun && s_tet[wv][le] == t) ++le;
-    const int32_t s = i0 - kWinLo + ls, e = i0 - kWinLo + le;
-    if (le - ls > kSmallRun) {
+    const int cnt = le - ls;
+    if (ls < 0 || cnt > kSmallRun) {
       // a long run: its members are handled by k_coll_rank_big
-      if (ls == li && s_tet[wv][li - 1] != t) {
-        int32_t lo = e, hi = n;  // first slot past the run
+      if (ls == li) {
+        int32_t lo = i0 - kWinLo + le, hi = n;  // first slot past the run
         while (lo < hi) {
           const int32_t mid = (lo + hi) >> 1;
           if (a.tet[mid] == t) lo = mid + 1; else hi = mid;
@@ -202,20 +223,27 @@ __global__ void __launch_bounds__(kThreads) k_coll_rank(CollideArgs a) {
       }
       continue;
     }
+    const int32_t s = i0 - kWinLo + ls;
     a.seg_s[i] = s;
-    a.seg_n[i] = e - s;
+    a.seg_n[i] = cnt;
     const uint64_t ki = s_key[wv][li];
-    const int64_t di = s_id[wv][li];
-    int32_t rank = 0;
+    int32_t rank = 0, same = 0;
 #pragma unroll 4
-    for (int j = ls; j < le; ++j)
-      rank += before(s_key[wv][j], s_id[wv][j], i0 - kWinLo + j, ki, di, i);
-    a.perm[s + rank] = i;
-    if (ls == li) {
-      long long q = 0;
-      for (int j = ls; j < le; ++j) q += fx_round(s_w[wv][j] * kFx);
-      a.seg_q[s] = q;
+    for (int j = ls; j < le; ++j) {
+      const uint64_t kj = s_key[wv][j];
+      rank += (int)(kj < ki);
+      same += (int)(kj == ki);
     }
+    if (same > 1) {  // equal keys: by (key, id, slot)
+      const int64_t di = a.id[i];
+      rank = 0;
+      for (int32_t j = s; j < s + cnt; ++j)
+        rank += before(a.key[j], a.id[j], j, ki, di, i);
+    }
+    a.perm[s + rank] = i;
+    if (ls == li)
+      a.seg_q[s] = le <= kWinLo + 64 ? s_end1 - sum[0] + q[0]
+                                     : s_all1 - sum[0] + q[0] + s_end2;
   }
 }
 
@@ -268,12 +296,12 @@ __global__ void __launch_bounds__(kThreads) k_coll_rank_big(CollideArgs a) {
   }
 }
 
-// The collision(s) led by position p of a run (rank p - s): the pair
-// (p, p + 1), or the odd run's triple at p = s.
-__device__ void collide_at(const CollideArgs& a, int32_t p, int32_t n) {
-  const int32_t cnt = a.seg_n[p];
-  const int32_t s = a.seg_s[p];
-  const bool triple = (cnt & 1) != 0 && p == s;
+// The collision(s) led by position p of a run from slot s (rank p - s): the
+// pair (p, p + 1), or the odd run's triple at p = s; run holds s, with the
+// sign bit set for a triple.
+__device__ void collide_at(const CollideArgs& a, int32_t p, int32_t run, int32_t n) {
+  const int32_t s = run & 0x7fffffff;
+  const bool triple = run < 0;
   // (range checks: with tets out of order a run's perm entries may be
   // stale; the result is then wrong but stays inside the arrays)
   const int32_t i0 = a.perm[p];
@@ -282,7 +310,7 @@ __device__ void collide_at(const CollideArgs& a, int32_t p, int32_t n) {
   if ((uint32_t)i0 >= (uint32_t)n || (uint32_t)i1 >= (uint32_t)n ||
       (uint32_t)i2 >= (uint32_t)n || a.tet[i0] < 0)
     return;
-  const double V = tet_volume(a.m.tg[a.tet[i0]]);
+  const double V = tet_volume(a.m, a.tet[i0]);
   const double ws = (double)a.seg_q[s] * (1.0 / kFx);
   const double nv = (a.w_sp * ws) * kLandau * a.dt_coll / V;
   const int64_t lead = a.id[i0];
@@ -299,7 +327,7 @@ __device__ void collide_at(const CollideArgs& a, int32_t p, int32_t n) {
 // positions of its blocks in LDS and collides them 64 at a time, all lanes
 // busy in the arithmetic.
 __global__ void __launch_bounds__(kThreads) k_coll_pair(CollideArgs a) {
-  __shared__ int32_t s_lead[kThreads / 64][128];
+  __shared__ int2 s_lead[kThreads / 64][128];  // (position, run)
   const int32_t n = *a.n_slots;
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
@@ -309,26 +337,30 @@ __global__ void __launch_bounds__(kThreads) k_coll_pair(CollideArgs a) {
        i0 += gridDim.x * blockDim.x) {
     const int32_t p = i0 + lane;
     bool lead = false;
+    int32_t run = 0;
     if (p < n) {
       const int32_t cnt = a.seg_n[p];
+      const int32_t s = a.seg_s[p];
       if (cnt >= 2) {
-        const int32_t r = p - a.seg_s[p];
+        const int32_t r = p - s;
         if (r >= 0 && r < cnt) {  // (only out-of-order tets fail this)
           const bool odd = (cnt & 1) != 0;
           lead = odd ? (r == 0 || (r >= 3 && ((r - 3) & 1) == 0 && r + 1 < cnt))
                      : ((r & 1) == 0);
+          run = odd && r == 0 ? s | (int32_t)0x80000000 : s;
         }
       }
     }
     const uint64_t m = __ballot(lead);
-    if (lead) s_lead[wv][qn + __popcll(m & below)] = p;
+    if (lead) s_lead[wv][qn + __popcll(m & below)] = make_int2(p, run);
     qn += __popcll(m);
     if (qn >= 64) {
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      collide_at(a, s_lead[wv][lane], n);
+      const int2 l = s_lead[wv][lane];
+      collide_at(a, l.x, l.y, n);
       const int rest = qn - 64;
-      const int32_t mv = lane < rest ? s_lead[wv][64 + lane] : 0;
+      const int2 mv = lane < rest ? s_lead[wv][64 + lane] : make_int2(0, 0);
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();
       if (lane < rest) s_lead[wv][lane] = mv;
@@ -337,7 +369,10 @@ __global__ void __launch_bounds__(kThreads) k_coll_pair(CollideArgs a) {
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  if (lane < qn) collide_at(a, s_lead[wv][lane], n);
+  if (lane < qn) {
+    const int2 l = s_lead[wv][lane];
+    collide_at(a, l.x, l.y, n);
+  }
 }
 
 }  // namespace
