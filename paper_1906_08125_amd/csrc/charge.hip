@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(kThreads) k_cut_bin(ChargeArgs a) {
 // Exclusive scan of the counts in place, cnt[c] becoming the first slot of
 // cell c and cnt[n_cells] the total, in tiles of 1024 cells (blockIdx.y 0:
 // atoms, 1: faces): k_cut_scan_tiles scans each tile and keeps its total,
-// k_cut_scan_top scans the totals, k_cut_scan_add adds them back.
+// k_cut_scan_add adds the sum of the totals before the tile's.
 __device__ inline int32_t block_excl_scan(int32_t v, int32_t* part, int32_t& total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int32_t x = v;
@@ -285,25 +285,18 @@ __global__ void __launch_bounds__(1024) k_cut_scan_tiles(ChargeArgs a) {
   if (threadIdx.x == 0) tsum[blockIdx.x] = total;
 }
 
-__global__ void __launch_bounds__(1024) k_cut_scan_top(ChargeArgs a) {
-  __shared__ int32_t part[17];
-  int32_t* cnt = blockIdx.x == 0 ? a.a_cnt : a.f_cnt;
-  int32_t* tsum = cnt + a.n_cells_pad;
-  const int64_t n = (int64_t)a.nx * a.ny * a.nz;
-  const int tiles = (int)((n + 1023) / 1024);
-  const int32_t v = (int)threadIdx.x < tiles ? tsum[threadIdx.x] : 0;
-  int32_t total;
-  const int32_t e = block_excl_scan(v, part, total);
-  if ((int)threadIdx.x < tiles) tsum[threadIdx.x] = e;
-  if (threadIdx.x == 0) cnt[n] = total;
-}
-
 __global__ void __launch_bounds__(1024) k_cut_scan_add(ChargeArgs a) {
+  __shared__ int32_t part[17];
   int32_t* cnt = blockIdx.y == 0 ? a.a_cnt : a.f_cnt;
   const int32_t* tsum = cnt + a.n_cells_pad;
   const int64_t n = (int64_t)a.nx * a.ny * a.nz;
+  // the sum of the tiles before this one (at most 1023 of them)
+  const int32_t v = (int)threadIdx.x < (int)blockIdx.x ? tsum[threadIdx.x] : 0;
+  int32_t before;
+  (void)block_excl_scan(v, part, before);
   const int64_t i = blockIdx.x * 1024ll + threadIdx.x;
-  if (i < n) cnt[i] += tsum[blockIdx.x];
+  if (i < n) cnt[i] += before;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) cnt[n] = before + tsum[blockIdx.x];
 }
 
 // Every item at its arrival slot of its cell (tmp), then at its place in
@@ -391,10 +384,15 @@ __global__ void __launch_bounds__(kThreads) k_cut_rank(ChargeArgs a) {
 // consecutive members (coalesced loads), four per lane and trip; lanes
 // past the end get p = 0 with valid false (f loads unconditionally and
 // only drops the contribution, so the four loads go out together).  Each
-// lane sees its own members; the caller reduces over the wave.  Every wave
-// of the workgroup calls this alike (it holds workgroup barriers).
+// lane sees its own members (every lane calls f); the caller reduces over
+// the wave.
 constexpr int kCutKMax = 5;
 constexpr int kSegMax = 4 * 64;
+
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 template <typename F>
 __device__ inline void wave_block_members(const ChargeArgs& a, const int32_t* cnt,
@@ -456,13 +454,14 @@ __device__ inline void wave_block_members(const ChargeArgs& a, const int32_t* cn
     run += len[u];
   }
   if (lane == 63) s_pre[kSegMax] = T;
-  __syncthreads();
-  for (int32_t c0 = lane; c0 < T; c0 += 256) {
+  wave_sync();
+  for (int32_t c0 = 0; c0 < T; c0 += 256) {
+    const int32_t cl = c0 + lane;
     int32_t p[4];
     bool v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int32_t cc = c0 + 64 * u;
+      const int32_t cc = cl + 64 * u;
       v[u] = cc < T;
       // the last run whose prefix is <= cc (runs of length 0 share a
       // prefix with the next one; the search lands on the last of them)
@@ -471,10 +470,62 @@ __device__ inline void wave_block_members(const ChargeArgs& a, const int32_t* cn
         if (s_pre[sg + step] <= cc) sg += step;
       p[u] = v[u] ? s_lo[sg] + (cc - s_pre[sg]) : 0;
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) f(p[u], v[u]);
+    f(p, v);
   }
-  __syncthreads();
+  wave_sync();
+}
+
+// The coordinates of four members.
+__device__ inline void load4(const double* xyz, const int32_t (&p)[4], double (&x)[4],
+                             double (&y)[4], double (&z)[4]) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    x[u] = xyz[3 * (int64_t)p[u]];
+    y[u] = xyz[3 * (int64_t)p[u] + 1];
+    z[u] = xyz[3 * (int64_t)p[u] + 2];
+  }
+}
+
+// Kept pairs queued per wave: about half of the candidates pass the screen,
+// and a lane whose candidate does not would wait through the other lanes'
+// root, exponential and divisions, so those are taken 64 queued pairs at a
+// time.  heavy(d2, p) is called with every lane that has a pair.  The charge
+// of a 48^2 x 96 tip's faces and atoms (seven launches): 97 us with each lane
+// taking its own pairs and workgroup barriers, 89 so.
+constexpr int kQueue = 128;
+struct PairQueue {
+  double d2[kQueue];
+  int32_t p[kQueue];
+};
+template <typename H>
+__device__ inline void queue_pair(PairQueue& q, int& n, bool keep, double d2, int32_t p,
+                                  H&& heavy) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t m = __ballot(keep);
+  if (keep) {
+    const int k = n + __popcll(m & ((1ull << lane) - 1ull));
+    q.d2[k] = d2;
+    q.p[k] = p;
+  }
+  n += __popcll(m);
+  if (n >= 64) {
+    wave_sync();
+    heavy(q.d2[lane], q.p[lane]);
+    n -= 64;
+    const double d = q.d2[64 + lane];
+    const int32_t pp = q.p[64 + lane];
+    wave_sync();
+    if (lane < n) {
+      q.d2[lane] = d;
+      q.p[lane] = pp;
+    }
+  }
+}
+template <typename H>
+__device__ inline void queue_rest(PairQueue& q, int n, H&& heavy) {
+  const int lane = threadIdx.x & 63;
+  wave_sync();
+  if (lane < n) heavy(q.d2[lane], q.p[lane]);
 }
 
 // Squared minimum-image distance in the order dist_mi sums it (its root is
@@ -503,22 +554,24 @@ constexpr double kScreen = 1.0 + 1e-12;
 __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
   __shared__ int32_t s_lo[kThreads / 64][kSegMax];
   __shared__ int32_t s_pre[kThreads / 64][kSegMax + 1];
+  __shared__ PairQueue s_q[kThreads / 64];
   const DevMesh& m = a.m;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  // a wave past the last face still takes part in the workgroup barriers
-  const int64_t p0 = blockIdx.x * (int64_t)(blockDim.x >> 6) + wv;
-  const bool live = p0 < m.n_emit;
-  const int64_t pf = live ? p0 : m.n_emit - 1;
+  const int64_t pf = blockIdx.x * (int64_t)(blockDim.x >> 6) + wv;
+  if (pf >= m.n_emit) return;
   const double cx = a.f_cen[3 * pf], cy = a.f_cen[3 * pf + 1], cz = a.f_cen[3 * pf + 2];
   const Cell3 cc = cell_of(a, cx, cy, cz);
   const double* ax = a.a_xyz;
   double m2 = 1.0 / 0.0;
   wave_block_members(a, a.a_cnt, cc, 1, 1.0 / 0.0, s_lo[wv], s_pre[wv],
-                     [&](int32_t p, bool v) {
-                       const double d2 = dist2_mi(m, cx, cy, cz, ax[3 * (int64_t)p],
-                                                  ax[3 * (int64_t)p + 1],
-                                                  ax[3 * (int64_t)p + 2]);
-                       m2 = v && d2 < m2 ? d2 : m2;
+                     [&](const int32_t (&p)[4], const bool (&v)[4]) {
+                       double x[4], y[4], z[4];
+                       load4(ax, p, x, y, z);
+#pragma unroll
+                       for (int u = 0; u < 4; ++u) {
+                         const double d2 = dist2_mi(m, cx, cy, cz, x[u], y[u], z[u]);
+                         m2 = v[u] && d2 < m2 ? d2 : m2;
+                       }
                      });
   m2 = wave_min_d(m2);
   double dmin = sqrt(m2);
@@ -532,21 +585,27 @@ __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
     dmin = wave_min_d(dmin);
   }
   const double cut = kCutRc * a.r_c;
-  const double bnd = (dmin + cut) * kScreen;
-  const double b2 = bnd * bnd;
   double S = 0.0;
-  // (every wave takes the walk's barriers; a far face's walk is empty)
-  wave_block_members(a, a.a_cnt, cc, far ? 0 : a.K, far ? -1.0 : b2, s_lo[wv], s_pre[wv],
-                     [&](int32_t p, bool v) {
-                       const double d2 = dist2_mi(m, cx, cy, cz, ax[3 * (int64_t)p],
-                                                  ax[3 * (int64_t)p + 1],
-                                                  ax[3 * (int64_t)p + 2]);
-                       if (v && d2 <= b2) {
-                         const double t = sqrt(d2) - dmin;
-                         if (t <= cut) S += exp(-t / a.r_c);
-                       }
-                     });
-  if (far) {
+  if (!far) {
+    const double bnd = (dmin + cut) * kScreen;
+    const double b2 = bnd * bnd;
+    int n = 0;
+    auto heavy = [&](double d2, int32_t) {
+      const double t = sqrt(d2) - dmin;
+      if (t <= cut) S += exp(-t / a.r_c);
+    };
+    wave_block_members(a, a.a_cnt, cc, a.K, b2, s_lo[wv], s_pre[wv],
+                       [&](const int32_t (&p)[4], const bool (&v)[4]) {
+                         double x[4], y[4], z[4];
+                         load4(ax, p, x, y, z);
+#pragma unroll
+                         for (int u = 0; u < 4; ++u) {
+                           const double d2 = dist2_mi(m, cx, cy, cz, x[u], y[u], z[u]);
+                           queue_pair(s_q[wv], n, v[u] && d2 <= b2, d2, p[u], heavy);
+                         }
+                       });
+    queue_rest(s_q[wv], n, heavy);
+  } else {
     const double3 c = make_double3(cx, cy, cz);
     for (int64_t j = lane; j < a.n_atoms; j += 64) {
       const double t = dist_mi(m, c, a.atoms + 3 * j) - dmin;
@@ -554,7 +613,7 @@ __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
     }
   }
   S = wave_sum_d(S);
-  if (lane == 0 && live) {
+  if (lane == 0) {
     const int32_t f = a.f_idx[pf];
     a.f_min[f] = dmin;
     a.f_sum[f] = S;
@@ -570,30 +629,39 @@ __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
 __global__ void __launch_bounds__(kThreads) k_atom_charge_cut(ChargeArgs a) {
   __shared__ int32_t s_lo[kThreads / 64][kSegMax];
   __shared__ int32_t s_pre[kThreads / 64][kSegMax + 1];
+  __shared__ PairQueue s_q[kThreads / 64];
   const bool any_far = *a.n_far != 0;
   const DevMesh& m = a.m;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t p0 = blockIdx.x * (int64_t)(blockDim.x >> 6) + wv;
-  const bool live = p0 < a.n_atoms;
-  const int64_t pa = live ? p0 : a.n_atoms - 1;
+  const int64_t pa = blockIdx.x * (int64_t)(blockDim.x >> 6) + wv;
+  if (pa >= a.n_atoms) return;
   const double at[3] = {a.a_xyz[3 * pa], a.a_xyz[3 * pa + 1], a.a_xyz[3 * pa + 2]};
-  const Cell3 cc = cell_of(a, at[0], at[1], at[2]);
   const double cut = kCutRc * a.r_c;
   const double R = a.c_min + cut;
   double q = 0.0;
-  wave_block_members(a, a.f_cnt, cc, any_far ? 0 : a.K, any_far ? -1.0 : R * R,
-                     s_lo[wv], s_pre[wv], [&](int32_t p, bool v) {
-                       const int64_t g = p;
-                       const double fm = a.f_min_s[g];
-                       const double d2 = dist2_mi(m, a.f_cen[3 * g], a.f_cen[3 * g + 1],
-                                                  a.f_cen[3 * g + 2], at[0], at[1], at[2]);
-                       const double bd = (fm + cut) * kScreen;
-                       if (v && d2 <= bd * bd) {
-                         const double t = sqrt(d2) - fm;
-                         if (t <= cut) q += (a.f_Q_s[g] * exp(-t / a.r_c)) / a.f_sum_s[g];
-                       }
-                     });
-  if (any_far) {
+  if (!any_far) {
+    const Cell3 cc = cell_of(a, at[0], at[1], at[2]);
+    int n = 0;
+    auto heavy = [&](double d2, int32_t g) {
+      const double t = sqrt(d2) - a.f_min_s[g];
+      if (t <= cut) q += (a.f_Q_s[g] * exp(-t / a.r_c)) / a.f_sum_s[g];
+    };
+    wave_block_members(a, a.f_cnt, cc, a.K, R * R, s_lo[wv], s_pre[wv],
+                       [&](const int32_t (&p)[4], const bool (&v)[4]) {
+                         double x[4], y[4], z[4], fm[4];
+                         load4(a.f_cen, p, x, y, z);
+#pragma unroll
+                         for (int u = 0; u < 4; ++u) fm[u] = a.f_min_s[p[u]];
+#pragma unroll
+                         for (int u = 0; u < 4; ++u) {
+                           const double d2 =
+                               dist2_mi(m, x[u], y[u], z[u], at[0], at[1], at[2]);
+                           const double bd = (fm[u] + cut) * kScreen;
+                           queue_pair(s_q[wv], n, v[u] && d2 <= bd * bd, d2, p[u], heavy);
+                         }
+                       });
+    queue_rest(s_q[wv], n, heavy);
+  } else {
     for (int64_t g = lane; g < m.n_emit; g += 64) {
       const double3 fc = make_double3(a.f_cen[3 * g], a.f_cen[3 * g + 1], a.f_cen[3 * g + 2]);
       const double t = dist_mi(m, fc, at) - a.f_min_s[g];
@@ -601,7 +669,7 @@ __global__ void __launch_bounds__(kThreads) k_atom_charge_cut(ChargeArgs a) {
     }
   }
   q = wave_sum_d(q);
-  if (lane == 0 && live) a.atom_q[a.a_idx[pa]] = q;
+  if (lane == 0) a.atom_q[a.a_idx[pa]] = q;
 }
 
 }  // namespace
@@ -677,7 +745,6 @@ hipError_t surface_charge_launch(const ChargeArgs& a, int n_cu, hipStream_t s) {
     hipLaunchKernelGGL(k_cut_bin, dim3(grid_for(items)), dim3(kThreads), 0, s, a);
     const int tiles = (int)((n_cells + 1023) / 1024);
     hipLaunchKernelGGL(k_cut_scan_tiles, dim3(tiles, 2), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_cut_scan_top, dim3(2), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(k_cut_scan_add, dim3(tiles, 2), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(k_cut_fill, dim3(grid_for(items)), dim3(kThreads), 0, s, a);
     hipLaunchKernelGGL(k_cut_rank, dim3(grid_for(items)), dim3(kThreads), 0, s, a);
