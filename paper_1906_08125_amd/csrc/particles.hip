@@ -412,6 +412,36 @@ __device__ int scan_locate(const DevMesh& m, double x, double y, double z) {
   return -1;
 }
 
+// Whether the closed tet with vertices v holds p: no face sees p on its far
+// side.  The four signs are filtered first and the exact predicate -- a long
+// chain of dependent FP64 operations -- runs once per undecided sign, in one
+// place: a point on a face, the usual case here, has one, where four
+// predicates in a row cost a wave the exact path at each of them.
+__device__ inline bool tet_holds(const double* v, const double p[3]) {
+  double A[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) A[c] = v[c];
+  unsigned open = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    double B[12], bound;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) B[c] = c / 3 == k ? p[c % 3] : A[c];
+    const double det = vol6_filtered(B, B + 3, B + 6, B + 9, bound);
+    if (-det > bound) return false;
+    if (!(det > bound)) open |= 1u << k;
+  }
+  while (open) {
+    const int k = __ffs((int)open) - 1;
+    open &= open - 1u;
+    double B[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) B[c] = c / 3 == k ? p[c % 3] : A[c];
+    if (vol6_sign_exact(B, B + 3, B + 6, B + 9) < 0) return false;
+  }
+  return true;
+}
+
 // The same canonical location with the 64 lanes of a wave testing 64
 // candidates at a time (the point is uniform across the wave; every lane
 // must call it).  The lowest lane holding the point gives the lowest index.
@@ -432,10 +462,7 @@ __device__ int scan_locate_wave(const DevMesh& m, double x, double y,
     bool hit = false;
     if (q < q1) {
       const double* v = m.tw[m.bitem[q]].v;
-      hit = vol6_sign(p, v + 3, v + 6, v + 9) >= 0 &&
-            vol6_sign(v, p, v + 6, v + 9) >= 0 &&
-            vol6_sign(v, v + 3, p, v + 9) >= 0 &&
-            vol6_sign(v, v + 3, v + 6, p) >= 0;
+      hit = tet_holds(v, p);
     }
     const unsigned long long mask = __ballot(hit);
     if (mask) return m.bitem[base + __ffsll((long long)mask) - 1];
