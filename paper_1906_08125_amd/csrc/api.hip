@@ -1062,12 +1062,18 @@ pic_status pic_step(pic_mesh* h, const pic_particles* P, const pic_fields* F,
   hipError_t e = ensure_capacity(h, P->capacity, prm->resort_every > 0, f32 ? 4 : 8);
   if (e != hipSuccess) return hip_fail(e, "pic_step");
 
-  StepSet ss = step_set(h, P, F, prm, h->step_push[f32 ? 1 : 0], h->step_inj, h->grid_fb);
+  // Five waves per SIMD where four have fewer lanes than the arrays have
+  // slots (see k_particles); no more push workgroups than the slots fill
+  // (fewer to start and fewer counter rows to sum after every step).
+  const int waves = P->capacity > (int64_t)h->n_cu * 4 * fp::kParticleBlock ? 5 : 4;
+  const int grid_push = (int)std::min<int64_t>(
+      h->step_push[f32 ? 1 : 0][waves == 5],
+      std::max<int64_t>(8, ((P->capacity + fp::kParticleBlock - 1) / fp::kParticleBlock + 7) / 8 * 8));
+  StepSet ss = step_set(h, P, F, prm, grid_push, h->step_inj, h->grid_fb);
   if ((ps = use_precond(h, &prm->solve, ss.ca, s, "pic_step")) != PIC_OK) return ps;
   const fp::StepArgs& a = ss.a;
   const fp::EmitArgs& ea = ss.ea;
   fp::CgArgs& ca = ss.ca;
-  const int grid_push = h->step_push[f32 ? 1 : 0];
   const int grid_inj = h->step_inj;
   const int grid_fb = h->grid_fb;
   // The kernels of step k before its solve: clears + emission counts, the
@@ -1133,7 +1139,7 @@ pic_status pic_step(pic_mesh* h, const pic_particles* P, const pic_fields* F,
       prof_end(h, s);
     }
     prof_begin(h, PIC_K_PUSH, s);
-    if ((e = fp::launch_particles(ak, &ek, grid_push, grid_inj, s)) != hipSuccess) return e;
+    if ((e = fp::launch_particles(ak, ek, grid_push, grid_inj, waves, s)) != hipSuccess) return e;
     prof_end(h, s);
     prof_begin(h, PIC_K_FALLBACK, s);
     if ((e = fp::launch_fallback(ak, grid_fb, s)) != hipSuccess) return e;

@@ -71,7 +71,7 @@ static_assert(sizeof(TetGeom32) == 64, "TetGeom32 is half a line");
 // neighbour of the exit face is read when the walk leaves the tet).
 // Table entry: the map (9), then lam_c max_j |m_kj| for k = 1..3 (see
 // lam_test).
-constexpr int kMapMax = 32;
+constexpr int kMapMax = 16;
 constexpr int kMapLen = 12;
 struct alignas(64) TetPack {
   double v0[3];
@@ -428,13 +428,12 @@ __host__ __device__ inline void charge_split(const double lam[4], double w,
 
 // Bucket index along one axis: a monotone map, shared by registration and
 // query, so a tet registered from its closed bounding box is found by every
-// point it holds.
+// point it holds.  (x inside the grid's box, so that the quotient fits an
+// int; clamped as integers, which keeps n out of the vector registers.)
 __host__ __device__ inline int bucket_axis(double x, double x0, double inv,
                                            int n) {
-  const double f = floor((x - x0) * inv);
-  if (f < 0.0) return 0;
-  if (f > (double)(n - 1)) return n - 1;
-  return (int)f;
+  const int i = (int)floor((x - x0) * inv);
+  return i < 0 ? 0 : (i > n - 1 ? n - 1 : i);
 }
 
 // Sum of the per-workgroup counter rows of one step into its stats record

@@ -852,11 +852,12 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   // single round has no tail of late workgroups (measured on the production
   // tip: 3 resident per CU, 91 us per push against 100 us for 8 per CU and
   // 107 us for 4), and fewer injecting workgroups queue behind it.
-  for (int f32 = 0; f32 < 2; ++f32) {
-    const int per_cu = std::max(1, particle_blocks_per_cu(f32, packed));
-    int g = std::min(h->grid_push, std::max(8, h->n_cu * per_cu));
-    h->step_push[f32] = g >= 8 ? g - g % 8 : g;
-  }
+  for (int f32 = 0; f32 < 2; ++f32)
+    for (int five = 0; five < 2; ++five) {
+      const int per_cu = std::max(1, particle_blocks_per_cu(f32, packed, five ? 5 : 4));
+      int g = std::min(h->grid_push, std::max(8, h->n_cu * per_cu));
+      h->step_push[f32][five] = g >= 8 ? g - g % 8 : g;
+    }
   h->step_inj = std::min(h->grid_inj, std::max(8, (h->n_cu / 2) - (h->n_cu / 2) % 8));
   h->acc_rows = (int64_t*)dev_alloc(
       h, sizeof(int64_t) * 16 * (size_t)(h->grid_push + h->grid_inj + h->grid_fb), err);

@@ -10,6 +10,8 @@ struct EmitConsts {
   double a_fn, b_fn, c_s, j_unit;
 };
 
+constexpr int kParticleBlock = 256;  // threads of a particle workgroup
+
 struct StepArgs {
   DevMesh m;
   void *x, *y, *z, *vx, *vy, *vz;  // double, or float when f32
@@ -91,13 +93,14 @@ struct DepositArgs {
 
 hipError_t launch_begin(const EmitArgs& a, int grid, hipStream_t s);
 // Workgroups of the particle kernel (FP64 or FP32 storage; packed tet records
-// or not) resident on one compute unit at once, by the runtime's occupancy
-// calculator (0 on error).
-int particle_blocks_per_cu(int f32, int packed);
-// e: the step's emission, computed by workgroup 0 while the others push
-// (e.defer set; the injecting workgroups wait for it), or null
-hipError_t launch_particles(const StepArgs& a, const EmitArgs* e, int g_push,
-                            int g_inj, hipStream_t s);
+// or not, built for so many waves per SIMD) resident on one compute unit at
+// once, by the runtime's occupancy calculator (0 on error).
+int particle_blocks_per_cu(int f32, int packed, int waves);
+// e: the step's emission, computed by workgroup 0 while the others push (the
+// injecting workgroups wait for it).  waves: 4, or 5 (packed records only;
+// else taken as 4).
+hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
+                            int g_inj, int waves, hipStream_t s);
 hipError_t launch_stats(const int64_t* rows, int n_rows, pic_step_stats* st,
                         const int32_t* gate, hipStream_t s);
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s);

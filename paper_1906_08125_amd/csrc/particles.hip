@@ -9,6 +9,8 @@
 // Block b of the grid sweeps a contiguous slot range chosen so that the 8
 // XCDs (block b runs on XCD b mod 8) each see one contiguous eighth of the
 // slots; with particles sorted by tet, neighbouring tets then share an L2.
+#include <type_traits>
+
 #include "common.h"
 #include "particles.h"
 #include "solver.h"
@@ -18,7 +20,7 @@ namespace fp {
 namespace {
 
 constexpr int kMaxWalk = 256;
-constexpr int kBlock = 256;
+constexpr int kBlock = kParticleBlock;
 
 struct Span {
   int64_t lo, hi;
@@ -44,17 +46,17 @@ __device__ inline bool gate_closed(const int32_t* gate) {
   return st != CG_DONE && st != CG_NOCONV;
 }
 
-// Per-thread counters of one kernel, flushed once per block.
+// Per-thread counters of one kernel, flushed once per block (a thread's
+// counts fit 32 bits).
 struct Acc {
-  long long n_before, q_before, n_anode, q_anode, n_after, q_after;
-  long long n_cathode, q_cathode, n_inj, q_inj, walk_steps;
-  int walk_max;
+  long long q_before, q_anode, q_after, q_cathode, q_inj;
+  int n_before, n_anode, n_after, n_cathode, n_inj, walk_steps, walk_max;
 };
 
 __device__ inline void acc_zero(Acc& a) {
-  a.n_before = a.q_before = a.n_anode = a.q_anode = a.n_after = a.q_after = 0;
-  a.n_cathode = a.q_cathode = a.n_inj = a.q_inj = a.walk_steps = 0;
-  a.walk_max = 0;
+  a.q_before = a.q_anode = a.q_after = a.q_cathode = a.q_inj = 0;
+  a.n_before = a.n_anode = a.n_after = a.n_cathode = a.n_inj = 0;
+  a.walk_steps = a.walk_max = 0;
 }
 
 __device__ inline long long wave_sum(long long v) {
@@ -119,15 +121,18 @@ typedef __attribute__((address_space(3))) const float* lds_f;
 
 struct MapTable {
   double m[kMapMax * kMapLen];
+};
+struct MapTable32 : MapTable {  // with the FP32 maps of the mixed gather
   float m32[kMapMax * kMapLen];
 };
 
 // (the caller synchronizes)
-__device__ inline void maps_load(const DevMesh& m, MapTable& M, bool f32) {
-  for (int k = threadIdx.x; k < kMapMax * kMapLen; k += blockDim.x) {
-    M.m[k] = m.maps[k];
-    if (f32) M.m32[k] = m.maps32[k];
-  }
+__device__ inline void maps_load(const DevMesh& m, MapTable& M) {
+  for (int k = threadIdx.x; k < kMapMax * kMapLen; k += blockDim.x) M.m[k] = m.maps[k];
+}
+__device__ inline void maps_load(const DevMesh& m, MapTable32& M) {
+  maps_load(m, static_cast<MapTable&>(M));
+  for (int k = threadIdx.x; k < kMapMax * kMapLen; k += blockDim.x) M.m32[k] = m.maps32[k];
 }
 
 template <bool PK>
@@ -218,13 +223,13 @@ __device__ inline void gather_field(const Geo<PK>& g, const MapTable* M,
                                     const void* E, double x, double y,
                                     double z, double& ex, double& ey,
                                     double& ez) {
+  double lam[4];
+  geo_lam<PK>(g, M, x, y, z, lam);
   const int32_t* nd = g.node();
   const double4 e0 = ld_E(E, 0, nd[0]);
   const double4 e1 = ld_E(E, 0, nd[1]);
   const double4 e2 = ld_E(E, 0, nd[2]);
   const double4 e3 = ld_E(E, 0, nd[3]);
-  double lam[4];
-  geo_lam<PK>(g, M, x, y, z, lam);
   ex = ((lam[0] * e0.x + lam[1] * e1.x) + lam[2] * e2.x) + lam[3] * e3.x;
   ey = ((lam[0] * e0.y + lam[1] * e1.y) + lam[2] * e2.y) + lam[3] * e3.y;
   ez = ((lam[0] * e0.z + lam[1] * e1.z) + lam[2] * e2.z) + lam[3] * e3.z;
@@ -481,6 +486,9 @@ constexpr int kTable = 2048;  // > 4 nodes x the particles of one block
 struct ChargeTable {
   int32_t key[kTable];
   unsigned long long val[kTable];
+  // the workgroup's absorbed superparticles (rare: kept out of the threads'
+  // registers)
+  unsigned long long n_anode, q_anode;
 };
 
 __device__ inline void table_clear(ChargeTable& T) {
@@ -488,6 +496,7 @@ __device__ inline void table_clear(ChargeTable& T) {
     T.key[k] = -1;
     T.val[k] = 0ull;
   }
+  if (threadIdx.x == 0) T.n_anode = T.q_anode = 0ull;
   __syncthreads();
 }
 
@@ -538,17 +547,17 @@ __device__ inline void deposit_table(const int32_t* node, const double lam[4],
 }
 
 // G: the record of the hint tet (have_G), or to be loaded when needed.
+// (tet: the slot's tet id; i: the slot)
 template <bool PK>
 __device__ inline void settle(const DevMesh& m, const MapTable* M,
-                              const StepArgs& a, int64_t i, double x, double y,
-                              double z, int sx, int sy, int hint, Geo<PK>& G,
-                              double w, long long qfx,
-                              Acc& acc, ChargeTable& T, bool far,
-                              bool have_G = true) {
+                              const StepArgs& a, int32_t* tet, int32_t i,
+                              double x, double y, double z, int sx, int sy,
+                              int hint, Geo<PK>& G, double w, Acc& acc,
+                              ChargeTable& T, bool far, bool have_G = true) {
   if (z >= m.z_top) {
-    a.tet[i] = -1;
-    acc.n_anode += 1;
-    acc.q_anode += qfx;
+    *tet = -1;
+    lds_add_u64(&T.n_anode, 1ull);
+    lds_add_u64(&T.q_anode, (unsigned long long)fx_round(w * kFx));
     return;
   }
   int steps = 0;
@@ -557,14 +566,14 @@ __device__ inline void settle(const DevMesh& m, const MapTable* M,
   acc.walk_steps += steps;
   if (steps > acc.walk_max) acc.walk_max = steps;
   if (t >= 0) {
-    a.tet[i] = t;
+    *tet = t;
     deposit_table(G.node(), lam, w, T, a.charge);
     acc.n_after += 1;
-    acc.q_after += qfx;
+    acc.q_after += fx_round(w * kFx);
   } else {
-    a.tet[i] = hint;
+    *tet = hint;
     const int slot = atomicAdd(&a.scratch->n_fallback, 1);
-    a.queue[slot] = (int32_t)i;
+    a.queue[slot] = i;
   }
 }
 
@@ -837,17 +846,15 @@ __device__ inline void push_role64(const StepArgs& a, const MapTable* M, int g,
   double* VY = (double*)a.vy + sp.lo;
   double* VZ = (double*)a.vz + sp.lo;
   const double* W = a.w + sp.lo;
-  const int32_t* TT = a.tet + sp.lo;
-  const uint32_t len = (uint32_t)(sp.hi - sp.lo);
+  int32_t* TT = a.tet + sp.lo;
+  const uint32_t len = (uint32_t)(sp.hi - sp.lo), lo32 = (uint32_t)sp.lo;
   for (uint32_t j = threadIdx.x; j < len; j += blockDim.x) {
     const uint32_t o8 = j * 8u;
     const int t = at_off<const int32_t>(TT, j * 4u);
     if (t < 0) continue;
-    const int64_t i = sp.lo + j;
     const double w = at_off<const double>(W, o8);
-    const long long qfx = fx_round(w * kFx);
     acc.n_before += 1;
-    acc.q_before += qfx;
+    acc.q_before += fx_round(w * kFx);
     double x = at_off<double>(X, o8), y = at_off<double>(Y, o8), z = at_off<double>(Z, o8);
     double vx = at_off<double>(VX, o8), vy = at_off<double>(VY, o8),
            vz = at_off<double>(VZ, o8);
@@ -875,7 +882,8 @@ __device__ inline void push_role64(const StepArgs& a, const MapTable* M, int g,
     at_off<double>(VX, o8) = vx;
     at_off<double>(VY, o8) = vy;
     at_off<double>(VZ, o8) = vz;
-    settle<PK>(m, M, a, i, x, y, z, sx, sy, t, R, w, qfx, acc, T, far);
+    settle<PK>(m, M, a, &at_off<int32_t>(TT, j * 4u), (int32_t)(lo32 + j), x, y, z, sx, sy, t,
+               R, w, acc, T, far);
   }
 }
 
@@ -900,17 +908,15 @@ __device__ inline void push_role32(const StepArgs& a, const MapTable* M, int g,
   float* VY = (float*)a.vy + sp.lo;
   float* VZ = (float*)a.vz + sp.lo;
   const double* W = a.w + sp.lo;
-  const int32_t* TT = a.tet + sp.lo;
-  const uint32_t len = (uint32_t)(sp.hi - sp.lo);
+  int32_t* TT = a.tet + sp.lo;
+  const uint32_t len = (uint32_t)(sp.hi - sp.lo), lo32 = (uint32_t)sp.lo;
   for (uint32_t j = threadIdx.x; j < len; j += blockDim.x) {
     const uint32_t o4 = j * 4u;
     const int t = at_off<const int32_t>(TT, o4);
     if (t < 0) continue;
-    const int64_t i = sp.lo + j;
     const double w = at_off<const double>(W, j * 8u);
-    const long long qfx = fx_round(w * kFx);
     acc.n_before += 1;
-    acc.q_before += qfx;
+    acc.q_before += fx_round(w * kFx);
     float x = at_off<float>(X, o4), y = at_off<float>(Y, o4), z = at_off<float>(Z, o4);
     float vx = at_off<float>(VX, o4), vy = at_off<float>(VY, o4), vz = at_off<float>(VZ, o4);
     // FP32 gather, from the packed record rounded to FP32, or from the FP32
@@ -921,7 +927,7 @@ __device__ inline void push_role32(const StepArgs& a, const MapTable* M, int g,
     int32_t nd[4];
     if constexpr (PK) {
       R.load(m, t);
-      const lds_f q = (lds_f)M->m32 + R.mp;
+      const lds_f q = (lds_f) static_cast<const MapTable32*>(M)->m32 + R.mp;
 #pragma unroll
       for (int k = 0; k < 9; ++k) r[k] = q[k];
 #pragma unroll
@@ -989,7 +995,8 @@ __device__ inline void push_role32(const StepArgs& a, const MapTable* M, int g,
     at_off<float>(VX, o4) = vx;
     at_off<float>(VY, o4) = vy;
     at_off<float>(VZ, o4) = vz;
-    settle<PK>(m, M, a, i, x, y, z, sx, sy, t, R, w, qfx, acc, T, far, PK);
+    settle<PK>(m, M, a, &at_off<int32_t>(TT, o4), (int32_t)(lo32 + j), x, y, z, sx, sy, t, R,
+               w, acc, T, far, PK);
   }
 }
 
@@ -1061,7 +1068,6 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
     wrap(m, x, y, sx, sy);
     const int64_t i = base + s;
     const double w = a.s_face ? a.s_face[f] : 1.0;
-    const long long qfx = fx_round(w * kFx);
     if (a.f32) {
       // stored in FP32; the walk and deposition use the stored values
       const float xf = (float)x, yf = (float)y, zf = (float)z;
@@ -1086,11 +1092,11 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
     a.birth[i] = f;
     a.id[i] = (a.step << 42) | ((int64_t)f << 21) | o;
     acc.n_inj += 1;
-    acc.q_inj += qfx;
+    acc.q_inj += fx_round(w * kFx);
     const int h = m.e_tet[f];
     Geo<PK> H;
     H.load(m, h);
-    settle<PK>(m, M, a, i, x, y, z, sx, sy, h, H, w, qfx, acc, T, false);
+    settle<PK>(m, M, a, a.tet + i, (int32_t)i, x, y, z, sx, sy, h, H, w, acc, T, false);
   }
 }
 
@@ -1144,8 +1150,8 @@ __device__ inline void particles_body(const StepArgs& a, VB vb, bool wait) {
   __shared__ ChargeTable T;
   const MapTable* M = nullptr;
   if constexpr (PK) {
-    __shared__ MapTable maps;
-    maps_load(a.m, maps, F32);
+    __shared__ std::conditional_t<F32, MapTable32, MapTable> maps;
+    maps_load(a.m, maps);
     M = &maps;
   }
   table_clear(T);  // (synchronizes)
@@ -1158,31 +1164,38 @@ __device__ inline void particles_body(const StepArgs& a, VB vb, bool wait) {
   } else if (!wait || emit_wait(a)) {
     inject_role<PK>(a, M, vb.id - g_push, vb.n - g_push, acc, T);
   }
-  table_flush(T, a.charge);
+  table_flush(T, a.charge);  // (synchronizes)
+  if (threadIdx.x == 0) {
+    acc.n_anode = (int)T.n_anode;
+    acc.q_anode = (long long)T.q_anode;
+  }
   acc_flush(acc, a.acc_rows, vb.id, a.acc_stride);
 }
 
-// With the emission inside (e.defer), workgroup 0 only emits and the
-// particle workgroups are 1 .. gridDim.x - 1 (virtual index one less: the
-// XCD grouping of the slot spans is a fixed rotation of the hardware's).
-// At most 128 VGPRs (4 waves per SIMD): the FP64 push needs 142 unbounded
-// and spills 9 dwords per lane at this bound, which the fourth wave's latency
-// hiding more than pays for (86.6 against 90.4 us per push at 1e6
-// superparticles); the FP32 push fits in 124 either way.
-template <bool F32, bool PK>
-__global__ void __launch_bounds__(kBlock, 4) k_particles(StepArgs a, EmitArgs e) {
+// Workgroup 0 only emits (see emit_publish) and the particle workgroups are
+// 1 .. gridDim.x - 1 (virtual index one less: the XCD grouping of the slot
+// spans is a fixed rotation of the hardware's).
+// Bound: the load path and its latency (17 divergent 16-byte gathers per
+// superparticle on packed records), so waves in flight count.  On packed
+// records the push and the injection fit 96 registers without spills (maps
+// in LDS, integer seed clamps, 32-bit counters, absorption counted in LDS)
+// and five waves run per SIMD; only the emission of workgroup 0 spills then.
+// Full records need 122 registers: four waves.  Ten steps of 1e6
+// superparticles, re-sort included: 1098 us at four waves, 1067 at five; of
+// 1e4, where the emission is the longest chain: 508 at four, 557 at five.
+// So W = 5 only where the arrays have more slots than four waves have lanes
+// (a fifth could not hold a superparticle otherwise).
+template <bool F32, bool PK, int W>
+__global__ void __launch_bounds__(kBlock, W) k_particles(StepArgs a, EmitArgs e) {
   if (gate_closed(a.gate)) return;
-  if (!e.defer) {
-    particles_body<F32, PK>(a, VB{(int)blockIdx.x, (int)gridDim.x}, false);
-  } else if (blockIdx.x == 0) {
+  if (blockIdx.x == 0)
     emit_publish(e);
-  } else {
+  else
     particles_body<F32, PK>(a, VB{(int)blockIdx.x - 1, (int)gridDim.x - 1}, true);
-  }
 }
 
 template <bool F32, bool PK>
-__global__ void __launch_bounds__(kBlock) k_particles_b(const StepArgs* A,
+__global__ void __launch_bounds__(kBlock, PK ? 4 : 3) k_particles_b(const StepArgs* A,
                                                         BatchMap map) {
   int i;
   const VB vb = batch_block(map, i);
@@ -1275,7 +1288,7 @@ __global__ void __launch_bounds__(kBlock) k_locate(LocateArgs a) {
   const MapTable* M = nullptr;
   if constexpr (PK) {
     __shared__ MapTable maps;
-    maps_load(m, maps, false);
+    maps_load(m, maps);
     M = &maps;
     __syncthreads();
   }
@@ -1388,28 +1401,27 @@ hipError_t launch_stats_b(const StepArgs* A, const BatchMap& map, int grid,
   hipLaunchKernelGGL(k_stats_b, dim3(grid), dim3(kBlock), 0, s, A, map);
   return hipGetLastError();
 }
-int particle_blocks_per_cu(int f32, int packed) {
+using ParticlesKernel = void (*)(StepArgs, EmitArgs);
+
+static ParticlesKernel particles_kernel(int f32, int packed, int waves) {
+  if (!packed) return f32 ? k_particles<true, false, 4> : k_particles<false, false, 4>;
+  if (waves == 5) return f32 ? k_particles<true, true, 5> : k_particles<false, true, 5>;
+  return f32 ? k_particles<true, true, 4> : k_particles<false, true, 4>;
+}
+
+int particle_blocks_per_cu(int f32, int packed, int waves) {
   int n = 0;
-  const auto kern = packed ? (f32 ? k_particles<true, true> : k_particles<false, true>)
-                           : (f32 ? k_particles<true, false> : k_particles<false, false>);
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, kBlock, 0);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &n, particles_kernel(f32, packed, waves), kBlock, 0);
   return e == hipSuccess ? n : 0;
 }
 
-hipError_t launch_particles(const StepArgs& a, const EmitArgs* e, int g_push,
-                            int g_inj, hipStream_t s) {
+hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
+                            int g_inj, int waves, hipStream_t s) {
   StepArgs b = a;
   b.g_push = g_push;
-  EmitArgs ee;
-  if (e) {
-    ee = *e;
-  } else {
-    ee = EmitArgs{};
-  }
-  const int grid = g_push + g_inj + (ee.defer ? 1 : 0);
-  const auto kern = a.m.tc ? (a.f32 ? k_particles<true, true> : k_particles<false, true>)
-                           : (a.f32 ? k_particles<true, false> : k_particles<false, false>);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, b, ee);
+  hipLaunchKernelGGL(particles_kernel(a.f32, a.m.tc != nullptr, waves),
+                     dim3(g_push + g_inj + 1), dim3(kBlock), 0, s, b, e);
   return hipGetLastError();
 }
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s) {
