@@ -129,6 +129,13 @@ struct DevMesh {
   const int32_t* k_sptr;   // [k_nslices + 1] slice offsets
   const int32_t* k_ncol;   // columns as node ids
   const double* k_sval;
+  // the same pass packed as in SellView: one word per entry (node id and
+  // code) and a table of the distinct (K, R_x, R_y, R_z), FP64 and with R
+  // rounded to FP32 (then widened); where these exist, k_sval, r_sval and
+  // r_sval32 do not
+  const uint32_t* kr_code;
+  const double* kr_dict;     // [kDictMax][4]
+  const double* kr_dict32;
   // K without its exact zeros, free-index columns (see SellView)
   SellView kz;
   const double* r_sval;    // [3][k_np] R on the free rows

@@ -580,6 +580,39 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
       }
     }
   }
+  // K and R together, packed where the node ids and the distinct quadruples
+  // fit (26 on the free rows of the lattice tips)
+  std::vector<uint32_t> kr_code;
+  std::vector<double> kr_dict;
+  if (N <= (1 << kColBits)) {
+    kr_dict.assign(4 * kDictMax, 0.0);
+    kr_code.assign(std::max<int64_t>(k_np, 1), 0);
+    std::unordered_map<uint64_t, std::vector<uint32_t>> seen;
+    uint32_t n = 0, last = 0;
+    for (int64_t q = 0; q < k_np; ++q) {
+      const double v[4] = {k_sval[q], r_sval[q], r_sval[k_np + q], r_sval[2 * k_np + q]};
+      uint32_t c = last;
+      if (n == 0 || std::memcmp(&kr_dict[4 * last], v, sizeof v) != 0) {
+        uint64_t b[4];
+        std::memcpy(b, v, sizeof v);
+        auto& list = seen[b[0] * 3 ^ b[1] * 5 ^ b[2] * 7 ^ b[3] * 11];
+        c = kDictMax;
+        for (uint32_t k : list)
+          if (std::memcmp(&kr_dict[4 * k], v, sizeof v) == 0) c = k;
+        if (c == (uint32_t)kDictMax) {
+          if (n == (uint32_t)kDictMax) {
+            kr_code.clear();
+            break;
+          }
+          c = n++;
+          std::memcpy(&kr_dict[4 * c], v, sizeof v);
+          list.push_back(c);
+        }
+      }
+      last = c;
+      kr_code[q] = (uint32_t)k_ncol[q] | (c << kColBits);
+    }
+  }
   // 6. Neumann load per unit E0 on the top plane
   for (int64_t t = 0; t < T; ++t)
     for (int f = 0; f < 4; ++f) {
@@ -760,15 +793,24 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
       M.kz.val = upload(h, z_val, err);
       M.kz.val32 = upload(h, z_val32, err);
     }
-    std::vector<float> r_sval32(r_sval.begin(), r_sval.end());
     std::vector<float> d_sval32(d_sval.begin(), d_sval.end());
     M.k_nslices = (int64_t)k_sptr.size() - 1;
     M.k_np = k_np;
     M.k_sptr = upload(h, k_sptr, err);
     M.k_ncol = upload(h, k_ncol, err);
-    M.k_sval = upload(h, k_sval, err);
-    M.r_sval = upload(h, r_sval, err);
-    M.r_sval32 = upload(h, r_sval32, err);
+    if (!kr_code.empty()) {
+      std::vector<double> kr_dict32(kr_dict);
+      for (size_t k = 0; k < kr_dict32.size(); ++k)
+        if (k % 4) kr_dict32[k] = (double)(float)kr_dict32[k];
+      M.kr_code = upload(h, kr_code, err);
+      M.kr_dict = upload(h, kr_dict, err);
+      M.kr_dict32 = upload(h, kr_dict32, err);
+    } else {
+      const std::vector<float> r_sval32(r_sval.begin(), r_sval.end());
+      M.k_sval = upload(h, k_sval, err);
+      M.r_sval = upload(h, r_sval, err);
+      M.r_sval32 = upload(h, r_sval32, err);
+    }
     M.d_nslices = (int64_t)d_sptr.size() - 1;
     M.d_np = d_np;
     M.d_sptr = upload(h, d_sptr, err);

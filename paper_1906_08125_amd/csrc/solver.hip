@@ -239,6 +239,8 @@ __device__ inline void report(const CgCtrl* c, CgReport* r, int64_t seq,
 
 // The pass over phi (see the file comment).  reset != 0 starts a new solve
 // (control word cleared by workgroup 0; no other workgroup reads it here).
+// Bound: the matrix bytes, 36 per entry plain (77 us on the production tip,
+// 278 MB of them) and 4 packed (33 us).
 // FP32 field (e32): E = R phi in the difference form
 //   E_i = sum_j R_ij (phi_j - phi_i) + S_i phi_i,   S_i = sum_j R_ij (FP64),
 // with R in FP32: the differences are of the size of E h, so rounding R
@@ -264,6 +266,13 @@ __device__ inline void k_cg_resfield_body(const CgArgs& a, int reset, VB vb,
   const bool e32 = a.e32 != 0;
   const int64_t np = m.k_np;
   double v[2] = {0.0, 0.0};
+  // packed: the table of (K, R) quadruples in LDS
+  __shared__ double quad[4 * kDictMax];
+  if (m.kr_code) {
+    const double* __restrict__ gd = e32 ? m.kr_dict32 : m.kr_dict;
+    for (int k = threadIdx.x; k < 4 * kDictMax; k += blockDim.x) quad[k] = gd[k];
+    __syncthreads();
+  }
   {
     const Range sl = my_range(m.k_nslices, vb);
     for (int64_t s = sl.lo + sub; s < sl.hi; s += nsub) {
@@ -276,7 +285,32 @@ __device__ inline void k_cg_resfield_body(const CgArgs& a, int reset, VB vb,
       // four entries per trip where the slice allows (uniform across the
       // wave): their loads are in flight together; sums in entry order
       int32_t p = p0 + lane;
-      if (!withE) {
+      if (m.kr_code) {
+        // eight entries per trip; the sums as below, in entry order
+        for (; p < p1; p += 8 * kSell) {
+          const int32_t left = p1 - (p - lane);
+          uint32_t c[8];
+          double xj[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (u * kSell < left) c[u] = m.kr_code[p + u * kSell];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (u * kSell < left) xj[u] = a.phi[c[u] & ((1u << kColBits) - 1)];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (u * kSell < left) {
+              const double* t = quad + 4 * (c[u] >> kColBits);
+              kx += t[0] * xj[u];
+              if (withE) {
+                const double d = e32 ? xj[u] - pi : xj[u];
+                ex += t[1] * d;
+                ey += t[2] * d;
+                ez += t[3] * d;
+              }
+            }
+        }
+      } else if (!withE) {
         for (; p + 3 * kSell < p1; p += 4 * kSell) {
           int32_t c[4];
           double kv[4], xj[4];
