@@ -380,12 +380,12 @@ __global__ void __launch_bounds__(kThreads) k_cut_rank(ChargeArgs a) {
 // left out and each row's x extent cut to what sqrt(R2) can reach (both
 // valid for any point of cell c).  Run s = 4 lane + u; the runs' starts
 // and prefix sums go to this wave's LDS table.  Every member position p
-// (runs in order) is passed to f(p, valid): consecutive lanes take
-// consecutive members (coalesced loads), four per lane and trip; lanes
-// past the end get p = 0 with valid false (f loads unconditionally and
-// only drops the contribution, so the four loads go out together).  Each
-// lane sees its own members (every lane calls f); the caller reduces over
-// the wave.
+// (runs in order) is passed to f(p, valid, end): consecutive lanes take
+// consecutive members (coalesced loads), four per lane and trip (end: the
+// last trip); lanes past the end get p = 0 with valid false (f loads
+// unconditionally and only drops the contribution, so the four loads go out
+// together).  Each lane sees its own members (every lane calls f); the caller
+// reduces over the wave.
 constexpr int kCutKMax = 5;
 constexpr int kSegMax = 4 * 64;
 
@@ -457,6 +457,7 @@ __device__ inline void wave_block_members(const ChargeArgs& a, const int32_t* cn
   wave_sync();
   for (int32_t c0 = 0; c0 < T; c0 += 256) {
     const int32_t cl = c0 + lane;
+    const bool end = c0 + 256 >= T;
     int32_t p[4];
     bool v[4];
 #pragma unroll
@@ -470,7 +471,7 @@ __device__ inline void wave_block_members(const ChargeArgs& a, const int32_t* cn
         if (s_pre[sg + step] <= cc) sg += step;
       p[u] = v[u] ? s_lo[sg] + (cc - s_pre[sg]) : 0;
     }
-    f(p, v);
+    f(p, v, end);
   }
   wave_sync();
 }
@@ -486,20 +487,19 @@ __device__ inline void load4(const double* xyz, const int32_t (&p)[4], double (&
   }
 }
 
-// Kept pairs queued per wave: about half of the candidates pass the screen,
+// Kept pairs stacked per wave: about half of the candidates pass the screen,
 // and a lane whose candidate does not would wait through the other lanes'
-// root, exponential and divisions, so those are taken 64 queued pairs at a
-// time.  heavy(d2, p) is called with every lane that has a pair.  The charge
-// of a 48^2 x 96 tip's faces and atoms (seven launches): 97 us with each lane
-// taking its own pairs and workgroup barriers, 89 so.
-constexpr int kQueue = 128;
-struct PairQueue {
-  double d2[kQueue];
-  int32_t p[kQueue];
+// root, exponential and divisions, so those are taken 64 stacked pairs at a
+// time.  heavy(d2, p) is called with every lane that has a pair, at one place
+// per walk: its code is long, and a first call fetches it from memory.  The
+// charge of a 48^2 x 96 tip's faces and atoms (eight launches): 97 us with
+// each lane taking its own pairs and workgroup barriers, 89 so.
+constexpr int kStack = 64 + 256;  // what a trip left and what it adds
+struct PairStack {
+  double d2[kStack];
+  int32_t p[kStack];
 };
-template <typename H>
-__device__ inline void queue_pair(PairQueue& q, int& n, bool keep, double d2, int32_t p,
-                                  H&& heavy) {
+__device__ inline void stack_push(PairStack& q, int& n, bool keep, double d2, int32_t p) {
   const int lane = threadIdx.x & 63;
   const uint64_t m = __ballot(keep);
   if (keep) {
@@ -508,24 +508,18 @@ __device__ inline void queue_pair(PairQueue& q, int& n, bool keep, double d2, in
     q.p[k] = p;
   }
   n += __popcll(m);
-  if (n >= 64) {
-    wave_sync();
-    heavy(q.d2[lane], q.p[lane]);
-    n -= 64;
-    const double d = q.d2[64 + lane];
-    const int32_t pp = q.p[64 + lane];
-    wave_sync();
-    if (lane < n) {
-      q.d2[lane] = d;
-      q.p[lane] = pp;
-    }
-  }
 }
+// Takes pairs off the top until fewer than `leave` are left.
 template <typename H>
-__device__ inline void queue_rest(PairQueue& q, int n, H&& heavy) {
+__device__ inline void stack_take(PairStack& q, int& n, int leave, H&& heavy) {
   const int lane = threadIdx.x & 63;
   wave_sync();
-  if (lane < n) heavy(q.d2[lane], q.p[lane]);
+  while (n >= leave) {
+    const int k = n < 64 ? n : 64;
+    n -= k;
+    if (lane < k) heavy(q.d2[n + lane], q.p[n + lane]);
+  }
+  wave_sync();
 }
 
 // Squared minimum-image distance in the order dist_mi sums it (its root is
@@ -554,7 +548,7 @@ constexpr double kScreen = 1.0 + 1e-12;
 __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
   __shared__ int32_t s_lo[kThreads / 64][kSegMax];
   __shared__ int32_t s_pre[kThreads / 64][kSegMax + 1];
-  __shared__ PairQueue s_q[kThreads / 64];
+  __shared__ PairStack s_q[kThreads / 64];
   const DevMesh& m = a.m;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t pf = blockIdx.x * (int64_t)(blockDim.x >> 6) + wv;
@@ -564,7 +558,7 @@ __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
   const double* ax = a.a_xyz;
   double m2 = 1.0 / 0.0;
   wave_block_members(a, a.a_cnt, cc, 1, 1.0 / 0.0, s_lo[wv], s_pre[wv],
-                     [&](const int32_t (&p)[4], const bool (&v)[4]) {
+                     [&](const int32_t (&p)[4], const bool (&v)[4], bool) {
                        double x[4], y[4], z[4];
                        load4(ax, p, x, y, z);
 #pragma unroll
@@ -595,16 +589,16 @@ __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
       if (t <= cut) S += exp(-t / a.r_c);
     };
     wave_block_members(a, a.a_cnt, cc, a.K, b2, s_lo[wv], s_pre[wv],
-                       [&](const int32_t (&p)[4], const bool (&v)[4]) {
+                       [&](const int32_t (&p)[4], const bool (&v)[4], bool end) {
                          double x[4], y[4], z[4];
                          load4(ax, p, x, y, z);
 #pragma unroll
                          for (int u = 0; u < 4; ++u) {
                            const double d2 = dist2_mi(m, cx, cy, cz, x[u], y[u], z[u]);
-                           queue_pair(s_q[wv], n, v[u] && d2 <= b2, d2, p[u], heavy);
+                           stack_push(s_q[wv], n, v[u] && d2 <= b2, d2, p[u]);
                          }
+                         stack_take(s_q[wv], n, end ? 1 : 64, heavy);
                        });
-    queue_rest(s_q[wv], n, heavy);
   } else {
     const double3 c = make_double3(cx, cy, cz);
     for (int64_t j = lane; j < a.n_atoms; j += 64) {
@@ -629,7 +623,7 @@ __global__ void __launch_bounds__(kThreads) k_face_charge_cut(ChargeArgs a) {
 __global__ void __launch_bounds__(kThreads) k_atom_charge_cut(ChargeArgs a) {
   __shared__ int32_t s_lo[kThreads / 64][kSegMax];
   __shared__ int32_t s_pre[kThreads / 64][kSegMax + 1];
-  __shared__ PairQueue s_q[kThreads / 64];
+  __shared__ PairStack s_q[kThreads / 64];
   const bool any_far = *a.n_far != 0;
   const DevMesh& m = a.m;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -647,7 +641,7 @@ __global__ void __launch_bounds__(kThreads) k_atom_charge_cut(ChargeArgs a) {
       if (t <= cut) q += (a.f_Q_s[g] * exp(-t / a.r_c)) / a.f_sum_s[g];
     };
     wave_block_members(a, a.f_cnt, cc, a.K, R * R, s_lo[wv], s_pre[wv],
-                       [&](const int32_t (&p)[4], const bool (&v)[4]) {
+                       [&](const int32_t (&p)[4], const bool (&v)[4], bool end) {
                          double x[4], y[4], z[4], fm[4];
                          load4(a.f_cen, p, x, y, z);
 #pragma unroll
@@ -657,10 +651,10 @@ __global__ void __launch_bounds__(kThreads) k_atom_charge_cut(ChargeArgs a) {
                            const double d2 =
                                dist2_mi(m, x[u], y[u], z[u], at[0], at[1], at[2]);
                            const double bd = (fm[u] + cut) * kScreen;
-                           queue_pair(s_q[wv], n, v[u] && d2 <= bd * bd, d2, p[u], heavy);
+                           stack_push(s_q[wv], n, v[u] && d2 <= bd * bd, d2, p[u]);
                          }
+                         stack_take(s_q[wv], n, end ? 1 : 64, heavy);
                        });
-    queue_rest(s_q[wv], n, heavy);
   } else {
     for (int64_t g = lane; g < m.n_emit; g += 64) {
       const double3 fc = make_double3(a.f_cen[3 * g], a.f_cen[3 * g + 1], a.f_cen[3 * g + 2]);
