@@ -107,6 +107,7 @@ fp::SortArgs sort_args(pic_mesh* h, const pic_particles* P, int real_bytes) {
   a.s_id = (int64_t*)take((size_t)cap * 8);
   a.hist = (uint32_t*)take((size_t)fp::kSortBins * fp::sort_tiles(cap) * 4);
   a.total = (uint32_t*)take((size_t)fp::kSortBins * 4);
+  a.ntiles = fp::sort_tiles(cap);
   return a;
 }
 
@@ -1168,7 +1169,7 @@ pic_status pic_step(pic_mesh* h, const pic_particles* P, const pic_fields* F,
       prof_begin(h, PIC_K_SORT, s);
       fp::SortArgs sa = alternate ? sort_from_current() : base_sort;
       sa.stats = st;
-      if ((e = fp::sort_particles(sa, P->capacity, h->n_cu, s, !alternate)) != hipSuccess)
+      if ((e = fp::sort_particles(sa, h->n_cu, s, !alternate)) != hipSuccess)
         return hip_fail(e, "pic_step sort");
       if (alternate) on_scratch ^= 1;
       prof_end(h, s);
@@ -1536,9 +1537,10 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
                                    f32 ? 4 : 8);
     if (e != hipSuccess) return hip_fail(e, "pic_batch_step");
   }
-  // per-step argument arrays: [k][i] StepArgs, EmitArgs, CgArgs
-  const size_t sa = sizeof(fp::StepArgs), se = sizeof(fp::EmitArgs), sg = sizeof(fp::CgArgs);
-  const size_t per = (size_t)n * (sa + se + sg);
+  // per-step argument arrays: [k][i] StepArgs, EmitArgs, CgArgs, SortArgs
+  const size_t sa = sizeof(fp::StepArgs), se = sizeof(fp::EmitArgs), sg = sizeof(fp::CgArgs),
+               so = sizeof(fp::SortArgs);
+  const size_t per = (size_t)n * (sa + se + sg + so);
   const size_t need = per * (size_t)n_steps;
   hipError_t e = hipEventSynchronize(b->uploaded);  // staging free again
   if (e != hipSuccess) return hip_fail(e, "pic_batch_step");
@@ -1578,6 +1580,10 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       std::memcpy(base + sa * i, &a, sa);
       std::memcpy(base + sa * n + se * i, &ea, se);
       std::memcpy(base + (sa + se) * n + sg * i, &ca, sg);
+      fp::SortArgs oa = prm[i].resort_every > 0 ? sort_args(b->h[i], &P[i], f32 ? 4 : 8)
+                                                : fp::SortArgs{};
+      oa.stats = st;
+      std::memcpy(base + (sa + se + sg) * n + so * i, &oa, so);
     }
   }
   if ((e = hipMemcpyAsync(b->d_args, b->h_args, need, hipMemcpyHostToDevice, s)) != hipSuccess)
@@ -1753,25 +1759,28 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
     for (int i = 0; i < n; ++i)
       b->h[i]->step_spec = (int)std::min<int64_t>(b->h[i]->cg_report_host->iters, 256);
     prof_end(h0, s);
+    // the re-sorts due, in shared launches, then their collisions
+    std::vector<char> due(n, 0);
+    std::vector<const fp::SortArgs*> hs(n);
     for (int i = 0; i < n; ++i) {
-      const int64_t step = prm[i].step0 + k;
-      if (prm[i].resort_every > 0 && (step + 1) % prm[i].resort_every == 0) {
-        prof_begin(h0, PIC_K_SORT, s);
-        fp::SortArgs sa2 = sort_args(b->h[i], &P[i], f32 ? 4 : 8);
-        sa2.stats = stats + (size_t)k * n + i;
-        if ((e = fp::sort_particles(sa2, P[i].capacity, b->h[i]->n_cu, s)) != hipSuccess)
-          return hip_fail(e, "pic_batch_step sort");
-        prof_end(h0, s);
-        if (prm[i].collide) {
-          prof_begin(h0, PIC_K_COLLIDE, s);
-          const fp::CollideArgs cl = collide_args(
-              b->h[i], &P[i], prm[i].dt * prm[i].resort_every, prm[i].w_sp,
-              prm[i].seed, step, prm[i].instance);
-          if ((e = fp::collide_particles(cl, b->h[i]->n_cu, s)) != hipSuccess)
-            return hip_fail(e, "pic_batch_step collide");
-          prof_end(h0, s);
-        }
-      }
+      due[i] = prm[i].resort_every > 0 && (prm[i].step0 + k + 1) % prm[i].resort_every == 0;
+      hs[i] = (const fp::SortArgs*)(hb + per * k + (sa + se + sg) * n + so * i);
+    }
+    if (std::find(due.begin(), due.end(), 1) == due.end()) continue;
+    prof_begin(h0, PIC_K_SORT, s);
+    if ((e = fp::sort_particles_b((const fp::SortArgs*)(base + (sa + se + sg) * n), hs, due,
+                                  h0->n_cu, s)) != hipSuccess)
+      return hip_fail(e, "pic_batch_step sort");
+    prof_end(h0, s);
+    for (int i = 0; i < n; ++i) {
+      if (!due[i] || !prm[i].collide) continue;
+      prof_begin(h0, PIC_K_COLLIDE, s);
+      const fp::CollideArgs cl = collide_args(
+          b->h[i], &P[i], prm[i].dt * prm[i].resort_every, prm[i].w_sp, prm[i].seed,
+          prm[i].step0 + k, prm[i].instance);
+      if ((e = fp::collide_particles(cl, b->h[i]->n_cu, s)) != hipSuccess)
+        return hip_fail(e, "pic_batch_step collide");
+      prof_end(h0, s);
     }
   }
   return PIC_OK;

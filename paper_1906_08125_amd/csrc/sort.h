@@ -1,5 +1,7 @@
 // Launch interface of the particle re-sort (by tet, with compaction).
 #pragma once
+#include <vector>
+
 #include "common.h"
 
 namespace fp {
@@ -11,6 +13,7 @@ struct SortArgs {
   int64_t n_tets;
   int32_t* n_slots;       // in: slots in use, out: live particles
   int32_t* n_live;        // scratch scalar
+  int ntiles;             // sort_tiles(capacity)
   pic_step_stats* stats;  // or null
   // particle arrays (x, y, z, vx, vy, vz of real_bytes each)
   void* real[6];
@@ -35,10 +38,16 @@ struct SortArgs {
 // from (real, w, ...); else they stay in the scratch arrays (s_real, s_w,
 // ...), which the caller then uses as the particle arrays, and only the
 // slot count is set.
-hipError_t sort_particles(const SortArgs& a, int64_t capacity, int n_cu,
-                          hipStream_t s, bool copyback = true);
+hipError_t sort_particles(const SortArgs& a, int n_cu, hipStream_t s,
+                          bool copyback = true);
 // the s_* arrays copied into real, w, ... for the *n_slots slots in use
 hipError_t copy_particles(const SortArgs& a, int n_cu, hipStream_t s);
+// The re-sorts (with the copy back) of the instances due[i] of a batch of one
+// precision, in shared launches; A: their arguments on the device, host: the
+// same on the host.  Ten steps of six tips with one re-sort each: 1959 us with
+// 66 launches of the re-sorts one after another, 1529 so.
+hipError_t sort_particles_b(const SortArgs* A, const std::vector<const SortArgs*>& host,
+                            const std::vector<char>& due, int n_cu, hipStream_t s);
 size_t sort_scratch_bytes(int64_t capacity, int real_bytes);
 int sort_tiles(int64_t capacity);
 
