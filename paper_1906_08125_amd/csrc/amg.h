@@ -51,6 +51,13 @@ struct AmgLevel {
   const float* invdiag32;
   float *b32, *t32;
 };
+__device__ inline void globalize(AmgLevel& a, const AmgLevel& from) {
+  globalize(a.A.v, from.A.v);
+  globalize(a.Ps.v, from.Ps.v);
+  globalize(a.Rs.v, from.Rs.v);
+  FP_GLOBAL(invdiag); FP_GLOBAL(b); FP_GLOBAL(t); FP_GLOBAL(invdiag32); FP_GLOBAL(b32);
+  FP_GLOBAL(t32);
+}
 
 struct AmgDev {
   int n_levels;   // levels with a smoother; the dense coarsest level follows

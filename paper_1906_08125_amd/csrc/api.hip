@@ -1129,7 +1129,6 @@ pic_status pic_step(pic_mesh* h, const pic_particles* P, const pic_fields* F,
     ak.step = ek.step = prm->step0 + k;
     ak.stats = ek.stats = stats + k;
     ak.gate = ek.gate = gate;
-    ek.defer = 1;  // the emission runs inside the particle kernel
     *prof0 = h->ev_class.size();
     hipError_t e;
     // the first step of a call clears the charges and counters itself;
@@ -1439,7 +1438,7 @@ fp::BatchMap batch_map(const std::vector<int>& counts,
   int j = 0;
   for (size_t i = 0; i < counts.size(); ++i) {
     if (!active.empty() && !active[i]) continue;
-    m.inst[j] = (int8_t)i;
+    m.inst[j] = (int32_t)i;
     m.off[j + 1] = m.off[j] + counts[i];
     ++j;
   }
@@ -1496,7 +1495,7 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
   if (n_steps == 0) return PIC_OK;
   const int n = (int)b->h.size();
   const bool f32 = P[0].precision == PIC_MIXED;
-  std::vector<int> c_push(n), c_inj(n), c_cg(n), c_clear(n), c_fb(n), c_stats(n, 16);
+  std::vector<int> c_push(n), c_inj(n), c_cg(n), c_clear(n), c_fb(n);
   const int fb = round8(std::max(sc->fallback_blocks, 8));
   for (int i = 0; i < n; ++i) {
     pic_mesh* h = b->h[i];
@@ -1573,6 +1572,19 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       ea.stats = st;
       fp::CgArgs ca = ss.ca;
       ca.step_stats = st;
+      ca.acc_rows = b->h[i]->acc_rows;
+      ca.acc_n = ss.a.acc_stride;
+      // the particle kernels of a step after the first may be enqueued before
+      // the solve ahead of them has ended (see below); its last kernel starts
+      // the next step
+      if (k > 0) a.gate = ea.gate = &ss.ca.ctrl->state;
+      if (k + 1 < n_steps) {
+        ca.next_stats = st + n;
+        ca.next_scratch = b->h[i]->scratch;
+        ca.n_slots = P[i].n_slots;
+        ca.clear_charge = F[i].charge;
+        ca.n_clear = b->h[i]->dm.n_nodes;
+      }
       // as in pic_step: the field and the true residual of the previous
       // solve still hold, so the first pass needs no product with K or R
       ca.keep_field = k > 0 ? 1 : 0;
@@ -1591,44 +1603,77 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
   if ((e = hipEventRecord(b->uploaded, s)) != hipSuccess) return hip_fail(e, "pic_batch_step");
   std::vector<int> c_part(n);
   for (int i = 0; i < n; ++i) c_part[i] = c_push[i] + c_inj[i];
-  // the particle launches: instances without packed tet records, then those
-  // that have them
-  std::vector<char> has_pk(n), no_pk(n);
-  for (int i = 0; i < n; ++i) {
-    has_pk[i] = b->h[i]->dm.tc != nullptr;
-    no_pk[i] = !has_pk[i];
-  }
-  const fp::BatchMap m_part[2] = {batch_map(c_part, no_pk), batch_map(c_part, has_pk)};
-  const fp::BatchMap m_clear = batch_map(c_clear), m_fb = batch_map(c_fb), m_stats = batch_map(c_stats),
-                     m_cg = batch_map(c_cg);
-  const int g_clear = m_clear.off[n], g_fb = m_fb.off[n],
-            g_stats = m_stats.off[n], g_cg = m_cg.off[n];
-  (void)g_cg;
+  const fp::BatchMap m_clear = batch_map(c_clear), m_cg = batch_map(c_cg);
   pic_mesh* h0 = b->h[0];
-  for (int32_t k = 0; k < n_steps; ++k) {
+  // The particle kernels of step k for the instances in on: those without
+  // packed tet records, then those that have them; then the exact fallback.
+  // (The counter rows are summed by the first pass of the step's solve.)
+  auto particles = [&](int32_t k, const std::vector<char>& on) {
     char* base = (char*)b->d_args + per * k;
     const fp::StepArgs* A = (const fp::StepArgs*)base;
     const fp::EmitArgs* E = (const fp::EmitArgs*)(base + sa * n);
+    hipError_t r;
+    bool any = false;
+    for (int pk = 0; pk < 2; ++pk) {
+      std::vector<char> sel(n);
+      for (int i = 0; i < n; ++i) sel[i] = on[i] && (b->h[i]->dm.tc != nullptr) == (pk == 1);
+      const fp::BatchMap m = batch_map(c_part, sel);
+      if (m.n_seg == 0) continue;
+      any = true;
+      prof_begin(h0, PIC_K_PUSH, s);
+      if ((r = fp::launch_particles_b(A, E, m, f32 ? 1 : 0, pk, s)) != hipSuccess) return r;
+      prof_end(h0, s);
+    }
+    if (!any) return hipSuccess;
+    const fp::BatchMap m = batch_map(c_fb, on);
+    prof_begin(h0, PIC_K_FALLBACK, s);
+    if ((r = fp::launch_fallback_b(A, m, m.off[m.n_seg], s)) != hipSuccess) return r;
+    prof_end(h0, s);
+    return hipSuccess;
+  };
+  std::vector<char> todo(n, 1);
+  for (int32_t k = 0; k < n_steps; ++k) {
+    char* base = (char*)b->d_args + per * k;
+    if (k == 0) {
+      prof_begin(h0, PIC_K_EMIT, s);
+      if ((e = fp::launch_begin_b((const fp::EmitArgs*)(base + sa * n), m_clear,
+                                  m_clear.off[n], s)) != hipSuccess)
+        return hip_fail(e, "pic_batch_step begin");
+      prof_end(h0, s);
+    }
+    // (the instances whose kernels were not let through, see ahead)
+    if ((e = particles(k, todo)) != hipSuccess)
+      return hip_fail(e, "pic_batch_step particles");
+    // the re-sorts due, in shared launches, then their collisions: before
+    // the solves (which touch the charge alone), so that the next step's
+    // kernels can follow those directly
+    std::vector<char> due(n, 0);
+    std::vector<const fp::SortArgs*> hs(n);
+    for (int i = 0; i < n; ++i) {
+      due[i] = prm[i].resort_every > 0 && (prm[i].step0 + k + 1) % prm[i].resort_every == 0;
+      hs[i] = (const fp::SortArgs*)(hb + per * k + (sa + se + sg) * n + so * i);
+    }
+    if (std::find(due.begin(), due.end(), 1) != due.end()) {
+      prof_begin(h0, PIC_K_SORT, s);
+      if ((e = fp::sort_particles_b((const fp::SortArgs*)(base + (sa + se + sg) * n), hs, due,
+                                    h0->n_cu, s)) != hipSuccess)
+        return hip_fail(e, "pic_batch_step sort");
+      prof_end(h0, s);
+    }
+    for (int i = 0; i < n; ++i) {
+      if (!due[i] || !prm[i].collide) continue;
+      prof_begin(h0, PIC_K_COLLIDE, s);
+      const fp::CollideArgs cl = collide_args(
+          b->h[i], &P[i], prm[i].dt * prm[i].resort_every, prm[i].w_sp, prm[i].seed,
+          prm[i].step0 + k, prm[i].instance);
+      if ((e = fp::collide_particles(cl, b->h[i]->n_cu, s)) != hipSuccess)
+        return hip_fail(e, "pic_batch_step collide");
+      prof_end(h0, s);
+    }
     fp::CgBatch cb;
     cb.args = (const fp::CgArgs*)(base + (sa + se) * n);
     cb.map = m_cg;
     cb.mask = 0;
-    prof_begin(h0, PIC_K_EMIT, s);
-    if ((e = fp::launch_begin_b(E, m_clear, g_clear, s)) != hipSuccess)
-      return hip_fail(e, "pic_batch_step begin");
-    prof_end(h0, s);
-    prof_begin(h0, PIC_K_PUSH, s);
-    for (int pk = 0; pk < 2; ++pk)
-      if (m_part[pk].n_seg > 0 &&
-          (e = fp::launch_particles_b(A, m_part[pk], m_part[pk].off[m_part[pk].n_seg],
-                                      f32 ? 1 : 0, pk, s)) != hipSuccess)
-        return hip_fail(e, "pic_batch_step particles");
-    prof_end(h0, s);
-    prof_begin(h0, PIC_K_FALLBACK, s);
-    if ((e = fp::launch_fallback_b(A, m_fb, g_fb, s)) != hipSuccess ||
-        (e = fp::launch_stats_b(A, m_stats, g_stats, s)) != hipSuccess)
-      return hip_fail(e, "pic_batch_step fallback");
-    prof_end(h0, s);
     // the solves of all instances, in shared launches: the first round
     // speculates as many iterations as the previous step needed; later
     // rounds launch only the instances still iterating
@@ -1728,11 +1773,29 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       ca.mask = 0;
       return fp::cg_batch_recheck_if(ca, ca.map.off[ca.map.n_seg], s);
     };
-    if ((e = fp::cg_batch_begin(cb, m_cg.off[m_cg.n_seg], k > 0 ? 1 : 0, s)) != hipSuccess ||
-        (spec > 0 && (e = iterate(spec_on, 0, 0, 0, &spec_n)) != hipSuccess) ||
-        (e = fp::cg_batch_report(cb, n, seq, s)) != hipSuccess ||
-        (e = batch_wait(b, seq, s)) != hipSuccess)
+    if ((e = fp::cg_batch_begin(cb, m_cg.off[m_cg.n_seg], k > 0 ? 1 : 0, spec > 0 ? 0 : seq,
+                                s)) != hipSuccess ||
+        (spec > 0 && ((e = iterate(spec_on, 0, 0, 0, &spec_n)) != hipSuccess ||
+                      (e = fp::cg_batch_report(cb, n, seq, s)) != hipSuccess)))
       return hip_fail(e, "pic_batch_step solve");
+    prof_end(h0, s);
+    // Ahead: the next step's particle kernels follow the first report; those
+    // of an instance whose solve goes on do nothing (StepArgs::gate) and are
+    // launched again with the next step.  Without them the GPU waits for the
+    // host in every step.  (Ten steps of six tips with one re-sort, 1529 us
+    // when each step began with launches of its own for clears, emission,
+    // counters and reports: 1190 with those in the particle and solver
+    // kernels, as in pic_step, and the launches ahead.)
+    const std::vector<char> all(n, 1);
+    if (k + 1 < n_steps && (e = particles(k + 1, all)) != hipSuccess)
+      return hip_fail(e, "pic_batch_step particles");
+    prof_begin(h0, PIC_K_SOLVE, s);
+    if ((e = batch_wait(b, seq, s)) != hipSuccess)
+      return hip_fail(e, "pic_batch_step solve");
+    for (int i = 0; i < n; ++i) {
+      const int32_t st = b->h[i]->cg_report_host->state;
+      todo[i] = st != fp::CG_DONE && st != fp::CG_NOCONV;
+    }
     // later rounds: Jacobi 8, 16, 32, ... iterations; AMG (an iteration past
     // the stop costs as much as a working one) 1, 2, 4 after a speculated
     // round, else 4
@@ -1759,29 +1822,6 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
     for (int i = 0; i < n; ++i)
       b->h[i]->step_spec = (int)std::min<int64_t>(b->h[i]->cg_report_host->iters, 256);
     prof_end(h0, s);
-    // the re-sorts due, in shared launches, then their collisions
-    std::vector<char> due(n, 0);
-    std::vector<const fp::SortArgs*> hs(n);
-    for (int i = 0; i < n; ++i) {
-      due[i] = prm[i].resort_every > 0 && (prm[i].step0 + k + 1) % prm[i].resort_every == 0;
-      hs[i] = (const fp::SortArgs*)(hb + per * k + (sa + se + sg) * n + so * i);
-    }
-    if (std::find(due.begin(), due.end(), 1) == due.end()) continue;
-    prof_begin(h0, PIC_K_SORT, s);
-    if ((e = fp::sort_particles_b((const fp::SortArgs*)(base + (sa + se + sg) * n), hs, due,
-                                  h0->n_cu, s)) != hipSuccess)
-      return hip_fail(e, "pic_batch_step sort");
-    prof_end(h0, s);
-    for (int i = 0; i < n; ++i) {
-      if (!due[i] || !prm[i].collide) continue;
-      prof_begin(h0, PIC_K_COLLIDE, s);
-      const fp::CollideArgs cl = collide_args(
-          b->h[i], &P[i], prm[i].dt * prm[i].resort_every, prm[i].w_sp, prm[i].seed,
-          prm[i].step0 + k, prm[i].instance);
-      if ((e = fp::collide_particles(cl, b->h[i]->n_cu, s)) != hipSuccess)
-        return hip_fail(e, "pic_batch_step collide");
-      prof_end(h0, s);
-    }
   }
   return PIC_OK;
 }

@@ -179,6 +179,50 @@ struct DevMesh {
   double lam_c;              // bound factor of the barycentric inside test
 };
 
+// Pointers that a kernel has read from memory (a batch's argument arrays) are
+// generic to the compiler, where those passed to it by value are global: the
+// accesses become flat ones, which occupy both the memory and the LDS
+// counters and need a 64-bit address in vector registers each (168 registers
+// and spills in the batched FP64 push on full records, 124 and none so; the
+// gather of a batched re-sort 122 us against 30).  globalize reads every
+// pointer of an argument record as one to global memory.
+template <typename P>
+__device__ inline P* global_ptr(P* const& p) {
+  return (P*)*reinterpret_cast<__attribute__((address_space(1))) P* const*>(&p);
+}
+#define FP_GLOBAL(f) a.f = global_ptr(from.f)
+__device__ inline void globalize(SellView& a, const SellView& from) {
+  FP_GLOBAL(sptr); FP_GLOBAL(code); FP_GLOBAL(dict); FP_GLOBAL(dict32); FP_GLOBAL(col);
+  FP_GLOBAL(val); FP_GLOBAL(val32);
+}
+__device__ inline void globalize(DevMesh& a, const DevMesh& from) {
+  FP_GLOBAL(tw); FP_GLOBAL(tg); FP_GLOBAL(tc); FP_GLOBAL(maps); FP_GLOBAL(maps32);
+  FP_GLOBAL(tg32); FP_GLOBAL(invdiag); FP_GLOBAL(invdiag32); FP_GLOBAL(g_unit);
+  FP_GLOBAL(free2node); FP_GLOBAL(node2free); FP_GLOBAL(k_sptr); FP_GLOBAL(k_ncol);
+  FP_GLOBAL(k_sval); FP_GLOBAL(kr_code); FP_GLOBAL(kr_dict); FP_GLOBAL(kr_dict32);
+  FP_GLOBAL(r_sval); FP_GLOBAL(r_sval32); FP_GLOBAL(d_sptr); FP_GLOBAL(d_ncol);
+  FP_GLOBAL(d_sval); FP_GLOBAL(d_sval32); FP_GLOBAL(f_rowsum); FP_GLOBAL(rt_sval);
+  FP_GLOBAL(t_sptr); FP_GLOBAL(t_ncol); FP_GLOBAL(t_sval); FP_GLOBAL(e_tet); FP_GLOBAL(e_nodes);
+  FP_GLOBAL(e_abc); FP_GLOBAL(e_area); FP_GLOBAL(e_nrm); FP_GLOBAL(en_node); FP_GLOBAL(en_ptr);
+  FP_GLOBAL(en_face); FP_GLOBAL(bstart); FP_GLOBAL(bitem); FP_GLOBAL(bseed); FP_GLOBAL(fseed);
+  globalize(a.kz, from.kz);
+}
+// Records that no running kernel writes, read as constant memory: a wave then
+// holds them in scalar registers.
+template <typename A>
+__device__ inline const A* const_args(const A* p) {
+  return (const A*)(const __attribute__((address_space(4))) A*)(uintptr_t)p;
+}
+// The arguments of instance i of a batched launch: a private copy, so that
+// nothing aliases the stores.
+template <typename A>
+__device__ inline A batch_args(const A* args, int i) {
+  const A* from = const_args(args + i);
+  A a = *from;
+  globalize(a, *from);
+  return a;
+}
+
 // Virtual workgroup: index and count within the grid of one instance.  A
 // single-instance launch uses (blockIdx.x, gridDim.x); a batched launch
 // maps its blocks onto the instances with a schedule table.
@@ -193,11 +237,12 @@ constexpr int kMaxBatch = 64;
 struct BatchMap {
   int32_t n_seg;
   int32_t off[kMaxBatch + 1];
-  int8_t inst[kMaxBatch];
+  int32_t inst[kMaxBatch];  // (words: scalar loads reach no bytes)
 };
 
-__device__ inline VB batch_block(const BatchMap& b, int& inst) {
-  const int g = (int)blockIdx.x;
+// lead: workgroups of the launch ahead of the map's
+__device__ inline VB batch_block(const BatchMap& b, int& inst, int lead = 0) {
+  const int g = (int)blockIdx.x - lead;
   int j = 0;
   while (j + 1 < b.n_seg && b.off[j + 1] <= g) ++j;
   inst = b.inst[j];

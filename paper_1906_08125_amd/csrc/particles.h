@@ -64,14 +64,25 @@ struct EmitArgs {
   int64_t* clear;         // node charges cleared by k_begin, or null
   int64_t n_clear;
   const int32_t* gate;    // as StepArgs::gate
-  // the emission counts are computed by the first workgroup of the particle
-  // kernel (launch_particles with these arguments), not by k_begin
-  int defer;
   int cell;               // as StepArgs::cell (face field of the face's tet)
   const double* phi;
   const int32_t* counts_in;  // frozen per-face counts (replace the rounding) or null
   int32_t* counts_out;       // the counts used, or null
 };
+
+__device__ inline void globalize(StepArgs& a, const StepArgs& from) {
+  globalize(a.m, from.m);
+  FP_GLOBAL(x); FP_GLOBAL(y); FP_GLOBAL(z); FP_GLOBAL(vx); FP_GLOBAL(vy); FP_GLOBAL(vz);
+  FP_GLOBAL(w); FP_GLOBAL(tet); FP_GLOBAL(birth); FP_GLOBAL(id); FP_GLOBAL(n_slots);
+  FP_GLOBAL(E); FP_GLOBAL(charge); FP_GLOBAL(s_face); FP_GLOBAL(offsets); FP_GLOBAL(queue);
+  FP_GLOBAL(scratch); FP_GLOBAL(stats); FP_GLOBAL(acc_rows); FP_GLOBAL(gate); FP_GLOBAL(phi);
+}
+__device__ inline void globalize(EmitArgs& a, const EmitArgs& from) {
+  globalize(a.m, from.m);
+  FP_GLOBAL(E); FP_GLOBAL(counts); FP_GLOBAL(offsets); FP_GLOBAL(n_slots); FP_GLOBAL(scratch);
+  FP_GLOBAL(stats); FP_GLOBAL(rate); FP_GLOBAL(face_F); FP_GLOBAL(clear); FP_GLOBAL(gate);
+  FP_GLOBAL(phi); FP_GLOBAL(counts_in); FP_GLOBAL(counts_out);
+}
 
 struct LocateArgs {
   DevMesh m;
@@ -101,8 +112,6 @@ int particle_blocks_per_cu(int f32, int packed, int waves);
 // else taken as 4).
 hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
                             int g_inj, int waves, hipStream_t s);
-hipError_t launch_stats(const int64_t* rows, int n_rows, pic_step_stats* st,
-                        const int32_t* gate, hipStream_t s);
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s);
 hipError_t launch_emit(const EmitArgs& a, hipStream_t s);
 hipError_t launch_fallback(const StepArgs& a, int grid, hipStream_t s);
@@ -114,11 +123,8 @@ hipError_t launch_deposit(const DepositArgs& a, int grid, hipStream_t s);
 hipError_t launch_begin_b(const EmitArgs* E, const BatchMap& map, int grid,
                           hipStream_t s);
 // (the instances of one launch all have packed tet records, or none has)
-hipError_t launch_particles_b(const StepArgs* A, const BatchMap& map, int grid,
+hipError_t launch_particles_b(const StepArgs* A, const EmitArgs* E, const BatchMap& map,
                               int f32, int packed, hipStream_t s);
 hipError_t launch_fallback_b(const StepArgs* A, const BatchMap& map, int grid,
                              hipStream_t s);
-hipError_t launch_stats_b(const StepArgs* A, const BatchMap& map, int grid,
-                          hipStream_t s);
-
 }  // namespace fp

@@ -764,14 +764,15 @@ __device__ void emit_block(const EmitArgs& a) {
   }
 }
 
-constexpr int kBeginBlock = 512;  // 1024 would cap registers below the emission path's needs
+constexpr int kBeginBlock = 512;
 
 __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a) {
   emit_block<kBlock, false>(a);
 }
 
-// Start of a step: workgroup 0 clears the step's stats and counters and
-// computes the emission counts; the others clear the node charges.
+// Start of the first step of a call (the solve of a step starts the next):
+// workgroup 0 clears the step's stats and counters, the others the node
+// charges.
 __device__ inline void begin_body(const EmitArgs& a, VB vb) {
   if (gate_closed(a.gate)) return;
   if (vb.id == 0) {  // dispatched first: the emission path is the longest
@@ -782,13 +783,9 @@ __device__ inline void begin_body(const EmitArgs& a, VB vb) {
     const int nc = (int)(sizeof(StepScratch) / sizeof(int32_t));
     if (threadIdx.x < nc) c32[threadIdx.x] = 0;
     __syncthreads();
-    if (a.defer) {
-      // the particle kernel emits; its pushing workgroups need the slot
-      // count before injection now
-      if (threadIdx.x == 0) a.scratch->inj_base = *a.n_slots;
-      return;
-    }
-    emit_block<kBeginBlock, false>(a);
+    // (the particle kernel emits; its pushing workgroups need the slot count
+    // before injection now)
+    if (threadIdx.x == 0) a.scratch->inj_base = *a.n_slots;
     return;
   }
   const int64_t G = vb.n - 1;
@@ -805,7 +802,7 @@ __global__ void __launch_bounds__(kBeginBlock) k_begin_b(const EmitArgs* E,
                                                          BatchMap map) {
   int i;
   const VB vb = batch_block(map, i);
-  const EmitArgs a = E[i];  // a private copy: no aliasing with the stores
+  const EmitArgs a = batch_args(E, i);
   begin_body(a, vb);
 }
 
@@ -1141,10 +1138,9 @@ __device__ inline bool emit_wait(const StepArgs& a) {
 }
 
 // One instance per storage precision and record form, so that only one push
-// is compiled in.  wait: the injecting workgroups wait for the emission (see
-// emit_wait).
+// is compiled in.
 template <bool F32, bool PK>
-__device__ inline void particles_body(const StepArgs& a, VB vb, bool wait) {
+__device__ inline void particles_body(const StepArgs& a, VB vb) {
   Acc acc;
   acc_zero(acc);
   __shared__ ChargeTable T;
@@ -1161,7 +1157,7 @@ __device__ inline void particles_body(const StepArgs& a, VB vb, bool wait) {
       push_role32<PK>(a, M, vb.id, g_push, acc, T);
     else
       push_role64<PK>(a, M, vb.id, g_push, acc, T);
-  } else if (!wait || emit_wait(a)) {
+  } else if (emit_wait(a)) {
     inject_role<PK>(a, M, vb.id - g_push, vb.n - g_push, acc, T);
   }
   table_flush(T, a.charge);  // (synchronizes)
@@ -1191,16 +1187,32 @@ __global__ void __launch_bounds__(kBlock, W) k_particles(StepArgs a, EmitArgs e)
   if (blockIdx.x == 0)
     emit_publish(e);
   else
-    particles_body<F32, PK>(a, VB{(int)blockIdx.x - 1, (int)gridDim.x - 1}, true);
+    particles_body<F32, PK>(a, VB{(int)blockIdx.x - 1, (int)gridDim.x - 1});
+}
+
+// The emitting workgroups of all instances come first, in a whole round of
+// the XCDs, so that they are resident before any workgroup that waits for
+// one of them.
+__host__ __device__ inline int batch_emitters(const BatchMap& map) {
+  return (map.n_seg + 7) / 8 * 8;
 }
 
 template <bool F32, bool PK>
-__global__ void __launch_bounds__(kBlock, PK ? 4 : 3) k_particles_b(const StepArgs* A,
-                                                        BatchMap map) {
+__global__ void __launch_bounds__(kBlock, 4) k_particles_b(const StepArgs* A,
+                                                            const EmitArgs* E,
+                                                            BatchMap map) {
+  const int lead = batch_emitters(map);
+  if ((int)blockIdx.x < lead) {
+    if ((int)blockIdx.x >= map.n_seg) return;
+    const EmitArgs e = batch_args(E, map.inst[blockIdx.x]);
+    if (!gate_closed(e.gate)) emit_publish(e);
+    return;
+  }
   int i;
-  const VB vb = batch_block(map, i);
-  const StepArgs a = A[i];  // a private copy: no aliasing with the stores
-  particles_body<F32, PK>(a, vb, false);
+  const VB vb = batch_block(map, i, lead);
+  const StepArgs a = batch_args(A, i);
+  if (gate_closed(a.gate)) return;
+  particles_body<F32, PK>(a, vb);
 }
 
 // ---------------------------------------------------------------------------
@@ -1257,26 +1269,8 @@ __global__ void __launch_bounds__(kBlock) k_fallback_b(const StepArgs* A,
                                                        BatchMap map) {
   int i;
   const VB vb = batch_block(map, i);
-  const StepArgs a = A[i];
+  const StepArgs a = batch_args(A, i);
   fallback_body(a, vb);
-}
-
-__global__ void __launch_bounds__(kBlock) k_stats(const int64_t* rows,
-                                                  int n_rows,
-                                                  pic_step_stats* st,
-                                                  const int32_t* gate) {
-  if (gate_closed(gate)) return;
-  step_counter_sum(rows, n_rows, st, (int)blockIdx.x);
-}
-
-// Batched: kAccFields workgroups per instance (schedule of 16 per instance).
-__global__ void __launch_bounds__(kBlock) k_stats_b(const StepArgs* A,
-                                                    BatchMap map) {
-  int i;
-  const VB vb = batch_block(map, i);
-  if (vb.id >= kAccFields) return;
-  const StepArgs& a = A[i];
-  step_counter_sum(a.acc_rows, a.acc_stride, a.stats, vb.id);
 }
 
 // ---------------------------------------------------------------------------
@@ -1384,21 +1378,17 @@ hipError_t launch_begin_b(const EmitArgs* E, const BatchMap& map, int grid,
   hipLaunchKernelGGL(k_begin_b, dim3(grid), dim3(kBeginBlock), 0, s, E, map);
   return hipGetLastError();
 }
-hipError_t launch_particles_b(const StepArgs* A, const BatchMap& map, int grid,
+hipError_t launch_particles_b(const StepArgs* A, const EmitArgs* E, const BatchMap& map,
                               int f32, int packed, hipStream_t s) {
   const auto kern = packed ? (f32 ? k_particles_b<true, true> : k_particles_b<false, true>)
                            : (f32 ? k_particles_b<true, false> : k_particles_b<false, false>);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, A, map);
+  hipLaunchKernelGGL(kern, dim3(batch_emitters(map) + map.off[map.n_seg]), dim3(kBlock), 0,
+                     s, A, E, map);
   return hipGetLastError();
 }
 hipError_t launch_fallback_b(const StepArgs* A, const BatchMap& map, int grid,
                              hipStream_t s) {
   hipLaunchKernelGGL(k_fallback_b, dim3(grid), dim3(kBlock), 0, s, A, map);
-  return hipGetLastError();
-}
-hipError_t launch_stats_b(const StepArgs* A, const BatchMap& map, int grid,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(k_stats_b, dim3(grid), dim3(kBlock), 0, s, A, map);
   return hipGetLastError();
 }
 using ParticlesKernel = void (*)(StepArgs, EmitArgs);
@@ -1426,11 +1416,6 @@ hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
 }
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_seed_build, dim3(grid), dim3(kBlock), 0, s, m);
-  return hipGetLastError();
-}
-hipError_t launch_stats(const int64_t* rows, int n_rows, pic_step_stats* st,
-                        const int32_t* gate, hipStream_t s) {
-  hipLaunchKernelGGL(k_stats, dim3(kAccFields), dim3(kBlock), 0, s, rows, n_rows, st, gate);
   return hipGetLastError();
 }
 hipError_t launch_emit(const EmitArgs& a, hipStream_t s) {

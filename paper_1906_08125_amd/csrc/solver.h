@@ -118,6 +118,15 @@ struct CgArgs {
   int lean;
   int b_saved;
 };
+__device__ inline void globalize(CgArgs& a, const CgArgs& from) {
+  globalize(a.m, from.m);
+  FP_GLOBAL(charge); FP_GLOBAL(rhs); FP_GLOBAL(bref); FP_GLOBAL(phi); FP_GLOBAL(E);
+  FP_GLOBAL(x); FP_GLOBAL(r); FP_GLOBAL(p); FP_GLOBAL(u); FP_GLOBAL(w); FP_GLOBAL(s);
+  FP_GLOBAL(z); FP_GLOBAL(rec0); FP_GLOBAL(rec1); FP_GLOBAL(part); FP_GLOBAL(bprev);
+  FP_GLOBAL(ctrl); FP_GLOBAL(amg_dev); FP_GLOBAL(report); FP_GLOBAL(dir_nodes);
+  FP_GLOBAL(stats); FP_GLOBAL(step_stats); FP_GLOBAL(acc_rows); FP_GLOBAL(next_stats);
+  FP_GLOBAL(next_scratch); FP_GLOBAL(n_slots); FP_GLOBAL(clear_charge);
+}
 
 // seq != 0: the last kernel of the launch writes the state with this
 // sequence number into args.report (host-mapped).
@@ -145,8 +154,9 @@ struct CgBatch {
   uint64_t mask;
 };
 // incremental: every instance's first pass forms its residual from its
-// previous solve (CgArgs::incremental; all instances alike)
-hipError_t cg_batch_begin(const CgBatch& b, int grid, int incremental,
+// previous solve (CgArgs::incremental; all instances alike).  seq: the test
+// reports every instance's state with it, or 0
+hipError_t cg_batch_begin(const CgBatch& b, int grid, int incremental, int64_t seq,
                           hipStream_t s);
 hipError_t cg_batch_iters(const CgBatch& b, int grid, int n, hipStream_t s);  // n even
 hipError_t cg_batch_recheck(const CgBatch& b, int grid, hipStream_t s);

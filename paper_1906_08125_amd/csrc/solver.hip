@@ -257,8 +257,11 @@ __device__ inline void k_cg_resfield_body(const CgArgs& a, int reset, VB vb,
   }
   const DevMesh& m = a.m;
   if (reset && vb.id == 0 && threadIdx.x == 0) ctrl_reset(a.ctrl);
-  if (reset && a.acc_rows && vb.id < kStepCounters)
-    step_counter_sum(a.acc_rows, a.acc_n, a.step_stats, vb.id);
+  if (reset && a.acc_rows)
+    for (int k = vb.id; k < kStepCounters; k += vb.n) {
+      step_counter_sum(a.acc_rows, a.acc_n, a.step_stats, k);
+      __syncthreads();
+    }
   const int lane = threadIdx.x & (kSell - 1);
   const int sub = threadIdx.x / kSell;
   const int nsub = blockDim.x / kSell;
@@ -467,8 +470,11 @@ __device__ inline void k_cg_resfield_body(const CgArgs& a, int reset, VB vb,
 __device__ inline void k_cg_resinc_body(const CgArgs& a, VB vb) {
   const DevMesh& m = a.m;
   if (vb.id == 0 && threadIdx.x == 0) ctrl_reset(a.ctrl);
-  if (a.acc_rows && vb.id < kStepCounters)
-    step_counter_sum(a.acc_rows, a.acc_n, a.step_stats, vb.id);
+  if (a.acc_rows)
+    for (int k = vb.id; k < kStepCounters; k += vb.n) {
+      step_counter_sum(a.acc_rows, a.acc_n, a.step_stats, k);
+      __syncthreads();
+    }
   const Range rows = my_range(m.n_free, vb);
   double v[2] = {0.0, 0.0};
   for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
@@ -911,33 +917,34 @@ __global__ void __launch_bounds__(kCgBlock) k_cg_resfield_b(CgBatch b, int reset
   int i;
   const VB vb = batch_block(b.map, i);
   if (gated == 1 && !((b.mask >> i) & 1ull)) return;
-  const CgArgs a = b.args[i];  // a private copy: no aliasing with the stores
+  const CgArgs a = batch_args(b.args, i);
   k_cg_resfield_body(a, reset, vb, gated == 2);
 }
 __global__ void __launch_bounds__(kCgBlock) k_cg_resinc_b(CgBatch b) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
+  const CgArgs a = batch_args(b.args, i);
   k_cg_resinc_body(a, vb);
 }
 __global__ void __launch_bounds__(kCgBlock) k_cg_scatter_b(CgBatch b, int gated) {
   int i;
   const VB vb = batch_block(b.map, i);
   if (gated == 1 && !((b.mask >> i) & 1ull)) return;
-  const CgArgs a = b.args[i];
+  const CgArgs a = batch_args(b.args, i);
   k_cg_scatter_body(a, vb, gated == 2);
 }
-__global__ void __launch_bounds__(kCgBlock) k_cg_start_b(CgBatch b, int gated) {
+// seq: as k_cg_start's, or 0
+__global__ void __launch_bounds__(kCgBlock) k_cg_start_b(CgBatch b, int64_t seq, int gated) {
   int i;
   const VB vb = batch_block(b.map, i);
   if (gated == 1 && !((b.mask >> i) & 1ull)) return;
-  const CgArgs a = b.args[i];
-  k_cg_start_body(a, 0, vb, gated == 2);
+  const CgArgs a = batch_args(b.args, i);
+  k_cg_start_body(a, seq, vb, gated == 2);
 }
 __global__ void __launch_bounds__(kCgBlock, 4) k_cg_iter_b(CgBatch b, int par) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
+  const CgArgs a = batch_args(b.args, i);
   k_cg_iter_body(a, par, vb);
 }
 // One thread per instance: report the control state with sequence seq.
@@ -1283,19 +1290,19 @@ struct AmgBatch {
 template <typename T>
 __device__ inline T* coarse_vec(const AmgDev& D, int which) {
   if constexpr (std::is_same<T, float>::value)
-    return which ? D.coarse_x32 : D.coarse_b32;
+    return global_ptr(which ? D.coarse_x32 : D.coarse_b32);
   else
-    return which ? D.coarse_x : D.coarse_b;
+    return global_ptr(which ? D.coarse_x : D.coarse_b);
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kCgBlock) k_amg_down_b(AmgBatch b, int level) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
-  const AmgDev* D = (const AmgDev*)a.amg_dev;
-  const AmgLevel L = D->lv[level];
-  T* nb = level + 1 < D->n_levels ? level_vecs<T>(D->lv[level + 1]).b
+  const CgArgs a = batch_args(b.args, i);
+  const AmgDev* D = const_args((const AmgDev*)a.amg_dev);
+  const AmgLevel L = batch_args(D->lv, level);
+  T* nb = level + 1 < D->n_levels ? level_vecs<T>(batch_args(D->lv, level + 1)).b
                                   : coarse_vec<T>(*D, 0);
   amg_down_body<T>(a, L, level, nb, vb);
 }
@@ -1303,10 +1310,10 @@ template <typename T>
 __global__ void __launch_bounds__(kCgBlock) k_amg_up_b(AmgBatch b, int level) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
-  const AmgDev* D = (const AmgDev*)a.amg_dev;
-  const AmgLevel L = D->lv[level];
-  const T* y = level + 1 < D->n_levels ? level_vecs<T>(D->lv[level + 1]).t
+  const CgArgs a = batch_args(b.args, i);
+  const AmgDev* D = const_args((const AmgDev*)a.amg_dev);
+  const AmgLevel L = batch_args(D->lv, level);
+  const T* y = level + 1 < D->n_levels ? level_vecs<T>(batch_args(D->lv, level + 1)).t
                                        : coarse_vec<T>(*D, 1);
   amg_up_body<T>(a, L, level, y, vb);
 }
@@ -1314,24 +1321,24 @@ template <typename T>
 __global__ void __launch_bounds__(kCgBlock) k_amg_coarse_b(AmgBatch b) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
-  const AmgDev* D = (const AmgDev*)a.amg_dev;
+  const CgArgs a = batch_args(b.args, i);
+  const AmgDev* D = const_args((const AmgDev*)a.amg_dev);
   const T* inv;
-  if constexpr (std::is_same<T, float>::value) inv = D->coarse_inv32;
-  else inv = D->coarse_inv;
+  if constexpr (std::is_same<T, float>::value) inv = global_ptr(D->coarse_inv32);
+  else inv = global_ptr(D->coarse_inv);
   amg_coarse_body<T>(a, D->n_coarse, inv, coarse_vec<T>(*D, 0),
                      coarse_vec<T>(*D, 1), vb);
 }
 __global__ void __launch_bounds__(kCgBlock) k_amg_spmv_b(AmgBatch b) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
+  const CgArgs a = batch_args(b.args, i);
   amg_spmv_body(a, vb);
 }
 __global__ void __launch_bounds__(kCgBlock) k_amg_upd_b(AmgBatch b) {
   int i;
   const VB vb = batch_block(b.map, i);
-  const CgArgs a = b.args[i];
+  const CgArgs a = batch_args(b.args, i);
   amg_upd_body(a, vb);
 }
 
@@ -1554,13 +1561,13 @@ hipError_t cg_launch_recheck_if(const CgArgs& a, hipStream_t s) {
     if (e_ != hipSuccess) return e_;                                          \
   } while (0)
 
-hipError_t cg_batch_begin(const CgBatch& b, int grid, int incremental,
+hipError_t cg_batch_begin(const CgBatch& b, int grid, int incremental, int64_t seq,
                           hipStream_t s) {
   if (incremental)
     BLAUNCH(k_cg_resinc_b, b);
   else
     BLAUNCH(k_cg_resfield_b, b, 1, 0);
-  BLAUNCH(k_cg_start_b, b, 0);
+  BLAUNCH(k_cg_start_b, b, seq, 0);
   return hipSuccess;
 }
 
@@ -1573,14 +1580,14 @@ hipError_t cg_batch_iters(const CgBatch& b, int grid, int n, hipStream_t s) {
 hipError_t cg_batch_recheck(const CgBatch& b, int grid, hipStream_t s) {
   BLAUNCH(k_cg_scatter_b, b, 1);
   BLAUNCH(k_cg_resfield_b, b, 0, 1);
-  BLAUNCH(k_cg_start_b, b, 1);
+  BLAUNCH(k_cg_start_b, b, (int64_t)0, 1);
   return hipSuccess;
 }
 
 hipError_t cg_batch_recheck_if(const CgBatch& b, int grid, hipStream_t s) {
   BLAUNCH(k_cg_scatter_b, b, 2);
   BLAUNCH(k_cg_resfield_b, b, 0, 2);
-  BLAUNCH(k_cg_start_b, b, 2);
+  BLAUNCH(k_cg_start_b, b, (int64_t)0, 2);
   return hipSuccess;
 }
 

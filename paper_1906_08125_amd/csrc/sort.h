@@ -34,6 +34,20 @@ struct SortArgs {
   int64_t* s_id;
 };
 
+__device__ inline void globalize(SortArgs& a, const SortArgs& from) {
+  for (int f = 0; f < 6; ++f) {
+    FP_GLOBAL(real[f]);
+    FP_GLOBAL(s_real[f]);
+  }
+  for (int k = 0; k < 2; ++k) {
+    FP_GLOBAL(key[k]);
+    FP_GLOBAL(val[k]);
+  }
+  FP_GLOBAL(n_slots); FP_GLOBAL(n_live); FP_GLOBAL(stats); FP_GLOBAL(w); FP_GLOBAL(tet);
+  FP_GLOBAL(birth); FP_GLOBAL(id); FP_GLOBAL(hist); FP_GLOBAL(total); FP_GLOBAL(s_w);
+  FP_GLOBAL(s_tet); FP_GLOBAL(s_birth); FP_GLOBAL(s_id);
+}
+
 // copyback: the sorted particles are copied back into the arrays they came
 // from (real, w, ...); else they stay in the scratch arrays (s_real, s_w,
 // ...), which the caller then uses as the particle arrays, and only the

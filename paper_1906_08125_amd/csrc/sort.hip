@@ -73,6 +73,12 @@ __device__ inline uint32_t block_exscan(uint32_t v, uint32_t* wsum,
   return before + inc - v;
 }
 
+// Buffer src of a pair.  (A selection: an index that the compiler does not
+// know would put a batch's arguments into scratch memory.)
+__device__ inline uint32_t* buffer(uint32_t* const* pair, int src) {
+  return src ? pair[1] : pair[0];
+}
+
 // Which pass: FIRST keys are the tets, else those of buffer src; the digit
 // is the eight bits from shift on; the output goes to buffer src ^ 1.
 template <bool FIRST>
@@ -81,7 +87,7 @@ __device__ inline uint32_t sort_key(const SortArgs& a, int src, int64_t i) {
     const int32_t t = a.tet[i];
     return t < 0 ? (uint32_t)a.n_tets : (uint32_t)t;
   } else {
-    return a.key[src][i];
+    return buffer(a.key, src)[i];
   }
 }
 
@@ -149,7 +155,7 @@ __device__ inline void scatter_body(const SortArgs& a, VB vb, int src, int shift
   for (int r = 0; r < kRounds; ++r) {
     const int64_t i = w0 + r * 64;
     kr[r] = i < n ? sort_key<FIRST>(a, src, i) : 0u;
-    vr[r] = i < n ? (FIRST ? (uint32_t)i : a.val[src][i]) : 0u;
+    vr[r] = i < n ? (FIRST ? (uint32_t)i : buffer(a.val, src)[i]) : 0u;
   }
   for (int b = lane; b < kBins; b += 64) wc[wave][b] = 0;
   const int dig = threadIdx.x % kBins;
@@ -232,8 +238,8 @@ __device__ inline void scatter_body(const SortArgs& a, VB vb, int src, int shift
   }
   __syncthreads();
   const int m = n - base < kSortTile ? (int)(n - base) : kSortTile;
-  uint32_t* okey = a.key[src ^ 1];
-  uint32_t* oval = a.val[src ^ 1];
+  uint32_t* okey = buffer(a.key, src ^ 1);
+  uint32_t* oval = buffer(a.val, src ^ 1);
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const int j = r * kThreads + (int)threadIdx.x;
@@ -276,11 +282,11 @@ __device__ inline void move_one(void* const* to, double* to_w, int32_t* to_t, in
 template <typename T>
 __device__ inline void gather_body(const SortArgs& a, VB vb, int src) {
   const int64_t n = *a.n_live;  // (the incoming slot count, see hist_body)
-  const uint32_t* key = a.key[src];
-  const uint32_t* val = a.val[src];
+  const uint32_t* key = buffer(a.key, src);
+  const uint32_t* val = buffer(a.val, src);
   const int parts = vb.n % 8 == 0 ? 8 : 1;
   const int part = vb.id % parts;
-  const int64_t per_part = (n + parts - 1) / parts;
+  const int64_t per_part = parts == 8 ? (n + 7) >> 3 : n;
   const int64_t lo = part * per_part;
   const int64_t hi = lo + per_part < n ? lo + per_part : n;
   const int64_t stride = (int64_t)(vb.n / parts) * blockDim.x;
@@ -341,13 +347,13 @@ __global__ void __launch_bounds__(kThreads) k_sort_hist_b(const SortArgs* A, Bat
                                                           int src, int shift) {
   int i;
   const VB vb = batch_block(map, i);
-  hist_body<FIRST>(A[i], vb, src, shift);
+  hist_body<FIRST>(batch_args(A, i), vb, src, shift);
 }
 __global__ void __launch_bounds__(kScanThreads) k_sort_scan_b(const SortArgs* A,
                                                               BatchMap map) {
   int i;
   const VB vb = batch_block(map, i);
-  const SortArgs& a = A[i];
+  const SortArgs a = batch_args(A, i);
   if (a.ntiles > kFoldTiles) scan_body(a, vb);
 }
 template <bool FIRST>
@@ -356,14 +362,14 @@ __global__ void __launch_bounds__(kThreads) k_sort_scatter_b(const SortArgs* A,
                                                              int shift) {
   int i;
   const VB vb = batch_block(map, i);
-  scatter_body<FIRST>(A[i], vb, src, shift);
+  scatter_body<FIRST>(batch_args(A, i), vb, src, shift);
 }
 template <typename T>
 __global__ void __launch_bounds__(kMoveThreads) k_sort_gather_b(const SortArgs* A,
                                                                 BatchMap map, int src) {
   int i;
   const VB vb = batch_block(map, i);
-  const SortArgs a = A[i];  // a private copy: no aliasing with the stores
+  const SortArgs a = batch_args(A, i);
   gather_body<T>(a, vb, src);
 }
 template <typename T>
@@ -371,7 +377,7 @@ __global__ void __launch_bounds__(kMoveThreads) k_sort_copy_b(const SortArgs* A,
                                                               BatchMap map) {
   int i;
   const VB vb = batch_block(map, i);
-  const SortArgs a = A[i];
+  const SortArgs a = batch_args(A, i);
   copy_body<T>(a, vb);
 }
 
@@ -423,7 +429,7 @@ hipError_t sort_particles_b(const SortArgs* A, const std::vector<const SortArgs*
   for (size_t i = 0; i < host.size(); ++i) {
     if (!due[i]) continue;
     const SortArgs& a = *host[i];
-    tiles.inst[j] = bins.inst[j] = moves.inst[j] = (int8_t)i;
+    tiles.inst[j] = bins.inst[j] = moves.inst[j] = (int32_t)i;
     tiles.off[j + 1] = tiles.off[j] + a.ntiles;
     bins.off[j + 1] = bins.off[j] + kBins;
     // one slot per thread, in whole rounds of the XCDs
