@@ -521,6 +521,15 @@ __device__ inline void step_counter_sum(const int64_t* rows, int n_rows,
 }
 
 // Internal per-handle device scratch layout (counters and scalars).
+// The running sums of a step's emission, in the order of the faces, after
+// one trip of its workgroups (flag: that trip's number plus one).
+struct EmitSums {
+  long long offset, n_clamp;
+  double cur, F_sum, F_max;
+  int32_t flag, pad;
+};
+constexpr int kEmitters = 8;  // emitting workgroups of a particle launch, at most
+
 struct StepScratch {
   // counters used by the particle kernels of one step
   int32_t n_fallback;
@@ -528,8 +537,9 @@ struct StepScratch {
   int32_t inj_total;
   int32_t inj_fit;
   int32_t n_live;
-  int32_t emitted;  // set once the emission counts of the step are published
+  int32_t emitted;  // emitting workgroups whose counts and offsets are out
   int32_t pad[2];
+  EmitSums sums[kEmitters];
 };
 
 }  // namespace fp

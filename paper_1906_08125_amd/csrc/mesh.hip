@@ -890,6 +890,7 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   h->grid_push = std::max(8, h->n_cu * 8);
   h->grid_inj = std::max(8, h->n_cu * 2);
   h->grid_fb = 64;
+  h->step_inj = std::min(h->grid_inj, std::max(8, (h->n_cu / 2) - (h->n_cu / 2) % 8));
   // One workgroup per resident slot: a push grid that fills the chip in a
   // single round has no tail of late workgroups (measured on the production
   // tip: 3 resident per CU, 91 us per push against 100 us for 8 per CU and
@@ -900,7 +901,6 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
       int g = std::min(h->grid_push, std::max(8, h->n_cu * per_cu));
       h->step_push[f32][five] = g >= 8 ? g - g % 8 : g;
     }
-  h->step_inj = std::min(h->grid_inj, std::max(8, (h->n_cu / 2) - (h->n_cu / 2) % 8));
   h->acc_rows = (int64_t*)dev_alloc(
       h, sizeof(int64_t) * 16 * (size_t)(h->grid_push + h->grid_inj + h->grid_fb), err);
   if (err == hipErrorOutOfMemory && h->ws_base) {

@@ -648,18 +648,53 @@ __device__ inline int32_t emit_get(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// What workgroup t of T hands to the next trip and takes from the one
+// before (one lane): stored and loaded past the caches, the flag last.
+__device__ inline void sums_put(EmitSums* p, const EmitSums& v, int32_t flag) {
+  const unsigned long long* w = reinterpret_cast<const unsigned long long*>(&v);
+  unsigned long long* o = reinterpret_cast<unsigned long long*>(p);
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    __hip_atomic_store(o + k, w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_s_waitcnt(0);
+  __hip_atomic_store(&p->flag, flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A wait is bounded: a flag not seen in time (never expected) ends it.
+constexpr int kEmitSpin = 1 << 22;
+
+__device__ inline bool sums_get(EmitSums* p, EmitSums& v, int32_t flag) {
+  for (int it = 0; it < kEmitSpin; ++it) {
+    if (emit_get(&p->flag) == flag) {
+      unsigned long long* w = reinterpret_cast<unsigned long long*>(&v);
+      unsigned long long* o = reinterpret_cast<unsigned long long*>(p);
+#pragma unroll
+      for (int k = 0; k < 5; ++k)
+        w[k] = __hip_atomic_load(o + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return true;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  v = EmitSums{};  // (offsets stay within the arrays)
+  return false;
+}
+
+// Workgroup t of T: the faces are taken NT to a trip, the trips by the
+// workgroups in turn.  Counts and currents of a trip are computed on their
+// own; the running sums (counts, and currents and fields in a fixed order)
+// then pass from trip to trip.
 template <int NT, bool PUB>
-__device__ void emit_block(const EmitArgs& a) {
+__device__ void emit_block(const EmitArgs& a, int t, int T) {
   const DevMesh& m = a.m;
   __shared__ long long s_scan[NT / 64];
   __shared__ double s_red[3][NT / 64];
   __shared__ long long s_cl[NT / 64];
-  long long offset = 0;
-  double cur_sum = 0.0, F_sum = 0.0, F_max = 0.0;
-  long long n_clamp = 0;
+  __shared__ EmitSums s_sums;
+  EmitSums sum{};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t f0 = 0; f0 < m.n_emit; f0 += NT) {
-    const int64_t f = f0 + threadIdx.x;
+  const int trips = (int)((m.n_emit + NT - 1) / NT);
+  for (int k = t; k < trips; k += T) {
+    const int64_t f = k * (int64_t)NT + threadIdx.x;
     long long cnt = 0;
     double cur = 0.0, F = 0.0;
     int clamped = 0;
@@ -719,31 +754,39 @@ __device__ void emit_block(const EmitArgs& a) {
       s_red[2][wave] = v2;
       s_cl[wave] = vc;
     }
+    if (T > 1 && k > 0 && threadIdx.x == 0 &&
+        !sums_get(a.scratch->sums + (k - 1) % T, s_sums, k) && a.stats)
+      a.stats->status = PIC_E_DEVICE;
     __syncthreads();
-    long long before = 0, chunk = 0;
+    if (T > 1 && k > 0) sum = s_sums;
+    const long long offset = sum.offset;
+    long long before = 0;
     for (int w = 0; w < NT / 64; ++w) {
       if (w < wave) before += s_scan[w];
-      chunk += s_scan[w];
-      cur_sum += s_red[0][w];
-      F_sum += s_red[1][w];
-      F_max = s_red[2][w] > F_max ? s_red[2][w] : F_max;
-      n_clamp += s_cl[w];
+      sum.offset += s_scan[w];
+      sum.cur += s_red[0][w];
+      sum.F_sum += s_red[1][w];
+      sum.F_max = s_red[2][w] > sum.F_max ? s_red[2][w] : sum.F_max;
+      sum.n_clamp += s_cl[w];
     }
+    if (T > 1 && k + 1 < trips && threadIdx.x == 0)
+      sums_put(a.scratch->sums + k % T, sum, k + 1);
     if (f < m.n_emit && a.counts) {
       a.counts[f] = (int32_t)cnt;
       emit_put<PUB>(a.offsets + f, (int32_t)(offset + before + inc - cnt));
     }
-    offset += chunk;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    if (a.rate) *a.rate = cur_sum;
+  // the workgroup of the last trip ends the emission
+  if (threadIdx.x == 0 && t == (trips > 0 ? (trips - 1) % T : 0)) {
+    const long long offset = sum.offset;
+    if (a.rate) *a.rate = sum.cur;
     if (a.stats) {
       pic_step_stats* st = a.stats;
-      st->emit_current = cur_sum;
-      st->mean_face_E = m.n_emit ? F_sum / (double)m.n_emit : 0.0;
-      st->max_face_E = F_max;
-      st->n_clamp = n_clamp;
+      st->emit_current = sum.cur;
+      st->mean_face_E = m.n_emit ? sum.F_sum / (double)m.n_emit : 0.0;
+      st->max_face_E = sum.F_max;
+      st->n_clamp = sum.n_clamp;
     }
     if (a.counts) {
       emit_put<PUB>(a.offsets + m.n_emit, (int32_t)offset);
@@ -767,7 +810,7 @@ __device__ void emit_block(const EmitArgs& a) {
 constexpr int kBeginBlock = 512;
 
 __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a) {
-  emit_block<kBlock, false>(a);
+  emit_block<kBlock, false>(a, 0, 1);
 }
 
 // Start of the first step of a call (the solve of a step starts the next):
@@ -1097,38 +1140,46 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
   }
 }
 
-// The emission of the step computed inside the particle kernel: workgroup 0
-// (dispatched first, so resident before any workgroup that waits for it)
-// computes the counts and offsets, then publishes them; the injecting
-// workgroups (dispatched last) wait for the flag.  The wait is bounded: a
-// flag not seen in time (never expected) skips the injection and marks the
-// step with a device error.
-// What is published (the offsets and inj_fit) is stored and loaded with
-// device-scope atomics, which go past the per-XCD caches, and each wave's
-// stores are complete before the barrier ahead of the flag: neither side
-// needs a fence, which would write back or invalidate an L2 that the pushing
-// workgroups are using (the waiting side did so at every poll).  With the
-// offsets searched in LDS, the particle kernel of a small step (10k
-// superparticles, 276 emitting faces) went from 40 to 30 us.
-__device__ inline void emit_publish(const EmitArgs& e) {
-  emit_block<kBlock, true>(e);
+// The emission of the step computed inside the particle kernel: the first
+// workgroups (dispatched first, so resident before any workgroup that waits
+// for them; each waits for an earlier one alone) compute the counts and
+// offsets and publish them; the injecting workgroups (dispatched last) wait
+// until all have.  The waits are bounded: a flag not seen in time (never
+// expected) skips the injection and marks the step with a device error.
+// What is published (the sums, the offsets and inj_fit) is stored and loaded
+// with device-scope atomics, which go past the per-XCD caches, and each
+// wave's stores are complete before the barrier ahead of the count: neither
+// side needs a fence, which would write back or invalidate an L2 that the
+// pushing workgroups are using (the waiting side did so at every poll).  With
+// the offsets searched in LDS, the particle kernel of a small step (10k
+// superparticles, 276 emitting faces) went from 40 to 30 us.  A trip of 256
+// faces takes 7 to 10 us, most of it dependent loads: one workgroup taking
+// the trips in turn published 612 faces after 31 us, eight at once after 19.
+__device__ inline int emitters(const DevMesh& m) {
+  const int64_t trips = (m.n_emit + kBlock - 1) / kBlock;
+  return trips < 1 ? 1 : (trips < kEmitters ? (int)trips : kEmitters);
+}
+
+__device__ inline void emit_publish(const EmitArgs& e, int t, int T) {
+  if (t >= T) return;
+  emit_block<kBlock, true>(e, t, T);
   __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have arrived
   __syncthreads();
   if (threadIdx.x == 0)
-    __hip_atomic_store(&e.scratch->emitted, 1, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(&e.scratch->emitted, 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline bool emit_wait(const StepArgs& a) {
+__device__ inline bool emit_wait(const StepArgs& a, int T) {
   __shared__ int seen;
   if (threadIdx.x == 0) {
     int ok = 0;
-    for (int it = 0; it < (1 << 22); ++it) {
-      if (emit_get(&a.scratch->emitted) != 0) {
+    for (int it = 0; it < kEmitSpin; ++it) {
+      if (emit_get(&a.scratch->emitted) == T) {
         ok = 1;
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(20);  // (128 workgroups poll one word)
     }
     if (!ok && a.stats) a.stats->status = PIC_E_DEVICE;
     seen = ok;
@@ -1138,9 +1189,9 @@ __device__ inline bool emit_wait(const StepArgs& a) {
 }
 
 // One instance per storage precision and record form, so that only one push
-// is compiled in.
+// is compiled in.  T_emit: emitting workgroups.
 template <bool F32, bool PK>
-__device__ inline void particles_body(const StepArgs& a, VB vb) {
+__device__ inline void particles_body(const StepArgs& a, VB vb, int T_emit) {
   Acc acc;
   acc_zero(acc);
   __shared__ ChargeTable T;
@@ -1157,7 +1208,7 @@ __device__ inline void particles_body(const StepArgs& a, VB vb) {
       push_role32<PK>(a, M, vb.id, g_push, acc, T);
     else
       push_role64<PK>(a, M, vb.id, g_push, acc, T);
-  } else if (emit_wait(a)) {
+  } else if (emit_wait(a, T_emit)) {
     inject_role<PK>(a, M, vb.id - g_push, vb.n - g_push, acc, T);
   }
   table_flush(T, a.charge);  // (synchronizes)
@@ -1168,14 +1219,14 @@ __device__ inline void particles_body(const StepArgs& a, VB vb) {
   acc_flush(acc, a.acc_rows, vb.id, a.acc_stride);
 }
 
-// Workgroup 0 only emits (see emit_publish) and the particle workgroups are
-// 1 .. gridDim.x - 1 (virtual index one less: the XCD grouping of the slot
-// spans is a fixed rotation of the hardware's).
+// The first kEmitters workgroups only emit (see emit_publish), the others push
+// and inject.
+static_assert(kEmitters % 8 == 0, "the workgroups after them keep their XCD");
 // Bound: the load path and its latency (17 divergent 16-byte gathers per
 // superparticle on packed records), so waves in flight count.  On packed
 // records the push and the injection fit 96 registers without spills (maps
 // in LDS, integer seed clamps, 32-bit counters, absorption counted in LDS)
-// and five waves run per SIMD; only the emission of workgroup 0 spills then.
+// and five waves run per SIMD; only the emission spills then.
 // Full records need 122 registers: four waves.  Ten steps of 1e6
 // superparticles, re-sort included: 1098 us at four waves, 1067 at five; of
 // 1e4, where the emission is the longest chain: 508 at four, 557 at five.
@@ -1184,15 +1235,17 @@ __device__ inline void particles_body(const StepArgs& a, VB vb) {
 template <bool F32, bool PK, int W>
 __global__ void __launch_bounds__(kBlock, W) k_particles(StepArgs a, EmitArgs e) {
   if (gate_closed(a.gate)) return;
-  if (blockIdx.x == 0)
-    emit_publish(e);
+  if (blockIdx.x < kEmitters)
+    emit_publish(e, (int)blockIdx.x, emitters(e.m));
   else
-    particles_body<F32, PK>(a, VB{(int)blockIdx.x - 1, (int)gridDim.x - 1});
+    particles_body<F32, PK>(a, VB{(int)blockIdx.x - kEmitters, (int)gridDim.x - kEmitters},
+                            emitters(a.m));
 }
 
-// The emitting workgroups of all instances come first, in a whole round of
-// the XCDs, so that they are resident before any workgroup that waits for
-// one of them.
+// The emitting workgroups of all instances, one each (the other instances'
+// pushes hide its trips; eight each took 1171 us instead of 1155 for ten
+// steps of six tips), come first, in a whole round of the XCDs, so that they
+// are resident before any workgroup that waits for one of them.
 __host__ __device__ inline int batch_emitters(const BatchMap& map) {
   return (map.n_seg + 7) / 8 * 8;
 }
@@ -1205,14 +1258,14 @@ __global__ void __launch_bounds__(kBlock, 4) k_particles_b(const StepArgs* A,
   if ((int)blockIdx.x < lead) {
     if ((int)blockIdx.x >= map.n_seg) return;
     const EmitArgs e = batch_args(E, map.inst[blockIdx.x]);
-    if (!gate_closed(e.gate)) emit_publish(e);
+    if (!gate_closed(e.gate)) emit_publish(e, 0, 1);
     return;
   }
   int i;
   const VB vb = batch_block(map, i, lead);
   const StepArgs a = batch_args(A, i);
   if (gate_closed(a.gate)) return;
-  particles_body<F32, PK>(a, vb);
+  particles_body<F32, PK>(a, vb, 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1411,7 +1464,7 @@ hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
   StepArgs b = a;
   b.g_push = g_push;
   hipLaunchKernelGGL(particles_kernel(a.f32, a.m.tc != nullptr, waves),
-                     dim3(g_push + g_inj + 1), dim3(kBlock), 0, s, b, e);
+                     dim3(kEmitters + g_push + g_inj), dim3(kBlock), 0, s, b, e);
   return hipGetLastError();
 }
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s) {
