@@ -704,11 +704,12 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
 // sums keep the order, and all values the bits, of separate update and
 // product launches.
 // Bound: latency of the record gathers, then the Infinity Cache.  The first
-// slice's words and records are in flight before the scalars are reduced.
-// An FP64 iteration on the production tip (515k rows, 64 MB) takes 17 us;
+// slice's words and records are in flight before the scalars are reduced, and
+// the first rows of the row-local part before the products.
+// An FP64 iteration on the production tip (515k rows, 64 MB) takes 16.5 us;
 // an update launch and a product over all 15 entries per row took 14 + 19,
-// this kernel without the early loads 22, with three waves per SIMD (136
-// registers) 22.
+// this kernel without the early loads of the products 22, without those of
+// the row-local part 17, with three waves per SIMD (136 registers) 22.
 template <typename T, bool PK>
 __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
   CgCtrl* c = a.ctrl;
@@ -801,6 +802,21 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
     rn = o.r - al * sn;
   };
   double v[3] = {0.0, 0.0, 0.0};
+  // the row-local part's first rows are in flight during the products
+  const bool first = it == 0;
+  T* __restrict__ pv = (T*)a.p;
+  double* __restrict__ x = a.x;
+  const Range rows = my_range(m.n_free, vb);
+  int64_t i = rows.lo + threadIdx.x;
+  CgRec<T> o;
+  T po = T(0);
+  double xo = 0.0;
+  auto fetch = [&]() {
+    o = in[i];
+    po = first ? start_u<T>(a, i) : pv[i];
+    xo = x[i];
+  };
+  if (i < rows.hi) fetch();
   while (s < sl.hi) {
     T acc = T(0);
     auto add = [&](T k, const CgRec<T>& o) {
@@ -844,19 +860,16 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
     s += nsub;
     if (s < sl.hi) open();
   }
-  const bool first = it == 0;
-  T* __restrict__ pv = (T*)a.p;
-  double* __restrict__ x = a.x;
-  const Range rows = my_range(m.n_free, vb);
-  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
-    const CgRec<T> o = in[i];
-    const T pi = first ? start_u<T>(a, i) : o.r * o.d + be * pv[i];
+  while (i < rows.hi) {
+    const T pi = first ? po : o.r * o.d + be * po;
     T si, ri;
     step(o, si, ri);
     pv[i] = pi;
-    x[i] += alpha * (double)pi;
+    x[i] = xo + alpha * (double)pi;
     v[0] += (double)ri * (double)ri;
     v[1] += (double)ri * (double)(ri * o.d);
+    i += blockDim.x;
+    if (i < rows.hi) fetch();
   }
   block_sum<3>(v);
   if (threadIdx.x == 0) {
