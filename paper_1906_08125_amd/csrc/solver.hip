@@ -1374,17 +1374,31 @@ CoarseVecs<T> coarse_host(const AmgDev& d) {
     return CoarseVecs<T>{d.coarse_inv, d.coarse_b, d.coarse_x};
 }
 
-// Workgroups for a level kernel over the rows of M: one lane of work per
+// Workgroups of a level kernel over the rows of M: one lane of work per
 // thread (a row takes M.lpr lanes; the rows of a SELL slice share a lane
 // column), at most the solver grid, so that the small coarse passes neither
 // loop over row groups in one workgroup nor launch and drain hundreds of
 // idle workgroups.  The finest level's way up keeps the solver grid (it also
 // reduces over it).
-int amg_grid(const CgArgs& a, const SellMat& M) {
-  const int64_t lanes = M.nrows * (int64_t)M.lpr;
-  const int64_t want = (lanes + kCgBlock - 1) / kCgBlock;
-  int g = (int)std::min<int64_t>(a.G, std::max<int64_t>(8, want));
-  return g >= 8 ? g - g % 8 : g;
+int amg_grid(const CgArgs& a, int64_t lanes, int block) {
+  // (rounded up to whole rounds of the XCDs: rounded down, a few rows make
+  // every workgroup loop once more)
+  const int64_t want = (lanes + block - 1) / block;
+  const int64_t most = (int64_t)a.G * (kCgBlock / block);
+  return (int)std::min<int64_t>(most, std::max<int64_t>(8, (want + 7) / 8 * 8));
+}
+int64_t lanes_of(const SellMat& M) { return M.nrows * (int64_t)M.lpr; }
+// Threads of a level's workgroups: half as many below the finest level and in
+// the dense coarsest one, whose hundred or two hundred workgroups of kCgBlock
+// left CUs without one.  (The finest level's sum partials of the whole grid,
+// each workgroup on its own.)  With the rounding above: an AMG solve a step at
+// 40^2 x 80 4.19 -> 3.92 ms for five steps, an adjoint window at 32^2 x 64
+// 17.6 -> 15.6 ms, a cold solve at 51^2 x 102 1.81 -> 1.73 ms.
+constexpr int kAmgBlock = kCgBlock / 2;
+int amg_block(int level) { return level > 0 ? kAmgBlock : kCgBlock; }
+// one wave per row of the dense coarsest inverse
+int coarse_grid(const CgArgs& a, int64_t n_coarse) {
+  return amg_grid(a, n_coarse * 64, kAmgBlock);
 }
 
 template <typename T>
@@ -1393,22 +1407,22 @@ hipError_t amg_iters_t(const CgArgs& a, const AmgDev& d, int n, hipStream_t s) {
   const int L = d.n_levels;
   auto vec = [](const AmgLevel& lv) { return level_vecs<T>(lv); };
   const auto cv = coarse_host<T>(d);
-  // one wave per row of the dense coarsest inverse
-  const int gc = (int)std::min<int64_t>(
-      a.G, std::max<int64_t>(8, (d.n_coarse + kCgBlock / 64 - 1) / (kCgBlock / 64)));
+  const int gc = coarse_grid(a, d.n_coarse);
   for (int k = 0; k < n; ++k) {
     for (int l = 0; l < L; ++l) {
       const AmgLevel& lv = d.lv[l];
       T* nb = l + 1 < L ? vec(d.lv[l + 1]).b : cv.b;
-      hipLaunchKernelGGL(k_amg_down<T>, dim3(amg_grid(a, lv.Rs)), b, 0, s, a, lv, l, nb);
+      hipLaunchKernelGGL(k_amg_down<T>, dim3(amg_grid(a, lanes_of(lv.Rs), amg_block(l))),
+                         dim3(amg_block(l)), 0, s, a, lv, l, nb);
     }
-    hipLaunchKernelGGL(k_amg_coarse<T>, dim3(gc), b, 0, s, a, d.n_coarse, cv.inv,
+    hipLaunchKernelGGL(k_amg_coarse<T>, dim3(gc), dim3(kAmgBlock), 0, s, a, d.n_coarse, cv.inv,
                        (const T*)cv.b, cv.x);
     for (int l = L - 1; l >= 0; --l) {
       const AmgLevel& lv = d.lv[l];
       const T* y = l + 1 < L ? vec(d.lv[l + 1]).t : cv.x;
-      hipLaunchKernelGGL(k_amg_up<T>, dim3(l == 0 ? a.G : amg_grid(a, lv.A)), b, 0, s, a,
-                         lv, l, y);
+      hipLaunchKernelGGL(k_amg_up<T>,
+                         dim3(l == 0 ? a.G : amg_grid(a, lanes_of(lv.A), amg_block(l))),
+                         dim3(amg_block(l)), 0, s, a, lv, l, y);
     }
     hipLaunchKernelGGL(k_amg_spmv, dim3(a.G), b, 0, s, a);
     hipLaunchKernelGGL(k_amg_upd, dim3(a.G), b, 0, s, a);
@@ -1427,12 +1441,6 @@ hipError_t amg_launch_iters(const CgArgs& a, const AmgDev& d, int n,
 
 namespace {
 
-// Workgroups of one dense coarse solve: one wave per row.
-int coarse_grid(const CgArgs& a, int64_t n_coarse) {
-  return (int)std::min<int64_t>(
-      a.G, std::max<int64_t>(8, (n_coarse + kCgBlock / 64 - 1) / (kCgBlock / 64)));
-}
-
 // Schedule over the instances with on[i] and count(i) > 0 workgroups.
 template <typename F>
 BatchMap sched(const std::vector<char>& on, F&& count) {
@@ -1443,7 +1451,7 @@ BatchMap sched(const std::vector<char>& on, F&& count) {
     if (!on[i]) continue;
     const int c = count((int)i);
     if (c <= 0) continue;
-    m.inst[j] = (int8_t)i;
+    m.inst[j] = (int32_t)i;
     m.off[j + 1] = m.off[j] + c;
     ++j;
   }
@@ -1463,11 +1471,11 @@ hipError_t amg_batch_t(const CgArgs* dargs, const std::vector<const CgArgs*>& ha
   for (int l = 0; l < L; ++l) {
     mA[l] = sched(on, [&](int i) {
       const AmgDev& d = hier(i);
-      return l >= d.n_levels ? 0 : l == 0 ? hargs[i]->G : amg_grid(*hargs[i], d.lv[l].A);
+      return l >= d.n_levels ? 0 : l == 0 ? hargs[i]->G : amg_grid(*hargs[i], lanes_of(d.lv[l].A), amg_block(l));
     });
     mR[l] = sched(on, [&](int i) {
       const AmgDev& d = hier(i);
-      return l >= d.n_levels ? 0 : amg_grid(*hargs[i], d.lv[l].Rs);
+      return l >= d.n_levels ? 0 : amg_grid(*hargs[i], lanes_of(d.lv[l].Rs), amg_block(l));
     });
   }
   const BatchMap mC = sched(on, [&](int i) { return coarse_grid(*hargs[i], hier(i).n_coarse); });
@@ -1476,10 +1484,15 @@ hipError_t amg_batch_t(const CgArgs* dargs, const std::vector<const CgArgs*>& ha
   auto B = [&](const BatchMap& m) { return AmgBatch{dargs, m}; };
   for (int k = 0; k < n; ++k) {
     for (int l = 0; l < L; ++l)
-      if (grid(mR[l])) hipLaunchKernelGGL(k_amg_down_b<T>, dim3(grid(mR[l])), blk, 0, s, B(mR[l]), l);
-    if (grid(mC)) hipLaunchKernelGGL(k_amg_coarse_b<T>, dim3(grid(mC)), blk, 0, s, B(mC));
+      if (grid(mR[l]))
+        hipLaunchKernelGGL(k_amg_down_b<T>, dim3(grid(mR[l])), dim3(amg_block(l)), 0, s,
+                           B(mR[l]), l);
+    if (grid(mC))
+      hipLaunchKernelGGL(k_amg_coarse_b<T>, dim3(grid(mC)), dim3(kAmgBlock), 0, s, B(mC));
     for (int l = L - 1; l >= 0; --l)
-      if (grid(mA[l])) hipLaunchKernelGGL(k_amg_up_b<T>, dim3(grid(mA[l])), blk, 0, s, B(mA[l]), l);
+      if (grid(mA[l]))
+        hipLaunchKernelGGL(k_amg_up_b<T>, dim3(grid(mA[l])), dim3(amg_block(l)), 0, s,
+                           B(mA[l]), l);
     if (grid(mG)) {
       hipLaunchKernelGGL(k_amg_spmv_b, dim3(grid(mG)), blk, 0, s, B(mG));
       hipLaunchKernelGGL(k_amg_upd_b, dim3(grid(mG)), blk, 0, s, B(mG));
