@@ -81,26 +81,26 @@ def solve_bytes(info, rows, first_full=True):
     """Algorithmic HBM bytes of the solves of a run of consecutive steps of
     one pic_step call (rows: their stats).  The first solve of a call starts
     with the fused residual + field pass over phi (rows: node map, own phi,
-    charge, Neumann load, x, r, u, D^-1, E; entries: node column, K, R (3));
-    every later one with the incremental residual pass r = (b - b_prev) +
-    r_prev, which needs no product with K because phi and the field have
-    not changed since the previous solve ended: node map, charge, Neumann
-    load, b_prev and r read and written, x written, phi, D^-1, u written
-    (84 B per free row).  Where the step before needed no iteration and a
-    step follows (the lean pass), it leaves x and u to a launch made only
-    if the test asks for iterations (node map, phi, r, D^-1 read, x and u
-    written: 44 B per free row) and clears the charges it reads (60 B per
-    free row, 12 B per Dirichlet node).  Per CG iteration: the update (7
-    vector reads, 5 writes) and the K u product (column + value per entry,
-    u and w per row); a solve that iterated ends with phi = x (20 B per
-    free row) and a fused re-check pass."""
+    charge, Neumann load, x, r, E; entries: one word each, node and number of
+    the (K, R) quadruple); every later one with the incremental residual pass
+    r = (b - b_prev) + r_prev, which needs no product with K because phi and
+    the field have not changed since the previous solve ended: node map,
+    charge, Neumann load, b_prev and r read and written, phi read, x written
+    (68 B per free row).  Where the step before needed no iteration and a
+    step follows (the lean pass), it leaves x to a launch made only if the
+    test asks for iterations (node map, phi read, x written: 20 B per free
+    row) and clears the charges it reads (60 B per free row, 12 B per
+    Dirichlet node).  Per CG iteration, in one launch: a 32-byte record read
+    and written, p and x read and written, and a word for each of the seven
+    entries of a row that are not exact zeros; a solve that iterated ends
+    with phi = x (20 B per free row) and a fused re-check pass."""
     n, nnz = info["n_free"], info["nnz"]
     N, nf = info["n_nodes"], info["nnz_field"]
-    fused = 100 * n + 36 * nnz + 28 * (nf - nnz) + 40 * (N - n)
-    inc = 84 * n
+    fused = 84 * n + 4 * nnz + 28 * (nf - nnz) + 40 * (N - n)
+    inc = 68 * n
     lean = 60 * n + 12 * (N - n)
-    prep = 44 * n
-    it = 96 * n + 12 * nnz + 16 * n
+    prep = 20 * n
+    it = 96 * n + 28 * n
     total = 0
     for k, r in enumerate(rows):
         if k == 0 and first_full:

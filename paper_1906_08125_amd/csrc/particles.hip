@@ -824,6 +824,7 @@ __device__ inline void begin_body(const EmitArgs& a, VB vb) {
     if (threadIdx.x < ns) s64[threadIdx.x] = 0;
     int32_t* c32 = reinterpret_cast<int32_t*>(a.scratch);
     const int nc = (int)(sizeof(StepScratch) / sizeof(int32_t));
+    static_assert(sizeof(StepScratch) / sizeof(int32_t) <= kBeginBlock, "one word per thread");
     if (threadIdx.x < nc) c32[threadIdx.x] = 0;
     __syncthreads();
     // (the particle kernel emits; its pushing workgroups need the slot count
