@@ -553,8 +553,15 @@ __device__ inline void k_cg_scatter_body(const CgArgs& a, VB vb, int dev_gate = 
   }
   const DevMesh& m = a.m;
   const Range rows = my_range(m.n_free, vb);
-  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x)
-    a.phi[m.free2node[i]] = a.x[i];
+  // a Jacobi recursion that stopped after an even iteration has left its x to
+  // the odd one (see cg_iter); the counters tell (no launch writes them here)
+  const bool pending = !a.amg && a.ctrl->it_b > a.ctrl->it_a;
+  const double alpha = a.ctrl->alpha[0];
+  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
+    double x = a.x[i];
+    if (pending) x += alpha * (a.mixed ? (double)((const float*)a.p)[i] : a.p[i]);
+    a.phi[m.free2node[i]] = x;
+  }
 }
 
 // u = D^-1 r at the (re)start of a Jacobi recursion, from the FP64 residual
@@ -672,6 +679,7 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
       if (threadIdx.x < ns) s64[threadIdx.x] = 0;
       int32_t* c32 = reinterpret_cast<int32_t*>(a.next_scratch);
       const int nc = (int)(sizeof(StepScratch) / sizeof(int32_t));
+      static_assert(sizeof(StepScratch) / sizeof(int32_t) <= kCgBlock, "one word per thread");
       if (threadIdx.x < nc) c32[threadIdx.x] = 0;
       __syncthreads();
       if (threadIdx.x == 0) a.next_scratch->inj_base = *a.n_slots;
@@ -702,14 +710,17 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
 // writes it; the new records go to the other array.  The row-local part (p,
 // x, (r,r), (r,u)) runs over even row ranges in a second loop, so that all
 // sums keep the order, and all values the bits, of separate update and
-// product launches.
+// product launches.  x takes its share of two iterations in the odd one, which
+// reads the direction of the even one anyway (the same sums in the same
+// order): 8 bytes per row and iteration less.
 // Bound: latency of the record gathers, then the Infinity Cache.  The first
 // slice's words and records are in flight before the scalars are reduced, and
 // the first rows of the row-local part before the products.
-// An FP64 iteration on the production tip (515k rows, 64 MB) takes 16.5 us;
+// An FP64 iteration on the production tip (515k rows, 60 MB) takes 16.3 us;
 // an update launch and a product over all 15 entries per row took 14 + 19,
 // this kernel without the early loads of the products 22, without those of
-// the row-local part 17, with three waves per SIMD (136 registers) 22.
+// the row-local part 17, with x in every iteration 16.5, with three waves per
+// SIMD (136 registers) 22.
 template <typename T, bool PK>
 __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
   CgCtrl* c = a.ctrl;
@@ -755,7 +766,7 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
     const T* __restrict__ gd = sell_dict<T>(K);
     for (int k = threadIdx.x; k < kDictMax; k += blockDim.x) dict[k] = gd[k];
   }
-  double alpha, beta, gamma;
+  double alpha, beta, gamma, a_prev = 0.0;
   if (it == 0) {
     double t[2];
     totals<2>(slot(a, 2), a.G, a.G, t);
@@ -786,7 +797,7 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
       return;
     }
     const double g_prev = c->gamma[pb];
-    const double a_prev = c->alpha[pb];
+    a_prev = c->alpha[pb];
     gamma = t[1];
     beta = gamma / g_prev;
     alpha = gamma / (t[2] - beta * gamma / a_prev);
@@ -814,7 +825,7 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
   auto fetch = [&]() {
     o = in[i];
     po = first ? start_u<T>(a, i) : pv[i];
-    xo = x[i];
+    if (par) xo = x[i];
   };
   if (i < rows.hi) fetch();
   while (s < sl.hi) {
@@ -865,7 +876,7 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
     T si, ri;
     step(o, si, ri);
     pv[i] = pi;
-    x[i] = xo + alpha * (double)pi;
+    if (par) x[i] = (xo + a_prev * (double)po) + alpha * (double)pi;
     v[0] += (double)ri * (double)ri;
     v[1] += (double)ri * (double)(ri * o.d);
     i += blockDim.x;
