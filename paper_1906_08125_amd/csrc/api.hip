@@ -354,9 +354,9 @@ hipError_t solve_finish(pic_mesh* h, const fp::CgArgs& a, int spec,
       // stops inside it comes back tested.  A solve needs few AMG iterations
       // and one past the stop costs as much as a working one (40 to 60 us,
       // against 30 for a round's end and the host's wait): the rounds run 4
-      // iterations, after a speculated one 1, 2, 4; Jacobi rounds start at 8 and stop
-      // doubling at 64: a round costs the host's wait and a re-check, some
-      // 30 us, and an iteration past the stop 4.
+      // iterations, after a speculated one 1, 2, 4.  Jacobi rounds start at 8
+      // and stop doubling at 64: a round costs the host's wait and a re-check,
+      // some 30 us, and an iteration past the stop 4.
       if (a.amg)
         batch = rounds == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * batch, 4);
       else
