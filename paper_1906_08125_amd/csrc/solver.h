@@ -25,6 +25,13 @@ struct CgCtrl {
   // set by the resfield pass of a conditional re-check (1: the recursion
   // had stopped, the re-check runs) and read by the start pass after it
   int32_t rc_gate, pad;
+  // Jacobi: whether the recursion has stopped (the state is not ITER), by
+  // the parity of the iteration that reads it.  An iteration that stops the
+  // recursion, or finds it stopped, sets the other word: each wave may then
+  // act on its own reading, as nothing in its launch changes it.  (On the
+  // state itself the waves of a late workgroup could disagree, some leaving
+  // before the barriers of its sums.)
+  int32_t stop[2];
 };
 
 // Host-visible report of the control word (pinned, device-mapped memory).

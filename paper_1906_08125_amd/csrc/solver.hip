@@ -225,6 +225,7 @@ __device__ inline void ctrl_reset(CgCtrl* c) {
   z.gamma[0] = z.gamma[1] = 0.0;
   z.it_a = z.it_b = 0;
   z.rc_gate = z.pad = 0;
+  z.stop[0] = z.stop[1] = 0;
   *c = z;
 }
 
@@ -633,6 +634,7 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
     c->rstart = rn;
     const int32_t state = done ? CG_DONE : (noconv ? CG_NOCONV : CG_ITER);
     c->state = state;
+    c->stop[0] = c->stop[1] = state != CG_ITER;
     c->it_a = 0;
     if (!done && !noconv) c->restarts += 1;
     if (bn == 0.0) c->zero_rhs = 1;
@@ -724,7 +726,10 @@ __device__ inline void k_cg_start_body(const CgArgs& a, int64_t seq, VB vb,
 template <typename T, bool PK>
 __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
   CgCtrl* c = a.ctrl;
-  if (c->state != CG_ITER) return;
+  if (c->stop[par]) {
+    if (vb.id == 0 && threadIdx.x == 0) c->stop[par ^ 1] = 1;
+    return;
+  }
   const int it = par ? c->it_b : c->it_a;
   const DevMesh& m = a.m;
   const SellView& K = m.kz;
@@ -792,6 +797,7 @@ __device__ inline void cg_iter(const CgArgs& a, int par, VB vb) {
     if (recursion_stops(a, c, it, t[0])) {
       if (vb.id == 0 && threadIdx.x == 0) {
         c->state = CG_RECHECK;
+        c->stop[par ^ 1] = 1;
         c->iters_final = c->iters + it;
       }
       return;
