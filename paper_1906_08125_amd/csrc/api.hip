@@ -408,12 +408,15 @@ void* amg_alloc(void* ctx, size_t bytes) {
 }
 
 // Points a.amg at the handle's hierarchy when the parameters ask for AMG,
-// building it on first use.
+// building it on first use; else settles the form of the Jacobi iterations.
 pic_status use_precond(pic_mesh* h, const pic_solve_params* p, fp::CgArgs& a,
                        hipStream_t s, const char* who) {
   a.amg = nullptr;
   a.amg_dev = nullptr;
-  if (p->precond != PIC_PRECOND_AMG) return PIC_OK;
+  if (p->precond != PIC_PRECOND_AMG) {
+    a.split = fp::jacobi_split(a);
+    return PIC_OK;
+  }
   if (!h->amg_ready) {
     std::string msg;
     const hipError_t e = fp::amg_build(h->dm, s, amg_alloc, h, h->amg, msg);
@@ -1712,7 +1715,8 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
     // instances iterating share the V-cycle launches (as many iterations as
     // the most any of them asks for, at most 16); a single one replays its
     // own graphs.  More than two Jacobi instances share batched launches,
-    // fewer replay their own graphs.  The round ends with the conditional
+    // fewer replay their own graphs, as do those of two launches an iteration
+    // (large ones).  The round ends with the conditional
     // re-check of every instance that iterated, so one whose recursion
     // stopped inside the round comes back tested.
     auto iterate = [&](const std::vector<char>& act, uint64_t mask, int count,
@@ -1722,6 +1726,7 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       };
       std::vector<char> amg_on(n, 0), jac_on(n, 0), iterated(n, 0);
       int n_amg = 0, n_jac = 0, c_amg = 0, c_jac = 0;
+      // (n_jac and c_jac: of those that can share)
       for (int i = 0; i < n; ++i) {
         if (!act[i] || ((mask >> i) & 1ull)) continue;
         if (host_cg(i).amg) {
@@ -1730,6 +1735,7 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
           c_amg = std::max(c_amg, std::min(want(i), 16));
         } else {
           jac_on[i] = 1;
+          if (host_cg(i).split) continue;
           ++n_jac;
           c_jac = std::max(c_jac, want(i));
         }
@@ -1750,7 +1756,8 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       }
       // iterations
       for (int i = 0; i < n; ++i) {
-        const bool mine = (amg_on[i] && !amg_shared) || (jac_on[i] && !jac_shared);
+        const bool mine = (amg_on[i] && !amg_shared) ||
+                          (jac_on[i] && (!jac_shared || host_cg(i).split));
         if (!mine) continue;
         const int c = host_cg(i).amg ? std::min(want(i), 16) : want(i);
         if (c <= 0) continue;
@@ -1766,6 +1773,8 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
           if (amg_on[i]) iterated[i] = 1;
       }
       if (jac_shared && c_jac > 0) {
+        for (int i = 0; i < n; ++i)
+          if (host_cg(i).split) jac_on[i] = 0;
         fp::CgBatch ca = cb;
         ca.map = batch_map(c_cg, jac_on);
         ca.mask = 0;

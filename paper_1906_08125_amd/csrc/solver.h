@@ -18,7 +18,8 @@ struct CgCtrl {
   double rstart;        // ||r|| at the last (re)start (mixed inner target)
   double alpha[2], gamma[2];
   // iteration counters (the host does not track them).  Jacobi: the even
-  // iterations read it_a and write it_b, the odd ones the reverse; AMG: the
+  // iterations read it_a and write it_b, the odd ones the reverse (split: the
+  // updates and the products); AMG: the
   // V-cycle and the product read it_a and the update writes it.  No kernel
   // reads a counter that the same launch writes.
   int32_t it_a, it_b;
@@ -26,7 +27,8 @@ struct CgCtrl {
   // had stopped, the re-check runs) and read by the start pass after it
   int32_t rc_gate, pad;
   // Jacobi: whether the recursion has stopped (the state is not ITER), by
-  // the parity of the iteration that reads it.  An iteration that stops the
+  // the parity of the iteration that reads it (split: the updates read the
+  // first, the products the second).  A launch that stops the
   // recursion, or finds it stopped, sets the other word: each wave may then
   // act on its own reading, as nothing in its launch changes it.  (On the
   // state itself the waves of a late workgroup could disagree, some leaving
@@ -59,7 +61,7 @@ struct CgArgs {
   double* phi;            // [n_nodes] in: guess, out: solution
   void* E;                // [4 n_nodes] double (float if mixed) or null
   double *x, *r, *p;      // [n_free]
-  double *u, *w, *s;      // [n_free], AMG only (within rec0)
+  double *u, *w, *s;      // [n_free], AMG and split (within rec0)
   void* z;                // [n_free] D^-1 r in the V-cycle's arithmetic, AMG
   // Jacobi: a record (r, w, s, d) per row and its successor (d the inverse
   // diagonal), four doubles, or four floats in mixed precision
@@ -73,6 +75,7 @@ struct CgArgs {
   int mixed;
   int e32;                // E in FP32 from R in FP32 (difference form)
   double inner_tol;
+  int split;              // Jacobi: an iteration in two launches, see jacobi_split
   double* part;           // [kCgSlots][G]
   int G;                  // workgroups of every solver kernel
   // E already equals R phi for the incoming phi (the previous solve of the
@@ -133,6 +136,21 @@ __device__ inline void globalize(CgArgs& a, const CgArgs& from) {
   FP_GLOBAL(ctrl); FP_GLOBAL(amg_dev); FP_GLOBAL(report); FP_GLOBAL(dir_nodes);
   FP_GLOBAL(stats); FP_GLOBAL(step_stats); FP_GLOBAL(acc_rows); FP_GLOBAL(next_stats);
   FP_GLOBAL(next_scratch); FP_GLOBAL(n_slots); FP_GLOBAL(clear_charge);
+}
+
+// Whether a Jacobi solve takes two launches per iteration, the updates and
+// the product, instead of one in which every row forms its neighbours' new u
+// from their records.  The one launch gathers 32 bytes per entry where the
+// product gathers 8.  Packed matrices (7 entries per row on the lattices) and
+// FP32 records gain by it at every size; an FP64 matrix in plain form with 15
+// entries per row gains a launch up to the size at which an XCD's share of
+// the records no longer stays in its L2 (moved lattices, cold solves in one
+// launch and in two: 128k rows 6.1 and 7.0 ms, 281k 13.3 and 13.8, 390k 16.7
+// and 16.9, 454k 20.2 and 19.1, 524k 23.5 and 21.6, 746k 36.1 and 30.8, 1.19M
+// 85.0 and 61.1).  The same bits either way.
+constexpr int64_t kSplitRows = 400000;
+inline int jacobi_split(const CgArgs& a) {
+  return !a.m.kz.code && !a.mixed && !a.amg && a.m.n_free > kSplitRows;
 }
 
 // seq != 0: the last kernel of the launch writes the state with this

@@ -11,7 +11,8 @@
 //   start   : convergence test on that true residual; stats; when not
 //             converged, u = D^-1 r, w = K u, (r,u), (w,u)
 //   iter(i) : one iteration in one launch: its scalars, the p, s, x, r, u
-//             updates and w = K u; (r,r), (r,u), (w,u)
+//             updates and w = K u; (r,r), (r,u), (w,u); or in two, the updates
+//             and the product (see jacobi_split)
 //   scatter : phi = x on free nodes, before the re-check (a resfield pass)
 // K and R share the sparsity of the free rows, so the field of phi comes out
 // of the same pass that tests phi: when the warm start already meets the
@@ -593,8 +594,27 @@ __device__ inline void start_records(const CgArgs& a, VB vb) {
   write_partials<2>(slot(a, 2), a.G, v, vb);
 }
 
+// The same with the vectors u, w, s of an iteration in two launches.
+__device__ inline void start_vectors(const CgArgs& a, VB vb) {
+  const DevMesh& m = a.m;
+  double v[2] = {0.0, 0.0};
+  sell_rows<double>(m.kz, m.k_nslices, m.n_free, vb,
+                    [&](int32_t c) { return start_u<double>(a, c); },
+                    [](double x) { return x; },
+                    [&](int64_t i, double w) {
+                      const double u = start_u<double>(a, i);
+                      a.u[i] = u;
+                      a.w[i] = w;
+                      v[0] += a.r[i] * u;
+                      v[1] += w * u;
+                    });
+  write_partials<2>(slot(a, 2), a.G, v, vb);
+}
+
 __device__ inline void start_product(const CgArgs& a, VB vb) {
-  if (a.mixed)
+  if (a.split)
+    start_vectors(a, vb);
+  else if (a.mixed)
     start_records<float>(a, vb);
   else
     start_records<double>(a, vb);
@@ -910,6 +930,87 @@ __device__ inline void k_cg_iter_body(const CgArgs& a, int par, VB vb) {
   }
 }
 
+// An iteration in two launches, the same operations in the same order: the
+// update of p, s, x, r and u, then w = K u.  The update reads it_a and its
+// stop word and writes it_b, the product the reverse.  Bound: the vectors'
+// and the matrix's bytes.
+__device__ inline void jacobi_update(const CgArgs& a, VB vb) {
+  CgCtrl* c = a.ctrl;
+  if (c->stop[0]) {
+    if (vb.id == 0 && threadIdx.x == 0) c->stop[1] = 1;
+    return;
+  }
+  const int it = c->it_a, par = it & 1;
+  double alpha, beta, gamma;
+  if (it == 0) {
+    double t[2];
+    totals<2>(slot(a, 2), a.G, a.G, t);
+    gamma = t[0];
+    alpha = gamma / t[1];
+    beta = 0.0;
+  } else {
+    const int pb = par ^ 1;
+    const double g_prev = c->gamma[pb], a_prev = c->alpha[pb];
+    double t[2], tw[1];
+    totals<2>(slot(a, 4 + 2 * pb), a.G, a.G, t);
+    totals<1>(slot(a, 8 + pb), a.G, 1, tw);
+    if (recursion_stops(a, c, it, t[0])) {
+      if (vb.id == 0 && threadIdx.x == 0) {
+        c->state = CG_RECHECK;
+        c->stop[1] = 1;
+        c->iters_final = c->iters + it;
+      }
+      return;
+    }
+    gamma = t[1];
+    beta = gamma / g_prev;
+    alpha = gamma / (tw[0] - beta * gamma / a_prev);
+  }
+  if (vb.id == 0 && threadIdx.x == 0) {
+    c->gamma[par] = gamma;
+    c->alpha[par] = alpha;
+    c->it_b = it;
+  }
+  const double* __restrict__ d = a.m.invdiag;
+  const Range rows = my_range(a.m.n_free, vb);
+  const bool first = it == 0;
+  double v[2] = {0.0, 0.0};
+  for (int64_t i = rows.lo + threadIdx.x; i < rows.hi; i += blockDim.x) {
+    const double pi = first ? a.u[i] : a.u[i] + beta * a.p[i];
+    const double si = first ? a.w[i] : a.w[i] + beta * a.s[i];
+    a.p[i] = pi;
+    a.s[i] = si;
+    a.x[i] += alpha * pi;
+    const double ri = a.r[i] - alpha * si;
+    a.r[i] = ri;
+    const double ui = ri * d[i];
+    a.u[i] = ui;
+    v[0] += ri * ri;
+    v[1] += ri * ui;
+  }
+  write_partials<2>(slot(a, 4 + 2 * par), a.G, v, vb);
+}
+
+__device__ inline void jacobi_product(const CgArgs& a, VB vb) {
+  CgCtrl* c = a.ctrl;
+  if (c->stop[1]) {
+    if (vb.id == 0 && threadIdx.x == 0) c->stop[0] = 1;
+    return;
+  }
+  const int it = c->it_b;
+  if (vb.id == 0 && threadIdx.x == 0) c->it_a = it + 1;
+  const DevMesh& m = a.m;
+  const double* __restrict__ u = a.u;
+  double v[1] = {0.0};
+  sell_rows<double>(m.kz, m.k_nslices, m.n_free, vb,
+                    [&](int32_t c) { return u[c]; }, [](double x) { return x; },
+                    [&](int64_t i, double w) {
+                      a.w[i] = w;
+                      v[0] += w * u[i];
+                    });
+  write_partials<1>(slot(a, 8 + (it & 1)), a.G, v, vb);
+}
+
 // Single-instance kernels.
 __global__ void __launch_bounds__(kCgBlock) k_cg_resfield(CgArgs a, int reset,
                                                          int dev_gate) {
@@ -931,6 +1032,13 @@ __global__ void __launch_bounds__(kCgBlock) k_cg_start(CgArgs a, int64_t seq,
 template <typename T, bool PK>
 __global__ void __launch_bounds__(kCgBlock, 4) k_cg_iter(CgArgs a, int par) {
   cg_iter<T, PK>(a, par, VB{(int)blockIdx.x, (int)gridDim.x});
+}
+
+__global__ void __launch_bounds__(kCgBlock) k_jacobi_update(CgArgs a) {
+  jacobi_update(a, VB{(int)blockIdx.x, (int)gridDim.x});
+}
+__global__ void __launch_bounds__(kCgBlock) k_jacobi_product(CgArgs a) {
+  jacobi_product(a, VB{(int)blockIdx.x, (int)gridDim.x});
 }
 
 __global__ void k_cg_report(CgArgs a, int64_t seq) {
@@ -1576,6 +1684,13 @@ hipError_t cg_launch_report(const CgArgs& a, int64_t seq, hipStream_t s) {
 
 hipError_t cg_launch_iters_dev(const CgArgs& a, int n, hipStream_t s) {
   if (n & 1) return hipErrorInvalidValue;
+  if (a.split) {
+    for (int k = 0; k < n; ++k) {
+      LAUNCH(k_jacobi_update, a);
+      LAUNCH(k_jacobi_product, a);
+    }
+    return hipSuccess;
+  }
   const auto kern = a.m.kz.code
                         ? (a.mixed ? k_cg_iter<float, true> : k_cg_iter<double, true>)
                         : (a.mixed ? k_cg_iter<float, false> : k_cg_iter<double, false>);
