@@ -23,7 +23,7 @@ namespace {
 
 constexpr int kMB = 256;       // threads per workgroup
 constexpr int kMaxG = 1024;    // workgroups of the row-loop kernels
-constexpr int kMaxS = 1024;    // workgroups of an iteration (a row per thread)
+constexpr int kMaxS = 1024;    // workgroups of an iteration, at most
 // CG iterations before the first host check and between the later ones
 // (both even: see k_cg_iter)
 constexpr int kChunk = 24;
@@ -576,6 +576,7 @@ struct MetalImpl {
   MetalCtrl* ctrl = nullptr;
   MetalCtrl* hctrl = nullptr;   // pinned host mirror
   int G = 1;
+  int slots = 8;   // workgroups of k_cg_iter resident at once (a multiple of 8)
   // kChunk and kChunkBig CG iterations captured once per handle (their
   // kernels read every per-solve value from the control word)
   hipGraph_t graph = nullptr, graph_big = nullptr;
@@ -769,6 +770,11 @@ pic_status metal_build(const pic_metal_desc* d, hipStream_t s, pic_metal** out,
   if (e == hipSuccess) e = hipMemcpyAsync(&nbad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   M.G = (int)std::min<int64_t>(kMaxG, std::max<int64_t>(1, (n + kMB - 1) / kMB));
+  int dev = 0, n_cu = 0;
+  if (e == hipSuccess) e = hipGetDevice(&dev);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  M.slots = std::max(8, std::min(kMaxS, 2 * n_cu) / 8 * 8);
   if (e != hipSuccess) {
     *err = std::string("metal_create: ") + hipGetErrorString(e);
     metal_free(h);
@@ -806,8 +812,14 @@ CgArgsM cg_args(MetalImpl& M, double dir_value, double tol) {
   a.x = M.x; a.r = M.r; a.z = M.z; a.p = M.p; a.part = M.part;
   a.rec[0] = M.rec[0]; a.rec[1] = M.rec[1];
   a.ctrl = M.ctrl; a.G = M.G;
-  // a row per thread (4 slices per workgroup), a multiple of the 8 XCDs
-  a.Gs = (int)std::min<int64_t>(kMaxS, ((M.n + kMB - 1) / kMB + 7) / 8 * 8);
+  // One resident round of workgroups, every wave of as many slices as the
+  // others, in a multiple of the 8 XCDs.  (A row per thread in up to 1024
+  // workgroups leaves the last round, or half of the waves, empty: solves and
+  // heat step of 131k rows 9.2 ms so and 8.8 in one round, 185k 13.0 and
+  // 10.2, 269k 16.8 and 13.6, 1.3M 92 and 89.)
+  const int64_t ns = (M.n + 63) / 64, waves = kMB / 64;
+  const int64_t trips = (ns + waves * M.slots - 1) / (waves * M.slots);
+  a.Gs = (int)((ns + waves * trips - 1) / (waves * trips) + 7) / 8 * 8;
   return a;
 }
 
