@@ -549,9 +549,7 @@ PIC_API pic_status heat_step(pic_metal* metal, const pic_heat_params* params,
 typedef struct pic_batch pic_batch;
 
 typedef struct {
-  int32_t push_blocks[PIC_MAX_BATCH];   /* live-particle workgroups, 8..push max   */
-                                        /* (in proportion: a launch that would    */
-                                        /* not fill the chip gets more of each)   */
+  int32_t push_blocks[PIC_MAX_BATCH];   /* live-particle workgroups, 8..push max  */
   int32_t inject_blocks[PIC_MAX_BATCH]; /* injection workgroups, 8..inject max    */
   int32_t cg_blocks[PIC_MAX_BATCH];     /* solver workgroups, 8..cg max           */
   int32_t clear_blocks[PIC_MAX_BATCH];  /* step-start workgroups (>= 8)           */

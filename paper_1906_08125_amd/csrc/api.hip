@@ -1525,24 +1525,6 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
         fb > h->grid_fb)
       return fail(PIC_E_ARG, "pic_batch_step: schedule beyond the instance's limits");
   }
-  // A push launch that leaves compute units without a workgroup: every
-  // instance's push count grows alike until one resident round is filled,
-  // within its limit (a schedule of 4,096 slots per workgroup gave six
-  // instances of 15k to 150k superparticles 176 workgroups of up to sixteen
-  // slots per thread, one after another: 447 us per launch).  The counts
-  // only split the slots, so the results do not depend on them.
-  {
-    int64_t push = 0, inj = 0;
-    for (int i = 0; i < n; ++i) {
-      push += c_push[i];
-      inj += c_inj[i];
-    }
-    const int64_t room = 4 * (int64_t)b->h[0]->n_cu - inj - round8(n);
-    if (push < room)
-      for (int i = 0; i < n; ++i)
-        c_push[i] = (int)std::min<int64_t>(b->h[i]->grid_push - b->h[i]->grid_push % 8,
-                                           c_push[i] * room / push / 8 * 8);
-  }
   hipStream_t s = (hipStream_t)stream;
   for (int i = 0; i < n; ++i) {
     hipError_t e = ensure_capacity(b->h[i], P[i].capacity, prm[i].resort_every > 0,

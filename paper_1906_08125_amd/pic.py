@@ -754,9 +754,10 @@ def window_objective(E0, s, window: Window, wQ=1.0, wE=1.0):
 class Batch:
     """Instances (Mesh, State, per-instance step keywords) advanced together
     by pic_batch_step.  The schedule gives each instance a number of
-    workgroups per kernel from its size: live particles per push workgroup
-    (push_tile) and free rows per solver workgroup (cg_rows);
-    `autotune` picks these two from measured step times."""
+    workgroups per kernel from its size: at most so many live particles per
+    push workgroup (push_tile; more workgroups where the chip has room) and
+    free rows per solver workgroup (cg_rows); `autotune` picks these two from
+    measured step times."""
 
     def __init__(self, meshes, states, params):
         torch = _torch()
@@ -770,6 +771,9 @@ class Batch:
         self._h = h
         _open_handles.add(self)
         self.limits = np.array(list(lim), dtype=np.int64).reshape(n, 4)
+        self._most = [[int(v) // 8 * 8 for v in row] for row in self.limits]
+        self.cus = torch.cuda.get_device_properties(
+            torch.cuda.current_device()).multi_processor_count
         self.push_tile, self.cg_rows = 4096, 1024
         self.inject_blocks, self.clear_blocks, self.fallback_blocks = 16, 16, 8
         self.tuning = []
@@ -796,18 +800,31 @@ class Batch:
         cr = cg_rows or self.cg_rows
         sc = BatchSchedule()
         r8 = lambda x: max(8, (int(x) + 7) // 8 * 8)
+        push, inject = [], 0
         for i, (m, st) in enumerate(zip(self.meshes, self.states)):
             live = int(st.n_slots.item())
-            lim = self.limits[i]
-            sc.push_blocks[i] = min(r8(-(-live // pt)), int(lim[0]) // 8 * 8)
-            sc.inject_blocks[i] = min(r8(self.inject_blocks), int(lim[1]) // 8 * 8)
+            lim = self._most[i]
+            push.append(min(r8(-(-live // pt)), lim[0]))
+            sc.inject_blocks[i] = min(r8(self.inject_blocks), lim[1])
+            inject += sc.inject_blocks[i]
             # an instance whose solve iterated gets the full solver grid,
             # the others (one residual pass per step) a grid by cg_rows
-            full = int(lim[2]) // 8 * 8
+            full = lim[2]
             sc.cg_blocks[i] = full if self.last_iters[i] > 0 else min(
                 r8(-(-m.n_free // cr)), full)
             sc.clear_blocks[i] = r8(self.clear_blocks)
-        sc.fallback_blocks = min(self.fallback_blocks, int(self.limits[:, 3].min()) // 8 * 8)
+        sc.fallback_blocks = min(self.fallback_blocks, *(lim[3] for lim in self._most))
+        # Push counts that leave compute units without a workgroup grow alike
+        # until one resident round (four per CU, the emitting and injecting
+        # ones included) is filled, each within its limit: with 4,096 slots
+        # per workgroup six instances of 15k to 150k superparticles had 176
+        # workgroups of up to sixteen slots per thread, one after another,
+        # and a launch took 447 us instead of 53.
+        room = 4 * self.cus - inject - r8(len(push))
+        if 0 < sum(push) < room:
+            grow = room / sum(push)
+            push = [min(lim[0], int(c * grow) // 8 * 8) for c, lim in zip(push, self._most)]
+        sc.push_blocks[:len(push)] = push
         return sc
 
     def step(self, step0, n_steps=1, sched=None, stats=None):
