@@ -1603,30 +1603,45 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
   // The particle kernels of step k for the instances in on: those without
   // packed tet records, then those that have them; then the exact fallback.
   // (The counter rows are summed by the first pass of the step's solve.)
-  auto particles = [&](int32_t k, const std::vector<char>& on) {
+  // Timing: ev[j] receives launch j's place in the event list (-1: not timed);
+  // one that is marked in counted is timed without counting it again.
+  struct Launches {
+    int ev[3] = {-1, -1, -1};
+    bool counted[3] = {false, false, false};
+  };
+  const std::vector<char> all(n, 1);
+  std::vector<char> form[2] = {std::vector<char>(n), std::vector<char>(n)};
+  for (int i = 0; i < n; ++i) form[b->h[i]->dm.tc != nullptr][i] = 1;
+  auto particles = [&](int32_t k, const std::vector<char>& on, Launches& L) {
     char* base = (char*)b->d_args + per * k;
     const fp::StepArgs* A = (const fp::StepArgs*)base;
     const fp::EmitArgs* E = (const fp::EmitArgs*)(base + sa * n);
     hipError_t r;
+    auto begin = [&](int j, int cls) {
+      const int at = (int)h0->ev_class.size();
+      prof_begin(h0, L.counted[j] ? cls | kProfNoCount : cls, s);
+      L.ev[j] = h0->prof_open ? at : -1;
+    };
     bool any = false;
     for (int pk = 0; pk < 2; ++pk) {
       std::vector<char> sel(n);
-      for (int i = 0; i < n; ++i) sel[i] = on[i] && (b->h[i]->dm.tc != nullptr) == (pk == 1);
+      for (int i = 0; i < n; ++i) sel[i] = on[i] && form[pk][i];
       const fp::BatchMap m = batch_map(c_part, sel);
       if (m.n_seg == 0) continue;
       any = true;
-      prof_begin(h0, PIC_K_PUSH, s);
+      begin(pk, PIC_K_PUSH);
       if ((r = fp::launch_particles_b(A, E, m, f32 ? 1 : 0, pk, s)) != hipSuccess) return r;
       prof_end(h0, s);
     }
     if (!any) return hipSuccess;
     const fp::BatchMap m = batch_map(c_fb, on);
-    prof_begin(h0, PIC_K_FALLBACK, s);
+    begin(2, PIC_K_FALLBACK);
     if ((r = fp::launch_fallback_b(A, m, m.off[m.n_seg], s)) != hipSuccess) return r;
     prof_end(h0, s);
     return hipSuccess;
   };
   std::vector<char> todo(n, 1);
+  Launches due_now;  // of the step at hand, as far as they ran ahead
   for (int32_t k = 0; k < n_steps; ++k) {
     char* base = (char*)b->d_args + per * k;
     if (k == 0) {
@@ -1637,7 +1652,7 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       prof_end(h0, s);
     }
     // (the instances whose kernels were not let through, see ahead)
-    if ((e = particles(k, todo)) != hipSuccess)
+    if ((e = particles(k, todo, due_now)) != hipSuccess)
       return hip_fail(e, "pic_batch_step particles");
     // the re-sorts due, in shared launches, then their collisions: before
     // the solves (which touch the charge alone), so that the next step's
@@ -1787,15 +1802,24 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
     // when each step began with launches of its own for clears, emission,
     // counters and reports: 1190 with those in the particle and solver
     // kernels, as in pic_step, and the launches ahead.)
-    const std::vector<char> all(n, 1);
-    if (k + 1 < n_steps && (e = particles(k + 1, all)) != hipSuccess)
+    Launches ahead;
+    if (k + 1 < n_steps && (e = particles(k + 1, all, ahead)) != hipSuccess)
       return hip_fail(e, "pic_batch_step particles");
-    prof_begin(h0, PIC_K_SOLVE, s);
     if ((e = batch_wait(b, seq, s)) != hipSuccess)
       return hip_fail(e, "pic_batch_step solve");
     for (int i = 0; i < n; ++i) {
       const int32_t st = b->h[i]->cg_report_host->state;
       todo[i] = st != fp::CG_DONE && st != fp::CG_NOCONV;
+    }
+    // a launch ahead that let no instance through is not timed; one that let
+    // some through counts, and the others' launch only adds its time to it
+    due_now = Launches{};
+    for (int j = 0; j < 3; ++j) {
+      if (ahead.ev[j] < 0) continue;
+      const std::vector<char>& of = j < 2 ? form[j] : all;
+      for (int i = 0; i < n; ++i)
+        due_now.counted[j] = due_now.counted[j] || (of[i] && !todo[i]);
+      if (!due_now.counted[j]) h0->ev_class[ahead.ev[j]] = -1;
     }
     // later rounds: Jacobi 8, 16, 32, ... iterations; AMG (an iteration past
     // the stop costs as much as a working one) 1, 2, 4 after a speculated
@@ -1815,14 +1839,16 @@ pic_status pic_batch_step(pic_batch* b, const pic_particles* P,
       batch = batch < 8 ? 8 : std::min(2 * batch, 256);
       if (mask) batch = std::min(batch, 16);
       amg_batch = guard == 0 ? (spec > 0 ? 1 : 4) : std::min(2 * amg_batch, 4);
+      prof_begin(h0, PIC_K_SOLVE | kProfNoCount, s);
       if ((e = iterate(active, mask, batch, amg_batch, nullptr)) != hipSuccess ||
-          (e = fp::cg_batch_report(cb, n, seq, s)) != hipSuccess ||
-          (e = batch_wait(b, seq, s)) != hipSuccess)
+          (e = fp::cg_batch_report(cb, n, seq, s)) != hipSuccess)
+        return hip_fail(e, "pic_batch_step solve");
+      prof_end(h0, s);
+      if ((e = batch_wait(b, seq, s)) != hipSuccess)
         return hip_fail(e, "pic_batch_step solve");
     }
     for (int i = 0; i < n; ++i)
       b->h[i]->step_spec = (int)std::min<int64_t>(b->h[i]->cg_report_host->iters, 256);
-    prof_end(h0, s);
   }
   return PIC_OK;
 }
