@@ -77,41 +77,67 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def solve_bytes(info, rows, first_full=True):
-    """Algorithmic HBM bytes of the solves of a run of consecutive steps of
-    one pic_step call (rows: their stats).  The first solve of a call starts
-    with the fused residual + field pass over phi (rows: node map, own phi,
-    charge, Neumann load, x, r, E; entries: one word each, node and number of
-    the (K, R) quadruple); every later one with the incremental residual pass
-    r = (b - b_prev) + r_prev, which needs no product with K because phi and
-    the field have not changed since the previous solve ended: node map,
-    charge, Neumann load, b_prev and r read and written, phi read, x written
-    (68 B per free row).  Where the step before needed no iteration and a
-    step follows (the lean pass), it leaves x to a launch made only if the
-    test asks for iterations (node map, phi read, x written: 20 B per free
-    row) and clears the charges it reads (60 B per free row, 12 B per
-    Dirichlet node).  Per CG iteration, in one launch: a 32-byte record read
-    and written, p and x read and written, and a word for each of the seven
-    entries of a row that are not exact zeros; a solve that iterated ends
-    with phi = x (20 B per free row) and a fused re-check pass."""
+def pass_bytes(info, e32=False):
+    """Algorithmic HBM bytes of the solver's passes on a lattice mesh (every
+    workload here: K and R in packed form).
+    full: the residual + field pass over phi (free rows: node map, own phi,
+    charge, Neumann load, x, b, r, E; entries: one word each, node and number
+    of the (K, R) quadruple; Dirichlet rows: R, phi, E; e32: E and R of the
+    Dirichlet rows in FP32, and the FP64 row sums of R read).
+    inc: the incremental residual r = (b - b_prev) + r_prev of a solve whose
+    phi and field have not changed since the previous one ended (node map,
+    charge, Neumann load, b_prev and r read and written, phi read, x written).
+    lean: the same where the step before needed no iteration and a step
+    follows: it leaves x to a launch made only if the test asks for
+    iterations (prep: node map, phi read, x written) and clears the charges
+    it reads.
+    iter: a Jacobi iteration, one launch: a 32-byte record read and written, p
+    and x read and written, and a word for each of the seven entries of a row
+    that are not exact zeros.
+    back: phi = x after iterations (a full pass follows)."""
     n, nnz = info["n_free"], info["nnz"]
     N, nf = info["n_nodes"], info["nnz_field"]
-    fused = 84 * n + 4 * nnz + 28 * (nf - nnz) + 40 * (N - n)
-    inc = 68 * n
-    lean = 60 * n + 12 * (N - n)
-    prep = 20 * n
-    it = 96 * n + 28 * n
+    full = (100 * n + 16 * (nf - nnz) + 24 * (N - n)) if e32 else \
+        (84 * n + 28 * (nf - nnz) + 40 * (N - n))
+    return dict(full=full + 4 * nnz,
+                inc=68 * n, lean=60 * n + 12 * (N - n), prep=20 * n,
+                iter=96 * n + 28 * n, back=20 * n)
+
+
+def solve_bytes(info, rows, first_full=True, lean=True, iterations=True, e32=False):
+    """Algorithmic HBM bytes of the solves of a run of consecutive steps of
+    one call (rows: their stats).  The first solve of a call starts with the
+    full pass, every later one with the incremental one (lean: a pic_step call,
+    whose solves may take the lean one); a solve that iterated ends with a full
+    pass.  iterations=False leaves the iterations themselves out."""
+    B = pass_bytes(info, e32)
     total = 0
     for k, r in enumerate(rows):
         if k == 0 and first_full:
-            total += fused
-        elif k > 0 and k + 1 < len(rows) and rows[k - 1]["cg_iters"] == 0:
-            total += lean + (prep if r["cg_iters"] > 0 else 0)
+            total += B["full"]
+        elif lean and k > 0 and k + 1 < len(rows) and rows[k - 1]["cg_iters"] == 0:
+            total += B["lean"] + (B["prep"] if r["cg_iters"] > 0 else 0)
         else:
-            total += inc
+            total += B["inc"]
         if r["cg_iters"] > 0:
-            total += r["cg_iters"] * it + 20 * n + fused
+            total += B["back"] + B["full"]
+            if iterations:
+                total += r["cg_iters"] * B["iter"]
     return total
+
+
+def operator_bytes(info):
+    """Bytes of a lattice mesh's operators: a word per entry of K and R on the
+    free rows and per entry of K that is not an exact zero, R of the
+    Dirichlet rows."""
+    return 4 * info["nnz"] + 28 * info["n_free"] + 28 * (info["nnz_field"] - info["nnz"])
+
+
+def metal_iter_bytes(nodes, nnz):
+    """Algorithmic bytes of one iteration of the metal solve, one launch: an
+    8-byte value and a 4-byte column per entry, and per row a 32-byte record
+    read and written, p and x read and written."""
+    return 12 * nnz + 96 * nodes
 
 
 def push_bytes(n_live, real_bytes=8):
@@ -576,14 +602,11 @@ def run_metal_leg(args):
         iters.append(sh["iters"])
     torch.cuda.synchronize()
     heat_s = (time.perf_counter() - t2) / args.metal_calls
-    # algorithmic bytes of one CG iteration: the CSR product (8-byte values
-    # and 4-byte columns per entry, the row pointers, z, r and w once) and
-    # the step's vector updates (7 vectors read, 5 written)
     e = np.sort(m.tet[:, [[0, 1], [0, 2], [0, 3], [1, 2], [1, 3], [2, 3]]]
                 .reshape(-1, 2), axis=1)
     nnz = 2 * int(np.unique(e[:, 0].astype(np.int64) * m.n_nodes + e[:, 1]).size) \
         + m.n_nodes
-    it_bytes = 12 * nnz + (4 + 32 + 96) * m.n_nodes
+    it_bytes = metal_iter_bytes(m.n_nodes, nnz)
     out = dict(nodes=m.n_nodes, tets=m.n_tets, interface_faces=m.n_faces,
                nnz=nnz, cg_bytes_per_iter=it_bytes,
                cg_GBps_wall=round(it_bytes * st["iters"] / cont_s / 1e9, 1),
@@ -709,21 +732,15 @@ def run_batch_leg(args):
     pushes = sum(x["n_before"] + x["n_inj"] for r in rows for x in r)
     # algorithmic bytes of the timed batch steps: the particle streams (64 B
     # per superparticle in mixed precision) and, per instance, the solver
-    # passes that ran (the fused residual + field pass of the call's first
-    # step, the incremental residual pass after it, a re-check pass after
-    # iterations); the V-cycle iterations themselves (a few per step over
+    # passes that ran; the V-cycle iterations themselves (a few per step over
     # all instances) are not counted, so the figure is a lower bound
     algo = 0.0
     for i, m in enumerate(meshes):
         ri = [r[i] for r in rows]
         algo += sum(push_bytes(x["n_before"] + x["n_inj"], 4) for x in ri)
-        inf = m.info
-        n, nnz, N, nf = inf["n_free"], inf["nnz"], inf["n_nodes"], inf["nnz_field"]
-        fused = 100 * n + 36 * nnz + 28 * (nf - nnz) + 40 * (N - n)
-        algo += fused + 84 * n * (len(ri) - 1)
-        algo += sum(20 * n + fused for x in ri if x["cg_iters"] > 0)
+        algo += solve_bytes(m.info, ri, lean=False, iterations=False, e32=True)
     batch_gbps = algo / t_batch / 1e9
-    csr_bytes = sum(12 * m.info["nnz"] + 36 * (m.info["nnz_field"]) for m in meshes)
+    csr_bytes = sum(operator_bytes(m.info) for m in meshes)
     live_b = sum(x["n_after"] for x in rows[-1])
     batch.close()
     del sts
