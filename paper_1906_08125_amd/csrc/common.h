@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "../../include/femocs_pic.h"
+#include "handover.h"
 
 namespace fp {
 
@@ -521,13 +522,6 @@ __device__ inline void step_counter_sum(const int64_t* rows, int n_rows,
 }
 
 // Internal per-handle device scratch layout (counters and scalars).
-// The running sums of a step's emission, in the order of the faces, after
-// one trip of its workgroups (flag: that trip's number plus one).
-struct EmitSums {
-  long long offset, n_clamp;
-  double cur, F_sum, F_max;
-  int32_t flag, pad;
-};
 constexpr int kEmitters = 8;  // emitting workgroups of a particle launch, at most
 
 struct StepScratch {
@@ -539,7 +533,7 @@ struct StepScratch {
   int32_t n_live;
   int32_t emitted;  // emitting workgroups whose counts and offsets are out
   int32_t pad[2];
-  EmitSums sums[kEmitters];
+  EmitSlot sums[kEmitters];
 };
 
 }  // namespace fp

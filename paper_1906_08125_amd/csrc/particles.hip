@@ -640,44 +640,9 @@ __device__ inline void face_field(const DevMesh& m, const void* E, int f32,
 template <bool PUB>
 __device__ inline void emit_put(int32_t* p, int32_t v) {
   if (PUB)
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    dev_put(p, v);
   else
     *p = v;
-}
-
-__device__ inline int32_t emit_get(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// What workgroup t of T hands to the next trip and takes from the one
-// before (one lane): stored and loaded past the caches, the flag last.
-__device__ inline void sums_put(EmitSums* p, const EmitSums& v, int32_t flag) {
-  const unsigned long long* w = reinterpret_cast<const unsigned long long*>(&v);
-  unsigned long long* o = reinterpret_cast<unsigned long long*>(p);
-#pragma unroll
-  for (int k = 0; k < 5; ++k)
-    __hip_atomic_store(o + k, w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __builtin_amdgcn_s_waitcnt(0);
-  __hip_atomic_store(&p->flag, flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// A wait is bounded: a flag not seen in time (never expected) ends it.
-constexpr int kEmitSpin = 1 << 22;
-
-__device__ inline bool sums_get(EmitSums* p, EmitSums& v, int32_t flag) {
-  for (int it = 0; it < kEmitSpin; ++it) {
-    if (emit_get(&p->flag) == flag) {
-      unsigned long long* w = reinterpret_cast<unsigned long long*>(&v);
-      unsigned long long* o = reinterpret_cast<unsigned long long*>(p);
-#pragma unroll
-      for (int k = 0; k < 5; ++k)
-        w[k] = __hip_atomic_load(o + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return true;
-    }
-    __builtin_amdgcn_s_sleep(1);
-  }
-  v = EmitSums{};  // (offsets stay within the arrays)
-  return false;
 }
 
 // Workgroup t of T: the faces are taken NT to a trip, the trips by the
@@ -1048,7 +1013,7 @@ template <bool PK>
 __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
                                    int G, Acc& acc, ChargeTable& T) {
   const DevMesh& m = a.m;
-  const int64_t n = emit_get(&a.scratch->inj_fit);
+  const int64_t n = dev_get(&a.scratch->inj_fit);
   const int64_t base = a.scratch->inj_base;
   const double dt = a.dt;
   // the offsets for the search of a slot's face: in LDS where they fit (ten
@@ -1058,10 +1023,10 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
   const bool in_lds = m.n_emit <= kEmitLds;
   if (g * (int64_t)blockDim.x >= n) return;  // (the whole workgroup)
   if (in_lds) {
-    for (int f = threadIdx.x; f < (int)m.n_emit; f += blockDim.x) s_off[f] = emit_get(off + f);
+    for (int f = threadIdx.x; f < (int)m.n_emit; f += blockDim.x) s_off[f] = dev_get(off + f);
     __syncthreads();
   }
-  auto at = [&](int f) { return in_lds ? s_off[f] : emit_get(off + f); };
+  auto at = [&](int f) { return in_lds ? s_off[f] : dev_get(off + f); };
   for (int64_t s = g * (int64_t)blockDim.x + threadIdx.x; s < n;
        s += (int64_t)G * blockDim.x) {
     // face: last f with off[f] <= s
@@ -1148,13 +1113,11 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
 // offsets and publish them; the injecting workgroups (dispatched last) wait
 // until all have.  The waits are bounded: a flag not seen in time (never
 // expected) skips the injection and marks the step with a device error.
-// What is published (the sums, the offsets and inj_fit) is stored and loaded
-// with device-scope atomics, which go past the per-XCD caches, and each
-// wave's stores are complete before the barrier ahead of the count: neither
-// side needs a fence, which would write back or invalidate an L2 that the
-// pushing workgroups are using (the waiting side did so at every poll).  With
-// the offsets searched in LDS, the particle kernel of a small step (10k
-// superparticles, 276 emitting faces) went from 40 to 30 us.  A trip of 256
+// What is published (the sums, the offsets and inj_fit) goes past the caches
+// (see handover.h), each wave's stores ahead of the barrier before the count.
+// With fences of device scope instead, and the offsets not searched in LDS,
+// the particle kernel of a small step (10k superparticles, 276 emitting faces)
+// took 40 us, 30 so.  A trip of 256
 // faces takes 7 to 10 us, most of it dependent loads: one workgroup taking
 // the trips in turn published 612 faces after 31 us, eight at once after 19.
 __device__ inline int emitters(const DevMesh& m) {
@@ -1165,7 +1128,7 @@ __device__ inline int emitters(const DevMesh& m) {
 __device__ inline void emit_publish(const EmitArgs& e, int t, int T) {
   if (t >= T) return;
   emit_block<kBlock, true>(e, t, T);
-  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have arrived
+  hand_over();
   __syncthreads();
   if (threadIdx.x == 0)
     __hip_atomic_fetch_add(&e.scratch->emitted, 1, __ATOMIC_RELAXED,
@@ -1177,12 +1140,13 @@ __device__ inline bool emit_wait(const StepArgs& a, int T) {
   if (threadIdx.x == 0) {
     int ok = 0;
     for (int it = 0; it < kEmitSpin; ++it) {
-      if (emit_get(&a.scratch->emitted) == T) {
+      if (dev_get(&a.scratch->emitted) == T) {
         ok = 1;
         break;
       }
       __builtin_amdgcn_s_sleep(20);  // (128 workgroups poll one word)
     }
+    take_over();
     if (!ok && a.stats) a.stats->status = PIC_E_DEVICE;
     seen = ok;
   }
