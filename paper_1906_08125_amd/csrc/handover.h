@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/femocs_pic.h"
+
 namespace fp {
 
 template <typename T>
@@ -33,9 +35,10 @@ __device__ inline void take_over() {
 }
 
 // The running sums of a step's emission, in the order of the faces, after
-// one trip of its workgroups.
+// one trip of its workgroups (lost: without those of a trip that was waited
+// for in vain).
 struct EmitSums {
-  long long offset, n_clamp;
+  long long offset, n_clamp, lost;
   double cur, F_sum, F_max;
 };
 // The same in memory, with that trip's number plus one as the flag.
@@ -58,21 +61,41 @@ __device__ inline void sums_put(EmitSlot* p, const EmitSums& v, int32_t flag) {
 // A wait is bounded: a flag not seen in time (never expected) ends it.
 constexpr int kEmitSpin = 1 << 22;
 
-// What a trip takes from the one before (one lane).
-__device__ inline bool sums_get(const EmitSlot* p, EmitSums& v, int32_t flag) {
-  for (int it = 0; it < kEmitSpin; ++it) {
+// What a trip takes from the one before (one lane); lost when it does not
+// come.
+__device__ inline void sums_get(const EmitSlot* p, EmitSums& v, int32_t flag,
+                                int spin = kEmitSpin) {
+  for (int it = 0; it < spin; ++it) {
     if (dev_get(&p->flag) == flag) {
       take_over();
       unsigned long long w[kEmitWords];
 #pragma unroll
       for (int k = 0; k < kEmitWords; ++k) w[k] = dev_get(p->word + k);
       __builtin_memcpy(&v, w, sizeof v);
-      return true;
+      return;
     }
     __builtin_amdgcn_s_sleep(1);
   }
   v = EmitSums{};  // (offsets stay within the arrays)
-  return false;
+  v.lost = 1;
+}
+
+// What a step injects, by the sums of all its trips: total superparticles, of
+// which fit have a slot behind the base slots in use.  After a lost trip the
+// offsets of the faces are not those of one scan, so nothing is injected.
+struct EmitEnd {
+  long long total, fit;
+  int32_t status;
+};
+__host__ __device__ inline EmitEnd emit_end(const EmitSums& sum, long long base,
+                                            long long capacity) {
+  EmitEnd e;
+  e.total = sum.lost ? 0 : sum.offset;
+  e.fit = capacity - base;
+  if (e.fit > e.total) e.fit = e.total;
+  if (e.fit < 0) e.fit = 0;
+  e.status = sum.lost ? PIC_E_DEVICE : e.total > e.fit ? PIC_E_CAPACITY : PIC_OK;
+  return e;
 }
 
 }  // namespace fp

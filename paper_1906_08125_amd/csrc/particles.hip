@@ -720,9 +720,8 @@ __device__ void emit_block(const EmitArgs& a, int t, int T) {
       s_red[2][wave] = v2;
       s_cl[wave] = vc;
     }
-    if (T > 1 && k > 0 && threadIdx.x == 0 &&
-        !sums_get(a.scratch->sums + (k - 1) % T, s_sums, k) && a.stats)
-      a.stats->status = PIC_E_DEVICE;
+    if (T > 1 && k > 0 && threadIdx.x == 0)
+      sums_get(a.scratch->sums + (k - 1) % T, s_sums, k);
     __syncthreads();
     if (T > 1 && k > 0) sum = s_sums;
     const long long offset = sum.offset;
@@ -745,7 +744,6 @@ __device__ void emit_block(const EmitArgs& a, int t, int T) {
   }
   // the workgroup of the last trip ends the emission
   if (threadIdx.x == 0 && t == (trips > 0 ? (trips - 1) % T : 0)) {
-    const long long offset = sum.offset;
     if (a.rate) *a.rate = sum.cur;
     if (a.stats) {
       pic_step_stats* st = a.stats;
@@ -755,19 +753,17 @@ __device__ void emit_block(const EmitArgs& a, int t, int T) {
       st->n_clamp = sum.n_clamp;
     }
     if (a.counts) {
-      emit_put<PUB>(a.offsets + m.n_emit, (int32_t)offset);
       const long long base = *a.n_slots;
-      long long fit = a.capacity - base;
-      if (fit > offset) fit = offset;
-      if (fit < 0) fit = 0;
+      const EmitEnd end = emit_end(sum, base, a.capacity);
+      emit_put<PUB>(a.offsets + m.n_emit, (int32_t)end.total);
       a.scratch->inj_base = (int32_t)base;
-      a.scratch->inj_total = (int32_t)offset;
-      emit_put<PUB>(&a.scratch->inj_fit, (int32_t)fit);
-      *a.n_slots = (int32_t)(base + fit);
+      a.scratch->inj_total = (int32_t)end.total;
+      emit_put<PUB>(&a.scratch->inj_fit, (int32_t)end.fit);
+      *a.n_slots = (int32_t)(base + end.fit);
       if (a.stats) {
-        a.stats->n_trunc = offset - fit;
-        if (offset > fit) a.stats->status = PIC_E_CAPACITY;
-        a.stats->n_slots = base + fit;
+        a.stats->n_trunc = end.total - end.fit;
+        if (end.status != PIC_OK) a.stats->status = end.status;
+        a.stats->n_slots = base + end.fit;
       }
     }
   }
@@ -1109,8 +1105,8 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
 
 // The emission of the step computed inside the particle kernel: the first
 // workgroups (dispatched first, so resident before any workgroup that waits
-// for them; each waits for an earlier one alone) compute the counts and
-// offsets and publish them; the injecting workgroups (dispatched last) wait
+// for them) compute the counts and offsets and publish them; the injecting
+// workgroups (dispatched last) wait
 // until all have.  The waits are bounded: a flag not seen in time (never
 // expected) skips the injection and marks the step with a device error.
 // What is published (the sums, the offsets and inj_fit) goes past the caches

@@ -1,7 +1,8 @@
-"""The hand-over of data between workgroups of a launch (csrc/handover.h), in
+"""The hand-over of data between workgroups of a launch (csrc/handover.h).  In
 the intermediate code that the compiler makes of it for gfx950: the data's
 stores, a release fence, the wait, a release fence, then the flag; and behind
-the flag's load an acquire fence before the data's loads."""
+the flag's load an acquire fence before the data's loads.  On the host, in a
+build of its own: what a step injects by its sums, none when a trip was lost."""
 import os
 import re
 import subprocess
@@ -15,7 +16,8 @@ KERNELS = """
 __global__ void put(fp::EmitSlot* p, fp::EmitSums v, int flag) { fp::sums_put(p, v, flag); }
 __global__ void get(const fp::EmitSlot* p, fp::EmitSums* v, int flag) {
   fp::EmitSums s;
-  if (fp::sums_get(p, s, flag)) *v = s;
+  fp::sums_get(p, s, flag);
+  *v = s;
 }
 """
 
@@ -47,11 +49,42 @@ def code(tmp_path_factory):
 
 
 def test_put(code):
-    assert code["put"] == ["store i64"] * 5 + ["release", "wait", "release", "store i32"]
+    assert code["put"] == ["store i64"] * 6 + ["release", "wait", "release", "store i32"]
 
 
 def test_get(code):
     """(the wait's loop may lie around the rest in the text)"""
     ops = code["get"]
     assert ops[0] == "load i32"
-    assert [o for o in ops if o != "load i32"] == ["acquire"] + ["load i64"] * 5
+    assert [o for o in ops if o != "load i32"] == ["acquire"] + ["load i64"] * 6
+
+
+END = """
+#include <cstdio>
+#include "handover.h"
+int main() {
+  const long long cases[][4] = {  // offset, lost, base, capacity
+      {5, 0, 10, 100}, {5, 0, 97, 100}, {5, 0, 100, 100}, {0, 0, 0, 100}, {5, 0, 101, 100},
+      {5, 1, 10, 100}, {5, 1, 99, 100}, {0, 1, 0, 100}};
+  for (const auto& c : cases) {
+    fp::EmitSums s{};
+    s.offset = c[0];
+    s.lost = c[1];
+    const fp::EmitEnd e = fp::emit_end(s, c[2], c[3]);
+    std::printf("%lld %lld %d\\n", e.total, e.fit, (int)e.status);
+  }
+}
+"""
+
+
+def test_what_is_injected(tmp_path):
+    from paper_1906_08125_amd import pic
+    src, exe = tmp_path / "end.hip", tmp_path / "end"
+    src.write_text(END)
+    subprocess.run([B.hipcc(), "-O1", "-std=c++17", f"--offload-arch={B.ARCH}", f"-I{B.CSRC}",
+                    str(src), "-o", str(exe)], check=True, capture_output=True, timeout=120)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60)
+    got = [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
+    ok, full, dev = pic.PIC_OK, pic.PIC_E_CAPACITY, pic.PIC_E_DEVICE
+    assert got == [(5, 5, ok), (5, 3, full), (5, 0, full), (0, 0, ok), (5, 0, full),
+                   (0, 0, dev), (0, 0, dev), (0, 0, dev)]
