@@ -1103,26 +1103,35 @@ __device__ inline void inject_role(const StepArgs& a, const MapTable* M, int g,
   }
 }
 
-// The emission of the step computed inside the particle kernel: the first
-// workgroups (dispatched first, so resident before any workgroup that waits
-// for them) compute the counts and offsets and publish them; the injecting
-// workgroups (dispatched last) wait
-// until all have.  The waits are bounded: a flag not seen in time (never
-// expected) skips the injection and marks the step with a device error.
+// The emission of the step computed inside the particle kernel: emitting
+// workgroups compute the counts and offsets and publish them; the injecting
+// workgroups (dispatched last) wait until all have.  The waits are bounded: a
+// flag not seen in time (never expected) skips the injection and marks the
+// step with a device error.
+// The emitting workgroups are blocks 0, 8, 16, ... of a launch: all on the XCD
+// of block 0, which takes its blocks in order, ahead of any block there that
+// waits.  So wherever a waiting block holds a place of that XCD, the blocks it
+// waits for have theirs, and launches of several streams cannot wait for one
+// another's places.  (Spread over the XCDs, each of two launches could fill an
+// XCD with waiting blocks while the other's emitting block for it had no
+// place: two batches of 64 instances at 16 injecting blocks have 128 of them
+// per XCD, as many as it has places.)  The seven blocks between two of them
+// end at once.
 // What is published (the sums, the offsets and inj_fit) goes past the caches
 // (see handover.h), each wave's stores ahead of the barrier before the count.
 // With fences of device scope instead, and the offsets not searched in LDS,
 // the particle kernel of a small step (10k superparticles, 276 emitting faces)
-// took 40 us, 30 so.  A trip of 256
-// faces takes 7 to 10 us, most of it dependent loads: one workgroup taking
-// the trips in turn published 612 faces after 31 us, eight at once after 19.
-__device__ inline int emitters(const DevMesh& m) {
+// took 40 us, 30 so.  A trip of 256 faces takes 7 to 10 us, most of it
+// dependent loads: one workgroup taking the trips in turn published 612 faces
+// after 31 us, eight at once after 19.
+constexpr int kXcds = 8;
+
+__host__ __device__ inline int emitters(const DevMesh& m) {
   const int64_t trips = (m.n_emit + kBlock - 1) / kBlock;
   return trips < 1 ? 1 : (trips < kEmitters ? (int)trips : kEmitters);
 }
 
 __device__ inline void emit_publish(const EmitArgs& e, int t, int T) {
-  if (t >= T) return;
   emit_block<kBlock, true>(e, t, T);
   hand_over();
   __syncthreads();
@@ -1181,9 +1190,8 @@ __device__ inline void particles_body(const StepArgs& a, VB vb, int T_emit) {
   acc_flush(acc, a.acc_rows, vb.id, a.acc_stride);
 }
 
-// The first kEmitters workgroups only emit (see emit_publish), the others push
-// and inject.
-static_assert(kEmitters % 8 == 0, "the workgroups after them keep their XCD");
+// The leading workgroups only emit (see emit_publish), the others push and
+// inject, each on the XCD of its index among them.
 // Bound: the load path and its latency (17 divergent 16-byte gathers per
 // superparticle on packed records), so waves in flight count.  On packed
 // records the push and the injection fit 96 registers without spills (maps
@@ -1197,29 +1205,27 @@ static_assert(kEmitters % 8 == 0, "the workgroups after them keep their XCD");
 template <bool F32, bool PK, int W>
 __global__ void __launch_bounds__(kBlock, W) k_particles(StepArgs a, EmitArgs e) {
   if (gate_closed(a.gate)) return;
-  if (blockIdx.x < kEmitters)
-    emit_publish(e, (int)blockIdx.x, emitters(e.m));
-  else
-    particles_body<F32, PK>(a, VB{(int)blockIdx.x - kEmitters, (int)gridDim.x - kEmitters},
-                            emitters(a.m));
+  const int T = emitters(a.m), lead = kXcds * T, g = (int)blockIdx.x;
+  if (g < lead) {
+    if (g % kXcds == 0) emit_publish(e, g / kXcds, T);
+    return;
+  }
+  particles_body<F32, PK>(a, VB{g - lead, (int)gridDim.x - lead}, T);
 }
 
-// The emitting workgroups of all instances, one each (the other instances'
-// pushes hide its trips; eight each took 1171 us instead of 1155 for ten
-// steps of six tips), come first, in a whole round of the XCDs, so that they
-// are resident before any workgroup that waits for one of them.
-__host__ __device__ inline int batch_emitters(const BatchMap& map) {
-  return (map.n_seg + 7) / 8 * 8;
-}
+// The emitting workgroups of all instances come first, one each (the other
+// instances' pushes hide its trips; eight each took 1171 us instead of 1155
+// for ten steps of six tips).
+__host__ __device__ inline int batch_lead(const BatchMap& map) { return kXcds * map.n_seg; }
 
 template <bool F32, bool PK>
 __global__ void __launch_bounds__(kBlock, 4) k_particles_b(const StepArgs* A,
                                                             const EmitArgs* E,
                                                             BatchMap map) {
-  const int lead = batch_emitters(map);
+  const int lead = batch_lead(map);
   if ((int)blockIdx.x < lead) {
-    if ((int)blockIdx.x >= map.n_seg) return;
-    const EmitArgs e = batch_args(E, map.inst[blockIdx.x]);
+    if (blockIdx.x % kXcds) return;
+    const EmitArgs e = batch_args(E, map.inst[blockIdx.x / kXcds]);
     if (!gate_closed(e.gate)) emit_publish(e, 0, 1);
     return;
   }
@@ -1397,7 +1403,7 @@ hipError_t launch_particles_b(const StepArgs* A, const EmitArgs* E, const BatchM
                               int f32, int packed, hipStream_t s) {
   const auto kern = packed ? (f32 ? k_particles_b<true, true> : k_particles_b<false, true>)
                            : (f32 ? k_particles_b<true, false> : k_particles_b<false, false>);
-  hipLaunchKernelGGL(kern, dim3(batch_emitters(map) + map.off[map.n_seg]), dim3(kBlock), 0,
+  hipLaunchKernelGGL(kern, dim3(batch_lead(map) + map.off[map.n_seg]), dim3(kBlock), 0,
                      s, A, E, map);
   return hipGetLastError();
 }
@@ -1426,7 +1432,7 @@ hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
   StepArgs b = a;
   b.g_push = g_push;
   hipLaunchKernelGGL(particles_kernel(a.f32, a.m.tc != nullptr, waves),
-                     dim3(kEmitters + g_push + g_inj), dim3(kBlock), 0, s, b, e);
+                     dim3(kXcds * emitters(a.m) + g_push + g_inj), dim3(kBlock), 0, s, b, e);
   return hipGetLastError();
 }
 hipError_t launch_seed_build(const DevMesh& m, int grid, hipStream_t s) {
