@@ -13,6 +13,8 @@ constexpr int kAmgCoarseMax = 512;  // the coarsest operator is inverted densely
 // A last smoothed level of at most this many rows is applied with all below
 // it as one dense matrix (see AmgDev): three dependent launches near the
 // floor (18 us at 1,089 rows) against one product that reads 5 to 16 MB.
+// The price is memory: 12 bytes an entry (FP64 and FP32), so up to 50 MB a
+// handle where the inverse of at most 512 rows took 3.
 constexpr int kAmgDenseMax = 2048;
 
 // A sparse matrix of the hierarchy.  lpr = 1: the sliced ELLPACK layout of

@@ -304,9 +304,9 @@ hipError_t solve_start(pic_mesh* h, fp::CgArgs& a, int spec, hipStream_t s,
   a.report = h->cg_report_dev;
   const int64_t seq = ++h->cg_seq;
   // A step solve after one that needed no iteration: its warm start is
-  // expected to meet the tolerance at once, so the first pass leaves x and
-  // u to a launch made only if it does not (and clears the charges for the
-  // next step as it reads them).
+  // expected to meet the tolerance at once, so the first pass leaves x to a
+  // launch made only if it does not (and clears the charges for the next
+  // step as it reads them).
   a.lean = spec <= 0 && a.incremental && !a.rhs && a.bprev && a.next_stats &&
                    a.charge && (const int64_t*)a.clear_charge == a.charge
                ? 1
@@ -329,8 +329,8 @@ void prof_end(pic_mesh* h, hipStream_t s);
 constexpr int kProfNoCount = 0x100;  // time the bracket, count no launch
 
 // Waits for the report of the first round and enqueues further rounds (a
-// true-residual re-check, or twice as many iterations as the last round)
-// until the solve has ended.  *first_state: the state the first report
+// true-residual re-check, or more iterations, see below) until the solve has
+// ended.  *first_state: the state the first report
 // carried.  Further rounds are timed as solve time while profiling.
 hipError_t solve_finish(pic_mesh* h, const fp::CgArgs& a, int spec,
                         int64_t seq, hipStream_t s, int64_t* iters_out,

@@ -19,8 +19,8 @@
 // so the sums below do not depend on scheduling, with their coordinates
 // copied in that order); k_face_charge_cut: one wave per face over the
 // atom cells near it; k_atom_charge_cut: one wave per atom over the face
-// cells near it.  Sums run over the cells in a fixed order and inside a
-// cell in index order.
+// cells near it.  Every lane sums the kept pairs that fall to it by their
+// place in that order, and the lanes are summed by a fixed tree.
 #include "charge.h"
 
 #include <algorithm>
@@ -492,8 +492,9 @@ __device__ inline void load4(const double* xyz, const int32_t (&p)[4], double (&
 // root, exponential and divisions, so those are taken 64 stacked pairs at a
 // time.  heavy(d2, p) is called with every lane that has a pair, at one place
 // per walk: its code is long, and a first call fetches it from memory.  The
-// charge of a 48^2 x 96 tip's faces and atoms (eight launches): 97 us with
-// each lane taking its own pairs and workgroup barriers, 89 so.
+// charge of a 48^2 x 96 tip's faces and atoms (eight launches): 98 us with
+// each lane taking its own pairs and workgroup barriers, 90 so (123 and 115 on
+// another machine; a surface's first call 433 and 417).
 constexpr int kStack = 64 + 256;  // what a trip left and what it adds
 struct PairStack {
   double d2[kStack];

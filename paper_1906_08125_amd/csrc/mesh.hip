@@ -891,10 +891,11 @@ pic_status build_mesh(const pic_mesh_desc* d, pic_mesh* h, std::string& msg) {
   h->grid_inj = std::max(8, h->n_cu * 2);
   h->grid_fb = 64;
   h->step_inj = std::min(h->grid_inj, std::max(8, (h->n_cu / 2) - (h->n_cu / 2) % 8));
-  // One workgroup per resident slot: a push grid that fills the chip in a
-  // single round has no tail of late workgroups (measured on the production
-  // tip: 3 resident per CU, 91 us per push against 100 us for 8 per CU and
-  // 107 us for 4), and fewer injecting workgroups queue behind it.
+  // One workgroup per resident place: a push grid that fills the chip in a
+  // single round has no tail of late workgroups, and fewer injecting ones queue
+  // behind it.  (Measured on the production tip when full records let three
+  // run per CU: 91 us per push, 100 with 8 per CU and 107 with 4.  Packed
+  // records let four or five run: 61 to 66 us.)
   for (int f32 = 0; f32 < 2; ++f32)
     for (int five = 0; five < 2; ++five) {
       const int per_cu = std::max(1, particle_blocks_per_cu(f32, packed, five ? 5 : 4));

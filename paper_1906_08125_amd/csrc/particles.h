@@ -107,8 +107,8 @@ hipError_t launch_begin(const EmitArgs& a, int grid, hipStream_t s);
 // or not, built for so many waves per SIMD) resident on one compute unit at
 // once, by the runtime's occupancy calculator (0 on error).
 int particle_blocks_per_cu(int f32, int packed, int waves);
-// e: the step's emission, computed by workgroup 0 while the others push (the
-// injecting workgroups wait for it).  waves: 4, or 5 (packed records only;
+// e: the step's emission, computed by the first workgroups while the others
+// push (the injecting ones wait for it).  waves: 4, or 5 (packed records only;
 // else taken as 4).
 hipError_t launch_particles(const StepArgs& a, const EmitArgs& e, int g_push,
                             int g_inj, int waves, hipStream_t s);

@@ -630,7 +630,7 @@ __device__ inline void face_field(const DevMesh& m, const void* E, int f32,
 
 
 // ---------------------------------------------------------------------------
-// Emission counts (one workgroup): per emitting face the centroid field
+// Emission counts: per emitting face the centroid field
 // ((E_a + E_b) + E_c)/3, the FN current when the field pulls electrons out of
 // the metal, Eq. nsp and the rounding of Eq. rnd_nsp; an exclusive scan of
 // the counts gives every new particle its slot.
@@ -780,7 +780,7 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a) {
 // charges.
 __device__ inline void begin_body(const EmitArgs& a, VB vb) {
   if (gate_closed(a.gate)) return;
-  if (vb.id == 0) {  // dispatched first: the emission path is the longest
+  if (vb.id == 0) {
     int64_t* s64 = reinterpret_cast<int64_t*>(a.stats);
     const int ns = (int)(sizeof(pic_step_stats) / sizeof(int64_t));
     if (threadIdx.x < ns) s64[threadIdx.x] = 0;

@@ -1487,10 +1487,7 @@ __global__ void __launch_bounds__(kCgBlock) k_amg_upd_b(AmgBatch b) {
 
 namespace {
 
-// Workgroups for a level kernel over n rows: the full solver grid on the
-// finest level (its kernels also reduce over that grid), fewer below, so
-// that the small coarse passes do not launch and drain hundreds of idle
-// workgroups.
+// The coarsest level's matrix and vectors in the arithmetic of T.
 template <typename T>
 struct CoarseVecs {
   const T* inv;
