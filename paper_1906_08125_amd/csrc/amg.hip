@@ -57,36 +57,66 @@ HCsr transpose(const HCsr& A) {
   return T;
 }
 
+// A row being summed: values by column, the columns in use sorted on demand.
+class RowSum {
+ public:
+  explicit RowSum(int64_t columns) : at_(columns, Cell{-1, 0.0}) {}
+  void open(int64_t row) {
+    row_ = row;
+    cols_.clear();
+  }
+  void add(int32_t j, double v) {
+    Cell& c = at_[j];
+    if (c.row != row_) {
+      c = Cell{row_, 0.0};
+      cols_.push_back(j);
+    }
+    c.v += v;
+  }
+  const std::vector<int32_t>& sorted() {
+    std::sort(cols_.begin(), cols_.end());
+    return cols_;
+  }
+  double operator[](int32_t j) const { return at_[j].v; }
+
+ private:
+  struct Cell {
+    int64_t row;
+    double v;
+  };
+  std::vector<Cell> at_;
+  std::vector<int32_t> cols_;
+  int64_t row_ = -1;
+};
+
+// Room for a matrix whose first rows are done, by their length.
+void reserve_like(HCsr& M, int64_t done) {
+  if (done != M.n / 32 || done == 0) return;
+  const size_t want = M.ci.size() / (size_t)done * (size_t)M.n;
+  M.ci.reserve(want + want / 8);
+  M.v.reserve(want + want / 8);
+}
+
 // C = A B (Gustavson, dense accumulator over the columns of B).
 HCsr multiply(const HCsr& A, const HCsr& B) {
   HCsr C;
   C.n = A.n;
   C.m = B.m;
   C.rp.assign(C.n + 1, 0);
-  std::vector<double> acc(B.m, 0.0);
-  std::vector<int64_t> mark(B.m, -1);
-  std::vector<int32_t> cols;
+  RowSum row(B.m);
   for (int64_t i = 0; i < A.n; ++i) {
-    cols.clear();
+    row.open(i);
     for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p) {
       const int32_t k = A.ci[p];
       const double a = A.v[p];
-      for (int64_t q = B.rp[k]; q < B.rp[k + 1]; ++q) {
-        const int32_t j = B.ci[q];
-        if (mark[j] != i) {
-          mark[j] = i;
-          acc[j] = 0.0;
-          cols.push_back(j);
-        }
-        acc[j] += a * B.v[q];
-      }
+      for (int64_t q = B.rp[k]; q < B.rp[k + 1]; ++q) row.add(B.ci[q], a * B.v[q]);
     }
-    std::sort(cols.begin(), cols.end());
-    for (int32_t j : cols) {
+    for (int32_t j : row.sorted()) {
       C.ci.push_back(j);
-      C.v.push_back(acc[j]);
+      C.v.push_back(row[j]);
     }
     C.rp[i + 1] = (int64_t)C.ci.size();
+    reserve_like(C, i + 1);
   }
   return C;
 }
@@ -98,6 +128,8 @@ HCsr symmetrize(const HCsr& A) {
   S.n = A.n;
   S.m = A.m;
   S.rp.assign(S.n + 1, 0);
+  S.ci.reserve(A.ci.size());
+  S.v.reserve(A.v.size());
   for (int64_t i = 0; i < A.n; ++i) {
     int64_t p = A.rp[i], q = T.rp[i];
     const int64_t pe = A.rp[i + 1], qe = T.rp[i + 1];
@@ -198,35 +230,27 @@ HCsr smoothed_p(const HCsr& A, const std::vector<double>& d,
   P.n = A.n;
   P.m = nc;
   P.rp.assign(A.n + 1, 0);
-  std::vector<std::pair<int32_t, double>> row;
+  RowSum row(nc);
   for (int64_t i = 0; i < A.n; ++i) {
-    row.clear();
-    row.push_back({agg[i], 1.0});
+    row.open(i);
+    row.add(agg[i], 1.0);
     const double s = omega / d[i];
-    for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p)
-      row.push_back({agg[A.ci[p]], -s * A.v[p]});
-    std::stable_sort(row.begin(), row.end(),
-              [](const std::pair<int32_t, double>& a,
-                 const std::pair<int32_t, double>& b) { return a.first < b.first; });
-    for (size_t k = 0; k < row.size();) {
-      const int32_t j = row[k].first;
-      double v = 0.0;
-      while (k < row.size() && row[k].first == j) v += row[k++].second;
-      if (v != 0.0) {
-        P.ci.push_back(j);
-        P.v.push_back(v);
-      }
+    for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p) row.add(agg[A.ci[p]], -s * A.v[p]);
+    for (int32_t j : row.sorted()) {
+      if (row[j] == 0.0) continue;
+      P.ci.push_back(j);
+      P.v.push_back(row[j]);
     }
     P.rp[i + 1] = (int64_t)P.ci.size();
+    reserve_like(P, i + 1);
   }
   return P;
 }
 
 // (I - omega D^-1 A) P from P and AP = A P (rows sorted; the pattern of P
 // lies in that of AP, whose rows hold a_ii P_i).
-HCsr smooth_again(const HCsr& P, const HCsr& AP, const std::vector<double>& d,
-                  double omega) {
-  HCsr S = AP;
+HCsr smooth_again(const HCsr& P, HCsr AP, const std::vector<double>& d, double omega) {
+  HCsr S = std::move(AP);
   for (int64_t i = 0; i < S.n; ++i) {
     const double s = -omega / d[i];
     int64_t q = P.rp[i];
@@ -324,24 +348,34 @@ std::vector<double> dense_cycle(const HCsr& A, const std::vector<double>& d,
       const double v = inv[k * nc + q];
       for (int64_t p = Rs.rp[q]; p < Rs.rp[q + 1]; ++p) M[k * n + Rs.ci[p]] += v * Rs.v[p];
     }
+  // (symmetric: the upper half, then mirrored by blocks -- a column of the
+  // whole matrix at a time misses the cache at every entry)
   std::vector<double> C(n * n, 0.0);
   for (int64_t i = 0; i < n; ++i) {
     double* c = &C[i * n];
-    for (int64_t p = Ps.rp[i]; p < Ps.rp[i + 1]; ++p) {
-      const double v = Ps.v[p];
-      const double* m = &M[(int64_t)Ps.ci[p] * n];
-      for (int64_t j = 0; j < n; ++j) c[j] += v * m[j];
+    int64_t p = Ps.rp[i];
+    const int64_t pe = Ps.rp[i + 1];
+    auto row = [&](int64_t q) { return &M[(int64_t)Ps.ci[q] * n]; };
+    for (; p + 4 <= pe; p += 4) {  // (four rows per pass over c)
+      const double *m0 = row(p), *m1 = row(p + 1), *m2 = row(p + 2), *m3 = row(p + 3);
+      const double v0 = Ps.v[p], v1 = Ps.v[p + 1], v2 = Ps.v[p + 2], v3 = Ps.v[p + 3];
+      for (int64_t j = i; j < n; ++j)
+        c[j] = (((c[j] + v0 * m0[j]) + v1 * m1[j]) + v2 * m2[j]) + v3 * m3[j];
     }
-    for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p)
-      c[A.ci[p]] -= omega * omega * A.v[p] / (d[i] * d[A.ci[p]]);
+    for (; p < pe; ++p) {
+      const double* m = row(p);
+      for (int64_t j = i; j < n; ++j) c[j] += Ps.v[p] * m[j];
+    }
+    for (int64_t q = A.rp[i]; q < A.rp[i + 1]; ++q)
+      if (A.ci[q] >= i) c[A.ci[q]] -= omega * omega * A.v[q] / (d[i] * d[A.ci[q]]);
     c[i] += 2.0 * omega / d[i];
   }
-  // exact symmetry of the applied operator
-  for (int64_t i = 0; i < n; ++i)
-    for (int64_t j = i + 1; j < n; ++j) {
-      const double v = 0.5 * (C[i * n + j] + C[j * n + i]);
-      C[i * n + j] = C[j * n + i] = v;
-    }
+  constexpr int64_t kB = 64;
+  for (int64_t i0 = 0; i0 < n; i0 += kB)
+    for (int64_t j0 = i0; j0 < n; j0 += kB)
+      for (int64_t i = i0; i < std::min(i0 + kB, n); ++i)
+        for (int64_t j = std::max(j0, i + 1); j < std::min(j0 + kB, n); ++j)
+          C[j * n + i] = C[i * n + j];
   return C;
 }
 
@@ -410,10 +444,11 @@ hipError_t amg_build(const DevMesh& m, hipStream_t s,
     if (nc >= Al.n) break;  // no coarsening possible
     omega.push_back(4.0 / (3.0 * lambda_max(Al, dl)));
     const HCsr P = smoothed_p(Al, dl, agg, nc, omega.back());
-    const HCsr AP = multiply(Al, P);
-    Ps.push_back(smooth_again(P, AP, dl, omega.back()));
+    HCsr AP = multiply(Al, P);
+    HCsr next = symmetrize(multiply(transpose(P), AP));
+    Ps.push_back(smooth_again(P, std::move(AP), dl, omega.back()));
     Rs.push_back(transpose(Ps.back()));
-    A.push_back(symmetrize(multiply(transpose(P), AP)));
+    A.push_back(std::move(next));  // (Al and dl end here)
     theta *= 0.5;
   }
   for (const auto* v : {&A, &Ps, &Rs})
