@@ -144,15 +144,21 @@ void* mesh_mem(pic_mesh* h, size_t bytes, hipError_t& err) {
 bool pack_records(const std::vector<TetGeom>& tg, double lam_c,
                   std::vector<double>& maps, std::vector<TetPack>& tc) {
   const size_t T = tg.size();
-  int n = 0;
+  int n = 0, k = 0;
   maps.assign((size_t)kMapMax * kMapLen, 0.0);
   tc.resize(T);
   for (size_t t = 0; t < T; ++t) {
     const TetGeom& g = tg[t];
-    int k = 0;
-    while (k < n && std::memcmp(&maps[(size_t)k * kMapLen], g.m, sizeof g.m) != 0) ++k;
-    if (k == n) {
+    // (the search starts behind the tet before's map: a cube's six follow one
+    // another)
+    int tried = 0;
+    for (; tried < n; ++tried) {
+      k = k + 1 < n ? k + 1 : 0;
+      if (std::memcmp(&maps[(size_t)k * kMapLen], g.m, sizeof g.m) == 0) break;
+    }
+    if (tried == n) {
       if (n == kMapMax) return false;
+      k = n;
       double* e = &maps[(size_t)n++ * kMapLen];
       std::memcpy(e, g.m, sizeof g.m);
       for (int r = 0; r < 3; ++r) {
