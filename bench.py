@@ -35,28 +35,33 @@ PUSH_TIMING_EVERY = 5
 # write 1.0000).  A figure is reported only while the sources it was taken
 # on are unchanged and the run's load matches the one profiled.
 # The dominant kernel (FP64 push) per launch at the production workload
-# (profiles/pic_step_fp64_production_tip.md):
-PUSH_TRAFFIC = dict(bytes=220.4e6, read=155.9e6, written=64.6e6, live=992_300,
+# (profiles/performance_cases_kernel_times.md):
+PUSH_TRAFFIC = dict(bytes=198.4e6, read=133.4e6, written=65.0e6, live=992_300,
                     sources=("paper_1906_08125_amd/csrc/particles.hip",
-                             "paper_1906_08125_amd/csrc/common.h"),
-                    sha256=("5770ae084b9f9585a4b0d54bd5d8e7f9e881e1d3cf0fe7c783617cdb6aa6d220",
-                            "df664d921b2048d0e38d5de9ccce0edb99bc52cb2a034c6b94b3b69f07cb3843"))
+                             "paper_1906_08125_amd/csrc/common.h",
+                             "paper_1906_08125_amd/csrc/handover.h"),
+                    sha256=("3d635ead40679aec1fcc001a8b27ed4446eeba1cd961dd9f96cf81e3760ea013",
+                            "c91bd269b3923d27025534e77b088a54043f1da9e85776b8f7cfd63fdb663134",
+                            "01e6d1386d1492bd3b94adb51c5b22214bae6e104122dcb199001c6009e445fd"))
 
-# One step of the 32-instance batch (every dispatch between consecutive
-# batched particle launches, averaged over the timed steps;
-# profiles/pic_batch_step_32_instances.md):
-BATCH_TRAFFIC = dict(bytes=3345.7e6, read=2717.9e6, written=627.8e6,
+# One step of the 32-instance batch (every dispatch of the timed call, averaged
+# over its steps; profiles/performance_cases_kernel_times.md):
+BATCH_TRAFFIC = dict(bytes=2528.2e6, read=1954.4e6, written=573.8e6,
                      live=3_371_102,
                      sources=("paper_1906_08125_amd/csrc/particles.hip",
                               "paper_1906_08125_amd/csrc/solver.hip",
                               "paper_1906_08125_amd/csrc/amg.hip",
                               "paper_1906_08125_amd/csrc/api.hip",
-                              "paper_1906_08125_amd/csrc/common.h"),
-                     sha256=("5770ae084b9f9585a4b0d54bd5d8e7f9e881e1d3cf0fe7c783617cdb6aa6d220",
-                             "48dc7dedd15d958bcf9d263391b89c760b31dc43d7838b22276f98ba3273aebf",
-                             "b7134060afc401da45819d5e18d224beee6fb57e6660ef3331fb9b6bb80d9af9",
-                             "e86b16e48b77a312e297ff1664407f4a6d70ef7381df77a5ce39d568443292e9",
-                             "df664d921b2048d0e38d5de9ccce0edb99bc52cb2a034c6b94b3b69f07cb3843"))
+                              "paper_1906_08125_amd/csrc/sort.hip",
+                              "paper_1906_08125_amd/csrc/common.h",
+                              "paper_1906_08125_amd/csrc/handover.h"),
+                     sha256=("3d635ead40679aec1fcc001a8b27ed4446eeba1cd961dd9f96cf81e3760ea013",
+                             "10de1d8ca08ad741e660b9f38c2d88a3bc2f72efeda2e9e12b3fb4c60343548e",
+                             "1a65c927af1c7c176df81ee06333e0ab12113ac5e62ab5a4dbe60e8f3632a8d7",
+                             "a9f10ae12b6cdb89f559a0f84287968d08b4b755bb29f42fdda6d57c0b1ff88a",
+                             "095351ec2ce0c9c606cef08495e0568b09e604871154ce9830ec4e9e62b1be11",
+                             "c91bd269b3923d27025534e77b088a54043f1da9e85776b8f7cfd63fdb663134",
+                             "01e6d1386d1492bd3b94adb51c5b22214bae6e104122dcb199001c6009e445fd"))
 
 
 def measured_traffic(rec, live):
