@@ -493,8 +493,8 @@ __device__ inline void load4(const double* xyz, const int32_t (&p)[4], double (&
 // time.  heavy(d2, p) is called with every lane that has a pair, at one place
 // per walk: its code is long, and a first call fetches it from memory.  The
 // charge of a 48^2 x 96 tip's faces and atoms (eight launches): 98 us with
-// each lane taking its own pairs and workgroup barriers, 90 so (123 and 115 on
-// another machine; a surface's first call 433 and 417).
+// each lane taking its own pairs and workgroup barriers, 90 so (calls behind one
+// another; one waited for takes 30 more, a surface's first call 433 and 417).
 constexpr int kStack = 64 + 256;  // what a trip left and what it adds
 struct PairStack {
   double d2[kStack];
